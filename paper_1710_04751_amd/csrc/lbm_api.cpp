@@ -364,9 +364,11 @@ lbm_status lbm_init_macros(lbm_handle* h, const float* ux, const float* uy, cons
     if (!h) return fail(LBM_ERR_ARG, "null handle");
     if (h->owner && !batch_allows_reinit(h->owner))
         return fail(LBM_ERR_STATE, "batch member re-initialised at an odd batch step");
-    // red()[10..13]: scratch of the staggered momentum sums
+    // red()[10..13]: the staggered momentum sums; the profiles' scratch holds
+    // the partial ones
     hipError_t e = launch_init_macros((Prec)h->p.precision, h->p.thermal_q, h->geom, h->lay.pl,
-                                      h->buf(0), ux, uy, uz, T, h->red() + 10, h->c, h->stream);
+                                      h->buf(0), ux, uy, uz, T, h->red() + 10, h->nu_hot(),
+                                      (int64_t)2 * h->p.ny * h->p.nz, h->c, h->stream);
     if (e != hipSuccess) return hip_fail(e, "init_macros");
     h->cur = 0;
     h->steps = 0;

@@ -60,10 +60,12 @@ hipError_t launch_fill_zero(void* ptr, size_t bytes, hipStream_t s);
 // scalar source, writes the scalar equilibrium at T = -R/2 into st.
 hipError_t launch_init_rest(Prec p, int qt, const Geom& g, PopLay pl, void* state,
                             size_t state_bytes, StateBuf st, const Coefs& c, hipStream_t s);
-// stag: device scratch of 4 doubles (16-byte aligned) for the staggered sums
+// stag: 4 doubles of device memory for the staggered sums; scratch: device
+// memory of scratch_doubles >= 4 doubles for the blocks' partial sums
 hipError_t launch_init_macros(Prec p, int qt, const Geom& g, PopLay pl, StateBuf st,
                               const float* ux, const float* uy, const float* uz, const float* T,
-                              double* stag, const Coefs& c, hipStream_t s);
+                              double* stag, double* scratch, int64_t scratch_doubles,
+                              const Coefs& c, hipStream_t s);
 hipError_t launch_macros(Prec p, int qt, const Geom& g, PopLay pl, StateBuf st, void* rho,
                          void* ux, void* uy, void* uz, void* T, bool fp64, const Coefs& c,
                          hipStream_t s);

@@ -27,33 +27,71 @@ __global__ void k_fill_zero(uint4* __restrict__ p, size_t n16) {
 }
 
 // Staggered sums of an initial state: sum (-1)^x ux, sum (-1)^y uy,
-// sum (-1)^z uz and sum (-1)^z (T - T_ref) (FP64, added into sums[0..3]).
-__global__ void __launch_bounds__(256) k_stagger_sums(const float* ux, const float* uy,
-                                                      const float* uz, const float* T,
-                                                      double T_ref, Geom g, double* sums) {
-    __shared__ double red[4][256];
-    const int64_t ncell = (int64_t)g.nx * g.ny * g.nz;
-    const int64_t c = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+// sum (-1)^z uz and sum (-1)^z (T - T_ref), FP64, in a fixed order and without
+// atomics: each block adds the rows its waves walk (wave w of the grid takes
+// rows w, w + waves, ...; lane l the cells l, l + 64, ...) and writes four
+// partial sums, which k_stagger_total adds up.  Bound by reading the fields
+// once.  One block per 256 cells adding into four shared words by FP64 atomics
+// had been bound by those: 397 us at 128^3 (25 ms at 512^3) against
+// about 18 us for the two kernels (a whole start at 128^3, with the projection
+// and the first macroscopic fields: 492 -> 114 us).
+__device__ __forceinline__ double wave_add(double v) {
+    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
+    return v;
+}
+
+constexpr int kStagWaves = 4;  // waves per block
+
+__global__ void __launch_bounds__(64 * kStagWaves)
+k_stagger_sums(const float* __restrict__ ux, const float* __restrict__ uy,
+               const float* __restrict__ uz, const float* __restrict__ T, double T_ref, Geom g,
+               double* __restrict__ part) {
+    __shared__ double red[kStagWaves][4];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const uint32_t rows = (uint32_t)g.ny * (uint32_t)g.nz;
+    // the loops run over lane and row strides whose x parity is the lane's
+    const double sx = (lane & 1) ? -1.0 : 1.0;
     double a[4] = {0.0, 0.0, 0.0, 0.0};
-    if (c < ncell) {
-        const int x = (int)(c % g.nx);
-        const int y = (int)((c / g.nx) % g.ny);
-        const int z = (int)(c / ((int64_t)g.nx * g.ny));
-        if (ux) a[0] = (x & 1) ? -(double)ux[c] : (double)ux[c];
-        if (uy) a[1] = (y & 1) ? -(double)uy[c] : (double)uy[c];
-        if (uz) a[2] = (z & 1) ? -(double)uz[c] : (double)uz[c];
-        const double t = (T ? (double)T[c] : 0.0) - T_ref;
-        a[3] = (z & 1) ? -t : t;
+    for (uint32_t row = blockIdx.x * kStagWaves + wave; row < rows;
+         row += gridDim.x * kStagWaves) {
+        const uint32_t z = row / (uint32_t)g.ny, y = row - z * (uint32_t)g.ny;
+        const double sy = (y & 1) ? -1.0 : 1.0, sz = (z & 1) ? -1.0 : 1.0;
+        const int64_t base = (int64_t)row * g.nx;
+        double r[4] = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll 4
+        for (int x = lane; x < g.nx; x += 64) {
+            const int64_t c = base + x;
+            if (ux) r[0] += (double)ux[c];
+            if (uy) r[1] += (double)uy[c];
+            if (uz) r[2] += (double)uz[c];
+            r[3] += (T ? (double)T[c] : 0.0) - T_ref;
+        }
+        a[0] += sx * r[0];
+        a[1] += sy * r[1];
+        a[2] += sz * r[2];
+        a[3] += sz * r[3];
     }
-    for (int k = 0; k < 4; ++k) red[k][threadIdx.x] = a[k];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        const double t = wave_add(a[k]);
+        if (lane == 0) red[wave][k] = t;
+    }
     __syncthreads();
-    for (int w = 128; w > 0; w >>= 1) {
-        if ((int)threadIdx.x < w)
-            for (int k = 0; k < 4; ++k) red[k][threadIdx.x] += red[k][threadIdx.x + w];
-        __syncthreads();
+    if (threadIdx.x < 4) {
+        double t = red[0][threadIdx.x];
+        for (int w = 1; w < kStagWaves; ++w) t += red[w][threadIdx.x];
+        part[4 * (int64_t)blockIdx.x + threadIdx.x] = t;
     }
-    if (threadIdx.x == 0)
-        for (int k = 0; k < 4; ++k) atomicAdd(&sums[k], red[k][0]);
+}
+
+// One block of 4 waves: wave k adds entry k of the blocks' partial sums.
+__global__ void __launch_bounds__(256)
+k_stagger_total(const double* __restrict__ part, int blocks, double* __restrict__ sums) {
+    const int lane = threadIdx.x & 63, k = threadIdx.x >> 6;
+    double t = 0.0;
+    for (int b = lane; b < blocks; b += 64) t += part[4 * (int64_t)b + k];
+    t = wave_add(t);
+    if (lane == 0) sums[k] = t;
 }
 
 // Equilibrium populations of (rho = 1, u, T), with the staggered part of
@@ -332,12 +370,19 @@ hipError_t launch_init_rest(Prec p, int qt, const Geom& g, PopLay pl, void* stat
 
 hipError_t launch_init_macros(Prec p, int qt, const Geom& g, PopLay pl, StateBuf st,
                               const float* ux, const float* uy, const float* uz, const float* T,
-                              double* stag, const Coefs& c, hipStream_t s) {
+                              double* stag, double* scratch, int64_t scratch_doubles,
+                              const Coefs& c, hipStream_t s) {
     const int64_t ncell = (int64_t)g.nx * g.ny * g.nz;
-    hipError_t e = launch_fill_zero(stag, 32, s);
+    // about 8 blocks per compute unit, as many as there are rows and scratch for
+    const int64_t rows = (int64_t)g.ny * g.nz;
+    const int blocks = (int)std::max<int64_t>(
+        1, std::min<int64_t>({2048, (rows + kStagWaves - 1) / kStagWaves, scratch_doubles / 4}));
+    hipLaunchKernelGGL(k_stagger_sums, dim3(blocks), dim3(64 * kStagWaves), 0, s, ux, uy, uz, T,
+                       c.T_ref, g, scratch);
+    hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(k_stagger_sums, dim3(blocks_for(ncell, 256)), dim3(256), 0, s, ux, uy, uz,
-                       T, c.T_ref, g, stag);
+    hipLaunchKernelGGL(k_stagger_total, dim3(1), dim3(256), 0, s, (const double*)scratch, blocks,
+                       stag);
     e = hipGetLastError();
     if (e != hipSuccess) return e;
     LBM_DISPATCH_PQ(p, qt, {
