@@ -74,7 +74,7 @@ k_batch_step(const DevCav* __restrict__ cavs, const uint32_t* __restrict__ tiles
         uint32_t seed = 0;
         if constexpr (std::is_same<S, _Float16>::value) seed = keys[c] + key_off;
         update_cell<R, S, QT, HG>((const S*)C.F[parity], (S*)C.F[1 - parity], x, y, z,
-                                  yt * C.rows, C.nx, C.ny, C.nz, C.pl.gs, coef_of<R>(C), seed);
+                                  yt * C.rows, z, C.nx, C.ny, C.nz, C.pl.gs, coef_of<R>(C), seed);
     }
 }
 

@@ -31,7 +31,7 @@ Layout layout_of(const lbm_params* p);
 // log2 of the rows per population run: the largest power of two R with
 // R*nx values of one population within 32 KB, and R no more than the rows.
 int run_rows_log2(const lbm_params* p);
-void default_block(int nx, int* bx, int* by);
+void default_block(int64_t ncell, int* bx, int* by);
 // Create a handle over caller memory without touching the device.
 lbm_status make_handle(const lbm_params* p, void* workspace, size_t bytes, void* stream,
                        lbm_handle** out);

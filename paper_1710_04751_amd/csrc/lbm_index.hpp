@@ -73,6 +73,45 @@ __host__ __device__ inline uint32_t row_at(const Window& w, uint32_t r) {
     return ((r >> w.gs) - w.g0) * w.glen + (r & w.gmask) * w.nx;
 }
 
+// Quotient t / d for t < d + 1024 with the divisor's magic number
+// small_magic(d): exact, since for d < 1024 both t and d are below 2^11 and
+// t (magic d - 2^22) < t d < 2^22; from 1024 on the quotient is 0 or 1.
+__host__ __device__ inline uint32_t small_magic(uint32_t d) {
+    return d < 1024 ? ((1u << 22) + d - 1) / d : 0;
+}
+__host__ __device__ inline uint32_t small_div(uint32_t t, uint32_t d, uint32_t magic) {
+    return magic ? (t * magic) >> 22 : (t >= d ? 1u : 0u);
+}
+
+// Cells of a block of consecutive cells in (z, y, x) order: `FlatStart` is
+// the block's first cell c0 (the same for every lane), flat_cell the cell of
+// lane tid < 1024.  mx, my: small_magic(nx), small_magic(ny).  Past the last
+// cell z >= nz.  The block's rows start at (z0, y0), so window_of(z0, y0, ..)
+// holds all it addresses: it spans at most 1024 / nx + 2 rows, and more than
+// ny of them only where ny and nx are so small that offsets stay far below
+// 32 bits.
+struct FlatStart {
+    uint32_t x0, y0, z0;
+};
+__host__ __device__ inline FlatStart flat_start(uint32_t c0, int nx, int ny) {
+    FlatStart f;
+    const uint32_t row = c0 / (uint32_t)nx;
+    f.x0 = c0 - row * (uint32_t)nx;
+    f.z0 = row / (uint32_t)ny;
+    f.y0 = row - f.z0 * (uint32_t)ny;
+    return f;
+}
+__host__ __device__ inline void flat_cell(const FlatStart& f, uint32_t tid, int nx, int ny,
+                                          uint32_t mx, uint32_t my, int* x, int* y, int* z) {
+    const uint32_t t = f.x0 + tid;
+    const uint32_t dr = small_div(t, (uint32_t)nx, mx);
+    *x = (int)(t - dr * (uint32_t)nx);
+    const uint32_t yy = f.y0 + dr;
+    const uint32_t dz = small_div(yy, (uint32_t)ny, my);
+    *y = (int)(yy - dz * (uint32_t)ny);
+    *z = (int)(f.z0 + dz);
+}
+
 // Wall flags of one cell.
 struct CellAt {
     int x, y, z;

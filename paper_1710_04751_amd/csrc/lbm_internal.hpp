@@ -11,7 +11,9 @@ namespace lbm {
 struct Geom {
     int32_t nx, ny, nz;
     int32_t bx, by;           // threads per block along x, y
-    int32_t tiles_x, tiles_y; // blocks per row / per plane
+    int32_t tiles_x, tiles_y; // blocks per row / per plane (0: blocks of bx * by
+                              // consecutive cells)
+    uint32_t mx, my;          // idx::small_magic of nx and ny
     int32_t gs;               // log2 of the rows per population run (PopLay)
 };
 

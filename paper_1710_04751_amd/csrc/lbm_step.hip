@@ -42,40 +42,54 @@ __device__ __forceinline__ uint32_t xcd_tile(uint32_t b, uint32_t nb) {
 }
 
 struct CellPos {
-    int x, y, z, y0;  // y0: first row of the block's tile
+    int x, y, z, y0, z0;  // (z0, y0): first row of the block
     bool ok;
 };
 
+// The block's cells: bx * by consecutive ones (tiles_x = 0) or a bx x by tile
+// of one plane.  set_geom chooses; see there.
 __device__ __forceinline__ CellPos tile_cell(const Geom& g) {
     const uint32_t t = xcd_tile(blockIdx.x, gridDim.x);
+    CellPos c;
+    if (g.tiles_x == 0) {
+        const idx::FlatStart f = idx::flat_start(t * (blockDim.x * blockDim.y), g.nx, g.ny);
+        idx::flat_cell(f, threadIdx.y * blockDim.x + threadIdx.x, g.nx, g.ny, g.mx, g.my, &c.x,
+                       &c.y, &c.z);
+        c.y0 = (int)f.y0;
+        c.z0 = (int)f.z0;
+        c.ok = c.z < g.nz;
+        return c;
+    }
     const uint32_t per_z = (uint32_t)g.tiles_x * (uint32_t)g.tiles_y;
     const uint32_t tz = t / per_z;
     const uint32_t rem = t - tz * per_z;
     const uint32_t ty = rem / (uint32_t)g.tiles_x;
     const uint32_t tx = rem - ty * (uint32_t)g.tiles_x;
-    CellPos c;
     c.x = (int)(tx * blockDim.x + threadIdx.x);
     c.y = (int)(ty * blockDim.y + threadIdx.y);
-    c.z = (int)tz;
+    c.z = c.z0 = (int)tz;
     c.y0 = (int)(ty * blockDim.y);
     c.ok = c.x < g.nx && c.y < g.ny;
     return c;
 }
 
-// Single cavity: one thread per cell, blocks of bx * by cells of one plane.
+// Single cavity: one thread per cell, blocks of bx * by cells.
 template <typename R, typename S, int QT, bool HG>
 __global__ void __launch_bounds__(1024)
 k_step(const S* __restrict__ in, S* __restrict__ out, Geom g, KCoef<R> k) {
     const CellPos p = tile_cell(g);
     if (!p.ok) return;
-    update_cell<R, S, QT, HG>(in, out, p.x, p.y, p.z, p.y0, g.nx, g.ny, g.nz, g.gs, k, k.seed);
+    update_cell<R, S, QT, HG>(in, out, p.x, p.y, p.z, p.y0, p.z0, g.nx, g.ny, g.nz, g.gs, k,
+                              k.seed);
 }
 
 template <typename R, typename S, int QT, bool HG>
 hipError_t step_impl(const Geom& g, StateBuf in, StateBuf out, const Coefs& c, hipStream_t s) {
     const KCoef<R> k = make_kcoef<R>(c, QT);
     const dim3 block(g.bx, g.by, 1);
-    const dim3 grid((unsigned)((int64_t)g.tiles_x * g.tiles_y * g.nz), 1, 1);
+    const int64_t ncell = (int64_t)g.nx * g.ny * g.nz, threads = (int64_t)g.bx * g.by;
+    const dim3 grid((unsigned)(g.tiles_x ? (int64_t)g.tiles_x * g.tiles_y * g.nz
+                                         : (ncell + threads - 1) / threads), 1, 1);
     hipLaunchKernelGGL((k_step<R, S, QT, HG>), grid, block, 0, s, (const S*)in.F, (S*)out.F, g,
                        k);
     return hipGetLastError();

@@ -182,16 +182,17 @@ KCoef<R> make_kcoef(const Coefs& c, int qt) {
 // Fused stream-collide update of one cell (shared by the single-cavity and
 // the batched kernels, so both compute bit-identical results)
 // ---------------------------------------------------------------------------
+// (z0, y0): the first row of the block's cells, the same for all of them.
 // seed: the step index keying stochastic rounding (FP16 storage with k.sr).
 template <typename R, typename S, int QT, bool HG>
 __device__ __forceinline__ void update_cell(const S* __restrict__ in, S* __restrict__ out, int x,
-                                            int y, int z, int y0, int nxi, int nyi, int nzi,
-                                            int gs, const KCoef<R>& k, uint32_t seed) {
+                                            int y, int z, int y0, int z0, int nxi, int nyi,
+                                            int nzi, int gs, const KCoef<R>& k, uint32_t seed) {
     constexpr int RQ = 15 + QT;
-    // The block's window starts at the group of row (z-1, y0-1) and runs to
-    // the end of the state; y0 and z are uniform over the block, so the base
+    // The block's window starts at the group of row (z0-1, y0-1) and runs to
+    // the end of the state; y0 and z0 are uniform over the block, so the base
     // is a scalar.  Every offset below is relative to it (lbm_index.hpp).
-    const idx::Window w = idx::window_of(z, y0, nxi, nyi, nzi, gs, RQ, (int)sizeof(S));
+    const idx::Window w = idx::window_of(z0, y0, nxi, nyi, nzi, gs, RQ, (int)sizeof(S));
     const __amdgpu_buffer_rsrc_t ri = pop_rsrc(in + (size_t)w.g0 * w.glen, w.bytes);
     const __amdgpu_buffer_rsrc_t ro = pop_rsrc(out + (size_t)w.g0 * w.glen, w.bytes);
     const idx::CellAt c = idx::cell_at(w, x, y, z, nxi, nyi, nzi);
