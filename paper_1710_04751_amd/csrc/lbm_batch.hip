@@ -1,14 +1,16 @@
 // Batched form: many independent cavities advanced by one persistent launch
 // per step, replayed from a captured hipGraph.
 //
-// Work decomposition.  A tile is `rows` whole x-rows of one z-plane of one
-// cavity, with rows = threads_per_block / nx (all sizes are covered, a block
-// wastes at most nx - 1 lanes).  The device holds the list of tiles of the
-// active cavities; each block of the persistent grid walks the list with a
-// stride of the grid size and updates its tile's cells with update_cell, the
-// same per-cell function the single-cavity kernel uses.  Retiring a cavity
-// rewrites the list and its length on the device, so a captured graph stays
-// valid.
+// Work decomposition.  A piece of work is one block's worth of consecutive
+// cells of one cavity (all sizes are covered, only a cavity's last block has
+// idle lanes).  The device holds the list of the active cavities' pieces; each
+// block of the persistent grid walks the list with a stride of the grid size
+// and updates its cells with update_cell, the same per-cell function the
+// single-cavity kernel uses.  Retiring a cavity rewrites the list and its
+// length on the device, so a captured graph stays valid.
+// The launch shape counts tiles of `rows` = threads / nx whole x-rows of one
+// plane (lbm_batch_launch_info, the grid of one block per tile): never fewer
+// than the pieces, so blocks past those return at once.
 #include <hip/hip_runtime.h>
 #include <math.h>
 #include <stdint.h>
@@ -32,9 +34,9 @@ struct DevCav {
     void* snap;      // temperature snapshot of the residual
     PopLay pl;
     int32_t nx, ny, nz;
-    int32_t rows;    // x-rows per tile
-    int32_t ytiles;  // tiles per z-plane
-    uint32_t magic;  // ceil(2^20 / nx): row = (lane * magic) >> 20 for lane < 1024
+    int32_t ytiles;  // tiles of the launch shape per z-plane
+    uint32_t mx, my; // idx::small_magic of nx and ny
+    int32_t stream_loads;  // streams_loads of the rows
     KCoef<double> kd;
     KCoef<float> kf;
 };
@@ -46,12 +48,16 @@ __device__ __forceinline__ const KCoef<double>& coef_of<double>(const DevCav& c)
 template <>
 __device__ __forceinline__ const KCoef<float>& coef_of<float>(const DevCav& c) { return c.kf; }
 
-// tile descriptor: cavity (8 bits) | z (10 bits) | y-tile (14 bits)
-__device__ __forceinline__ void decode_tile(uint32_t d, int& cav, int& z, int& yt) {
+// piece descriptor: cavity (8 bits) | number within the cavity (24 bits; at
+// most ny nz <= 16383 * 1023 pieces, since a block has at least nx threads)
+__device__ __forceinline__ void decode_piece(uint32_t d, int& cav, uint32_t& piece) {
     cav = (int)(d >> 24);
-    z = (int)((d >> 14) & 1023u);
-    yt = (int)(d & 0x3FFFu);
+    piece = d & 0xFFFFFFu;
 }
+
+// The words of the device counter: tiles of the launch shape and pieces of the
+// active members, and keep_sixteenths of their states.
+enum { kTilesWord, kPiecesWord, kKeepWord };
 
 // keys[c] + key_off: member c's step index, the key of its stochastic
 // rounding (FP16 storage), so a member draws the random bits a single run of
@@ -59,22 +65,24 @@ __device__ __forceinline__ void decode_tile(uint32_t d, int& cav, int& z, int& y
 // device keys advance once per replay, k_batch_advance).
 template <typename R, typename S, int QT, bool HG>
 __global__ void __launch_bounds__(1024)
-k_batch_step(const DevCav* __restrict__ cavs, const uint32_t* __restrict__ tiles,
-             const uint32_t* __restrict__ ntiles_p, int parity,
+k_batch_step(const DevCav* __restrict__ cavs, const uint32_t* __restrict__ list,
+             const uint32_t* __restrict__ counts, int parity,
              const uint32_t* __restrict__ keys, uint32_t key_off) {
-    const uint32_t ntiles = *ntiles_p;
-    for (uint32_t t = blockIdx.x; t < ntiles; t += gridDim.x) {
-        int c, z, yt;
-        decode_tile(tiles[t], c, z, yt);
+    const uint32_t pieces = counts[kPiecesWord], keep16 = counts[kKeepWord];
+    for (uint32_t t = blockIdx.x; t < pieces; t += gridDim.x) {
+        int c;
+        uint32_t piece;
+        decode_piece(list[t], c, piece);
         const DevCav& C = cavs[c];
-        const int r = (int)((threadIdx.x * C.magic) >> 20);
-        const int x = (int)threadIdx.x - r * C.nx;
-        const int y = yt * C.rows + r;
-        if (r >= C.rows || y >= C.ny) continue;
+        const idx::FlatStart f = idx::flat_start(piece * blockDim.x, C.nx, C.ny);
+        int x, y, z;
+        idx::flat_cell(f, threadIdx.x, C.nx, C.ny, C.mx, C.my, &x, &y, &z);
+        if (z >= C.nz) continue;
         uint32_t seed = 0;
         if constexpr (std::is_same<S, _Float16>::value) seed = keys[c] + key_off;
-        update_cell<R, S, QT, HG>((const S*)C.F[parity], (S*)C.F[1 - parity], x, y, z,
-                                  yt * C.rows, z, C.nx, C.ny, C.nz, C.pl.gs, coef_of<R>(C), seed);
+        update_cell_policy<R, S, QT, HG>(t, keep16, C.stream_loads, (const S*)C.F[parity],
+                                         (S*)C.F[1 - parity], x, y, z, (int)f.y0, (int)f.z0, C.nx,
+                                         C.ny, C.nz, C.pl.gs, coef_of<R>(C), seed);
     }
 }
 
@@ -90,22 +98,19 @@ __global__ void k_batch_advance(uint32_t* __restrict__ keys, const int32_t* __re
 // the snapshot.  compare[c] = 0 only takes the snapshot.
 template <typename S, int QT, typename Snap>
 __global__ void __launch_bounds__(1024)
-k_batch_residual(const DevCav* __restrict__ cavs, const uint32_t* __restrict__ tiles,
-                 const uint32_t* __restrict__ ntiles_p, int parity, const int32_t* compare,
+k_batch_residual(const DevCav* __restrict__ cavs, const uint32_t* __restrict__ list,
+                 const uint32_t* __restrict__ counts, int parity, const int32_t* compare,
                  unsigned long long* max_bits, unsigned int* bad) {
     __shared__ double s_red[16];
-    const uint32_t ntiles = *ntiles_p;
-    for (uint32_t t = blockIdx.x; t < ntiles; t += gridDim.x) {
-        int c, z, yt;
-        decode_tile(tiles[t], c, z, yt);
+    const uint32_t pieces = counts[kPiecesWord];
+    for (uint32_t t = blockIdx.x; t < pieces; t += gridDim.x) {
+        int c;
+        uint32_t piece;
+        decode_piece(list[t], c, piece);
         const DevCav& C = cavs[c];
-        const int r = (int)((threadIdx.x * C.magic) >> 20);
-        const int x = (int)threadIdx.x - r * C.nx;
-        const int y = yt * C.rows + r;
+        const uint32_t cell = piece * blockDim.x + threadIdx.x;
         double dev = 0;
-        if (r < C.rows && y < C.ny) {
-            const uint32_t cell =
-                ((uint32_t)z * (uint32_t)C.ny + (uint32_t)y) * (uint32_t)C.nx + (uint32_t)x;
+        if (cell < (uint32_t)C.nx * (uint32_t)C.ny * (uint32_t)C.nz) {
             const S* G = (const S*)C.G[parity];
             double T = 0;
 #pragma unroll
@@ -128,26 +133,34 @@ k_batch_residual(const DevCav* __restrict__ cavs, const uint32_t* __restrict__ t
     }
 }
 
-// Rebuild the tile list of the active members (one block).
+// Rebuild the piece list of the active members (one block) for blocks of
+// `threads`; keep16: keep_sixteenths of their states.
 __global__ void __launch_bounds__(1024)
 k_batch_compact(const DevCav* __restrict__ cavs, const int32_t* __restrict__ active, int n,
-                uint32_t* __restrict__ tiles, uint32_t* __restrict__ ntiles) {
+                uint32_t threads, uint32_t keep16, uint32_t* __restrict__ list,
+                uint32_t* __restrict__ counts) {
     __shared__ uint32_t off[257];
+    auto pieces_of = [&](int c) {
+        const uint32_t cells = (uint32_t)cavs[c].nx * (uint32_t)cavs[c].ny * (uint32_t)cavs[c].nz;
+        return (cells + threads - 1) / threads;
+    };
     if (threadIdx.x == 0) {
+        uint32_t tiles = 0;
         off[0] = 0;
-        for (int c = 0; c < n; ++c)
-            off[c + 1] = off[c] + (active[c] ? (uint32_t)(cavs[c].nz * cavs[c].ytiles) : 0u);
-        *ntiles = off[n];
+        for (int c = 0; c < n; ++c) {
+            off[c + 1] = off[c] + (active[c] ? pieces_of(c) : 0u);
+            if (active[c]) tiles += (uint32_t)(cavs[c].nz * cavs[c].ytiles);
+        }
+        counts[kTilesWord] = tiles;
+        counts[kPiecesWord] = off[n];
+        counts[kKeepWord] = keep16;
     }
     __syncthreads();
     for (int c = 0; c < n; ++c) {
         if (!active[c]) continue;
-        const uint32_t yts = (uint32_t)cavs[c].ytiles;
-        const uint32_t cnt = (uint32_t)cavs[c].nz * yts;
-        for (uint32_t j = threadIdx.x; j < cnt; j += blockDim.x) {
-            const uint32_t z = j / yts, yt = j - z * yts;
-            tiles[off[c] + j] = ((uint32_t)c << 24) | (z << 14) | yt;
-        }
+        const uint32_t cnt = pieces_of(c);
+        for (uint32_t j = threadIdx.x; j < cnt; j += blockDim.x)
+            list[off[c] + j] = ((uint32_t)c << 24) | j;
     }
 }
 
@@ -171,7 +184,7 @@ constexpr size_t kAlignB = 256;
 size_t alignb(size_t v) { return (v + kAlignB - 1) / kAlignB * kAlignB; }
 
 struct BatchLayout {
-    size_t off_table, off_tiles, off_ntiles, off_flags, off_res, off_keys, off_members, total;
+    size_t off_table, off_list, off_counts, off_flags, off_res, off_keys, off_members, total;
     std::vector<size_t> member_off, member_bytes;
     size_t max_tiles;
 };
@@ -208,9 +221,9 @@ bool batch_layout(const lbm_params* p, int n, BatchLayout* L, std::string* why) 
     }
     L->max_tiles = max_tiles;
     L->off_table = 0;
-    L->off_tiles = alignb(sizeof(DevCav) * n);
-    L->off_ntiles = L->off_tiles + alignb(max_tiles * sizeof(uint32_t));
-    L->off_flags = L->off_ntiles + kAlignB;                    // active[n], compare[n]
+    L->off_list = alignb(sizeof(DevCav) * n);
+    L->off_counts = L->off_list + alignb(max_tiles * sizeof(uint32_t));
+    L->off_flags = L->off_counts + kAlignB;                    // active[n], compare[n]
     L->off_res = L->off_flags + alignb(2 * n * sizeof(int32_t));  // max bits[n], bad[n]
     L->off_keys = L->off_res + alignb(2 * n * sizeof(unsigned long long));  // step keys[n]
     L->off_members = L->off_keys + alignb(n * sizeof(uint32_t));
@@ -249,8 +262,8 @@ struct lbm_batch {
     bool keys_ok;
 
     DevCav* d_table() const { return (DevCav*)(ws + lay.off_table); }
-    uint32_t* d_tiles() const { return (uint32_t*)(ws + lay.off_tiles); }
-    uint32_t* d_ntiles() const { return (uint32_t*)(ws + lay.off_ntiles); }
+    uint32_t* d_list() const { return (uint32_t*)(ws + lay.off_list); }
+    uint32_t* d_counts() const { return (uint32_t*)(ws + lay.off_counts); }
     int32_t* d_active() const { return (int32_t*)(ws + lay.off_flags); }
     int32_t* d_compare() const { return d_active() + n; }
     unsigned long long* d_maxbits() const { return (unsigned long long*)(ws + lay.off_res); }
@@ -295,9 +308,11 @@ void fill_kcoef(const lbm_handle* h, KCoef<R>* k) {
 // rebuild the device tile list.
 lbm_status upload_table(lbm_batch* b) {
     b->tiles_all = 0;
+    uint64_t active_bytes = 0;  // both states of the members that step
     for (int i = 0; i < b->n; ++i) {
         const lbm_handle* h = b->mem[i];
         DevCav& d = b->table[i];
+        if (b->active[i]) active_bytes += 2 * (uint64_t)h->lay.state_bytes;
         StateBuf A = h->buf(0), B = h->buf(1);
         d.F[0] = A.F;
         d.G[0] = A.G;
@@ -308,14 +323,12 @@ lbm_status upload_table(lbm_batch* b) {
         d.nx = h->p.nx;
         d.ny = h->p.ny;
         d.nz = h->p.nz;
-        d.rows = std::max(1, b->threads / h->p.nx);
-        d.ytiles = (h->p.ny + d.rows - 1) / d.rows;
+        const int rows = std::max(1, b->threads / h->p.nx);
+        d.ytiles = (h->p.ny + rows - 1) / rows;
         b->tiles_all += (int64_t)d.nz * d.ytiles;
-        d.magic = (uint32_t)(((1u << 20) + (uint32_t)h->p.nx - 1) / (uint32_t)h->p.nx);
-        // the row index must be exact for every lane of the block
-        for (uint32_t lane = 0; lane < (uint32_t)b->threads; ++lane)
-            if (((lane * d.magic) >> 20) != lane / (uint32_t)h->p.nx)
-                return fail(LBM_ERR_ARG, "row decomposition is not exact for this block size");
+        d.mx = idx::small_magic((uint32_t)h->p.nx);
+        d.my = idx::small_magic((uint32_t)h->p.ny);
+        d.stream_loads = h->geom.stream_loads;
         fill_kcoef<double>(h, &d.kd);
         fill_kcoef<float>(h, &d.kf);
     }
@@ -326,7 +339,8 @@ lbm_status upload_table(lbm_batch* b) {
                            hipMemcpyHostToDevice, b->stream);
     if (e != hipSuccess) return hip_fail(e, "batch table upload");
     hipLaunchKernelGGL(k_batch_compact, dim3(1), dim3(1024), 0, b->stream, b->d_table(),
-                       b->d_active(), b->n, b->d_tiles(), b->d_ntiles());
+                       b->d_active(), b->n, (uint32_t)b->threads, keep_sixteenths(active_bytes),
+                       b->d_list(), b->d_counts());
     e = hipGetLastError();
     if (e != hipSuccess) return hip_fail(e, "batch compaction");
     // the host table and flags are pageable: make sure they are consumed
@@ -363,7 +377,7 @@ hipError_t launch_one_step(lbm_batch* b, int parity, uint32_t key_off) {
     const dim3 grid(batch_grid(b)), block((unsigned)b->threads);
     LBM_BATCH_DISPATCH(b->prec, b->qt, b->general, {
         hipLaunchKernelGGL((k_batch_step<R, S, Q, G>), grid, block, 0, b->stream, b->d_table(),
-                           b->d_tiles(), b->d_ntiles(), parity, (const uint32_t*)b->d_keys(),
+                           b->d_list(), b->d_counts(), parity, (const uint32_t*)b->d_keys(),
                            key_off);
     });
     return hipGetLastError();
@@ -565,29 +579,29 @@ lbm_status lbm_batch_residuals(lbm_batch* b, double* max_dT, int32_t* status) {
     if (b->prec == Prec::FP64) {
         if (b->qt == 7)
             hipLaunchKernelGGL((k_batch_residual<double, 7, double>), grid, block, 0, b->stream,
-                               b->d_table(), b->d_tiles(), b->d_ntiles(), parity, b->d_compare(),
+                               b->d_table(), b->d_list(), b->d_counts(), parity, b->d_compare(),
                                b->d_maxbits(), b->d_bad());
         else
             hipLaunchKernelGGL((k_batch_residual<double, 15, double>), grid, block, 0, b->stream,
-                               b->d_table(), b->d_tiles(), b->d_ntiles(), parity, b->d_compare(),
+                               b->d_table(), b->d_list(), b->d_counts(), parity, b->d_compare(),
                                b->d_maxbits(), b->d_bad());
     } else if (b->prec == Prec::FP32) {
         if (b->qt == 7)
             hipLaunchKernelGGL((k_batch_residual<float, 7, float>), grid, block, 0, b->stream,
-                               b->d_table(), b->d_tiles(), b->d_ntiles(), parity, b->d_compare(),
+                               b->d_table(), b->d_list(), b->d_counts(), parity, b->d_compare(),
                                b->d_maxbits(), b->d_bad());
         else
             hipLaunchKernelGGL((k_batch_residual<float, 15, float>), grid, block, 0, b->stream,
-                               b->d_table(), b->d_tiles(), b->d_ntiles(), parity, b->d_compare(),
+                               b->d_table(), b->d_list(), b->d_counts(), parity, b->d_compare(),
                                b->d_maxbits(), b->d_bad());
     } else {
         if (b->qt == 7)
             hipLaunchKernelGGL((k_batch_residual<_Float16, 7, float>), grid, block, 0, b->stream,
-                               b->d_table(), b->d_tiles(), b->d_ntiles(), parity, b->d_compare(),
+                               b->d_table(), b->d_list(), b->d_counts(), parity, b->d_compare(),
                                b->d_maxbits(), b->d_bad());
         else
             hipLaunchKernelGGL((k_batch_residual<_Float16, 15, float>), grid, block, 0, b->stream,
-                               b->d_table(), b->d_tiles(), b->d_ntiles(), parity, b->d_compare(),
+                               b->d_table(), b->d_list(), b->d_counts(), parity, b->d_compare(),
                                b->d_maxbits(), b->d_bad());
     }
     e = hipGetLastError();
@@ -758,7 +772,7 @@ lbm_status lbm_batch_launch_info(lbm_batch* b, int32_t* threads, int32_t* grid_b
     if (steps) *steps = b->gsteps;
     if (active_tiles) {
         uint32_t nt = 0;
-        hipError_t e = hipMemcpyAsync(&nt, b->d_ntiles(), sizeof nt, hipMemcpyDeviceToHost, b->stream);
+        hipError_t e = hipMemcpyAsync(&nt, b->d_counts(), sizeof nt, hipMemcpyDeviceToHost, b->stream);
         if (e == hipSuccess) e = hipStreamSynchronize(b->stream);
         if (e != hipSuccess) return hip_fail(e, "launch info");
         *active_tiles = (int32_t)nt;

@@ -14,6 +14,8 @@ struct Geom {
     int32_t tiles_x, tiles_y; // blocks per row / per plane (0: blocks of bx * by
                               // consecutive cells)
     uint32_t mx, my;          // idx::small_magic of nx and ny
+    uint32_t keep16;          // keep_sixteenths of the two states
+    int32_t stream_loads;     // streams_loads of the rows
     int32_t gs;               // log2 of the rows per population run (PopLay)
 };
 
@@ -54,6 +56,24 @@ struct StateBuf {
 enum class Prec : int32_t { FP64 = 0, FP32 = 1, FP32_S16 = 2 };
 
 int value_bytes(Prec p);
+
+// Whether blocks that stream also load past the caches: rows of whole 128-byte
+// lines of values of 4 bytes or more, so that a wave shares at most the lines
+// at its ends with its neighbours (512^3: FP32 3.75 against 3.81 ms a step
+// with ordinary loads, FP64 2.5% better; but FP16 2.05 against 1.98 ms, and
+// rows of odd length 301^3 0.92 against 0.89 ms, D3Q15 333^3 1.72 against 1.67).
+inline bool streams_loads(int64_t nx, int vbytes) {
+    return vbytes >= 4 && nx * vbytes % 128 == 0;
+}
+
+// Of 16 blocks of the step, how many leave their results in the 256 MB
+// memory-side cache (Policy, lbm_step.hpp), for states of `bytes` in all (A
+// and B): all of them while everything fits, else the share that holds about
+// 170 MB, none once that is below 1/16.
+inline uint32_t keep_sixteenths(uint64_t bytes) {
+    constexpr uint64_t MB = 1 << 20;
+    return bytes <= 240 * MB ? 16u : (uint32_t)(16 * 170 * MB / bytes);
+}
 
 hipError_t launch_step(Prec p, int qt, bool general, const Geom& g, StateBuf in,
                        StateBuf out, const Coefs& c, hipStream_t s);

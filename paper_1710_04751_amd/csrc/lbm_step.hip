@@ -79,8 +79,8 @@ __global__ void __launch_bounds__(1024)
 k_step(const S* __restrict__ in, S* __restrict__ out, Geom g, KCoef<R> k) {
     const CellPos p = tile_cell(g);
     if (!p.ok) return;
-    update_cell<R, S, QT, HG>(in, out, p.x, p.y, p.z, p.y0, p.z0, g.nx, g.ny, g.nz, g.gs, k,
-                              k.seed);
+    update_cell_policy<R, S, QT, HG>(blockIdx.x, g.keep16, g.stream_loads, in, out, p.x, p.y, p.z,
+                                     p.y0, p.z0, g.nx, g.ny, g.nz, g.gs, k, k.seed);
 }
 
 template <typename R, typename S, int QT, bool HG>

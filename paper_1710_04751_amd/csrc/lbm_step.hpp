@@ -100,42 +100,75 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t pop_rsrc(const void* base, uin
     return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(base), (short)0, (int)bytes,
                                              0x00020000);
 }
-constexpr int kNonTemporal = 2;  // cache policy of the stores: non-temporal
+// Cache policies of the step's population accesses (bits of the buffer
+// instructions: 1 sc0, 2 non-temporal, 16 sc1), chosen per block.
+//   kKeep: ordinary loads, write-through stores, so the memory-side cache
+//     (256 MB) keeps the stored lines for the next step.
+//   kStream: ordinary loads, write-through non-temporal stores, which stream
+//     past it.
+//   kStreamLoads: the same with non-temporal loads, where few lines are
+//     shared between waves (streams_loads).
+// keep_sixteenths says how many of 16 blocks keep.  Measured, FP32 D3Q7, us a
+// step, streaming / keeping / the mix chosen (two states' size in brackets):
+// 64^3 (44 MB) 10.6 / 8.4 / 8.4, 100^3 (167) 34.0 / 25.9 / 25.9, 128^3 (352)
+// 63.4 / 67.4 / 54.2, 150^3 (566) 108 / 109 / 98, 192^3 (1188) 220 / 227 /
+// 204, 256^3 (2816) 480 / 520 / 480, 512^3 3.75 / 4.2 / 3.75 ms.  Before,
+// non-temporal stores that allocate (2) with ordinary loads for every size:
+// 10.6, 34.0, 65.0, 106, 225, 493 us and 3.87 ms.
+enum PolicyKind { kKeep, kStream, kStreamLoads };
+template <int POL>
+struct Policy {
+    static constexpr int ld = POL == kStreamLoads ? 2 : 0;
+    static constexpr int st = POL == kKeep ? 16 : 18;
+};
+
+// Whether block b keeps: spread over the 8 XCDs (b mod 8) alike, and
+// alternating along each XCD's blocks so that both memory paths stay busy.
+__device__ __forceinline__ bool keeps(uint32_t b, uint32_t keep16) {
+    return ((b >> 3) & 15u) < keep16;
+}
 
 template <typename S>
 struct Buf;
 template <>
 struct Buf<float> {
-    template <typename R>
+    template <typename R, int POL>
     __device__ static R ld(__amdgpu_buffer_rsrc_t r, uint32_t i) {
-        return (R)__builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(r, i * 4u, 0, 0));
+        return (R)__builtin_bit_cast(
+            float, __builtin_amdgcn_raw_buffer_load_b32(r, i * 4u, 0, Policy<POL>::ld));
     }
+    template <int POL>
     __device__ static void st(__amdgpu_buffer_rsrc_t r, uint32_t i, float v) {
         __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(unsigned, v), r, i * 4u, 0,
-                                              kNonTemporal);
+                                              Policy<POL>::st);
     }
 };
 template <>
 struct Buf<double> {
     typedef unsigned v2u __attribute__((ext_vector_type(2)));
-    template <typename R>
+    template <typename R, int POL>
     __device__ static R ld(__amdgpu_buffer_rsrc_t r, uint32_t i) {
-        return (R)__builtin_bit_cast(double, __builtin_amdgcn_raw_buffer_load_b64(r, i * 8u, 0, 0));
+        return (R)__builtin_bit_cast(
+            double, __builtin_amdgcn_raw_buffer_load_b64(r, i * 8u, 0, Policy<POL>::ld));
     }
+    template <int POL>
     __device__ static void st(__amdgpu_buffer_rsrc_t r, uint32_t i, double v) {
-        __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(v2u, v), r, i * 8u, 0, kNonTemporal);
+        __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(v2u, v), r, i * 8u, 0,
+                                              Policy<POL>::st);
     }
 };
 template <>
 struct Buf<_Float16> {
-    template <typename R>
+    template <typename R, int POL>
     __device__ static R ld(__amdgpu_buffer_rsrc_t r, uint32_t i) {
-        return (R)(float)__builtin_bit_cast(_Float16, __builtin_amdgcn_raw_buffer_load_b16(r, i * 2u, 0, 0));
+        return (R)(float)__builtin_bit_cast(
+            _Float16, __builtin_amdgcn_raw_buffer_load_b16(r, i * 2u, 0, Policy<POL>::ld));
     }
+    template <int POL>
     __device__ static void st(__amdgpu_buffer_rsrc_t r, uint32_t i, float v) {
         // round to nearest even
         __builtin_amdgcn_raw_buffer_store_b16(__builtin_bit_cast(unsigned short, (_Float16)v), r,
-                                              i * 2u, 0, kNonTemporal);
+                                              i * 2u, 0, Policy<POL>::st);
     }
 };
 
@@ -184,7 +217,8 @@ KCoef<R> make_kcoef(const Coefs& c, int qt) {
 // ---------------------------------------------------------------------------
 // (z0, y0): the first row of the block's cells, the same for all of them.
 // seed: the step index keying stochastic rounding (FP16 storage with k.sr).
-template <typename R, typename S, int QT, bool HG>
+// POL: the block's cache policy (Policy).
+template <typename R, typename S, int QT, bool HG, int POL>
 __device__ __forceinline__ void update_cell(const S* __restrict__ in, S* __restrict__ out, int x,
                                             int y, int z, int y0, int z0, int nxi, int nyi,
                                             int nzi, int gs, const KCoef<R>& k, uint32_t seed) {
@@ -198,7 +232,7 @@ __device__ __forceinline__ void update_cell(const S* __restrict__ in, S* __restr
     const idx::CellAt c = idx::cell_at(w, x, y, z, nxi, nyi, nzi);
     R d[15];
 #pragma unroll
-    for (int a = 0; a < 15; ++a) d[a] = Buf<S>::template ld<R>(ri, idx::flow_load(w, c, a));
+    for (int a = 0; a < 15; ++a) d[a] = Buf<S>::template ld<R, POL>(ri, idx::flow_load(w, c, a));
     R gq[QT];
     // Scalar gather: anti-bounce-back across the Dirichlet walls (this rule
     // wins on edges), bounce-back or -- with specular reflection, D3Q15
@@ -209,7 +243,7 @@ __device__ __forceinline__ void update_cell(const S* __restrict__ in, S* __restr
 #pragma unroll
         for (int a = 0; a < QT; ++a) {
             const idx::ScalarLoad l = idx::scalar_load<QT, SPEC>(w, c, a);
-            R v = Buf<S>::template ld<R>(ri, l.off);
+            R v = Buf<S>::template ld<R, POL>(ri, l.off);
             if (l.dirichlet) {
                 const int ex = QT == 7 ? EX7[a] : EX15[a];
                 const int ey = QT == 7 ? EY7[a] : EY15[a];
@@ -257,19 +291,48 @@ __device__ __forceinline__ void update_cell(const S* __restrict__ in, S* __restr
             // value 2j takes the high half of word j, value 2j + 1 the low half
 #pragma unroll
             for (int a = 0; a < 15; ++a)
-                Buf<S>::st(ro, idx::store_at(w, c, a),
+                Buf<S>::template st<POL>(ro, idx::store_at(w, c, a),
                            (float)half_stochastic(d[a], rnd[a >> 1] << (16 * (a & 1))));
 #pragma unroll
             for (int a = 0; a < QT; ++a)
-                Buf<S>::st(ro, idx::store_at(w, c, 15 + a),
+                Buf<S>::template st<POL>(ro, idx::store_at(w, c, 15 + a),
                            (float)half_stochastic(gq[a], rnd[(a + 15) >> 1] << (16 * ((a + 15) & 1))));
             return;
         }
     }
 #pragma unroll
-    for (int a = 0; a < 15; ++a) Buf<S>::st(ro, idx::store_at(w, c, a), d[a]);
+    for (int a = 0; a < 15; ++a) Buf<S>::template st<POL>(ro, idx::store_at(w, c, a), d[a]);
 #pragma unroll
-    for (int a = 0; a < QT; ++a) Buf<S>::st(ro, idx::store_at(w, c, 15 + a), gq[a]);
+    for (int a = 0; a < QT; ++a) Buf<S>::template st<POL>(ro, idx::store_at(w, c, 15 + a), gq[a]);
+}
+
+// update_cell under the block's cache policy; b: the block's number,
+// stream_loads: streams_loads of the box.  Each branch takes its own opaque
+// copy of x: otherwise the compiler computes what the branches have in common
+// before them and holds it in registers (FP64 D3Q7 72 instead of 64, D3Q15
+// spilled).
+__device__ __forceinline__ int opaque(int v) {
+    __asm__ volatile("" : "+v"(v));
+    return v;
+}
+template <typename R, typename S, int QT, bool HG>
+__device__ __forceinline__ void update_cell_policy(uint32_t b, uint32_t keep16, int stream_loads,
+                                                   const S* __restrict__ in, S* __restrict__ out,
+                                                   int x, int y, int z, int y0, int z0, int nx,
+                                                   int ny, int nz, int gs, const KCoef<R>& k,
+                                                   uint32_t seed) {
+    if (keeps(b, keep16)) {
+        update_cell<R, S, QT, HG, kKeep>(in, out, opaque(x), opaque(y), opaque(z), y0, z0, nx, ny, nz, gs, k, seed);
+        return;
+    }
+    if constexpr (sizeof(S) > 2) {
+        if (stream_loads) {
+            update_cell<R, S, QT, HG, kStreamLoads>(in, out, opaque(x), opaque(y), opaque(z), y0, z0, nx, ny, nz, gs, k,
+                                                    seed);
+            return;
+        }
+    }
+    update_cell<R, S, QT, HG, kStream>(in, out, opaque(x), opaque(y), opaque(z), y0, z0, nx, ny, nz, gs, k, seed);
 }
 
 }  // namespace kern
