@@ -7,9 +7,12 @@
 //   A (16 x 32): lane holds row r, k = 8q .. 8q+7;
 //   B (32 x 16): lane holds column r, k = 8q .. 8q+7;
 //   D (16 x 16, FP32): lane holds rows 4q .. 4q+3 of column r.
-// Forward: rows are 16 voxels, columns output channels, k runs over
+// Forward: rows are output channels, columns 16 voxels, k runs over
 // (tap, input channel) with the channels of one tap contiguous, so a lane's
-// 8 k values are one 16-byte load of a channels-last voxel.  The input
+// 8 k values are one 16-byte load of a channels-last voxel, and its 4 results
+// are 4 consecutive channels of one voxel: one 8-byte store (and one 8-byte
+// load of the ReLU mask).  With voxels as rows and channels as columns the
+// products are the same but each lane stored four 2-byte values.  The input
 // gradient is the same kernel run on the output gradient with the
 // transposed, tap-flipped weight.  The weight gradient takes rows = output
 // channels, columns = (tap, input channel) and k = voxels; each block sums
@@ -67,6 +70,37 @@ struct ConvArgs {
     int32_t n, lg, taps, c1s, c2, cin, K, kpad, cout, ys, relu;
     int32_t wrows;        // rows of the packed weight w (set by launch_conv)
 };
+
+// The convolutions' results: lane (r, q) has channels co .. co + 3 (co a
+// multiple of 4) of one voxel, acc + bias, ReLU, 0 where the mask is not
+// positive and for padding channels co >= cout; nothing for co >= ys.
+// bias_quad: the lane's four biases, loaded ahead.
+__device__ __forceinline__ floatx4 bias_quad(const ConvArgs& a, int co) {
+    floatx4 b = {0.f, 0.f, 0.f, 0.f};
+    if (a.bias) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) b[i] = co + i < a.cout ? a.bias[co + i] : 0.f;
+    }
+    return b;
+}
+
+__device__ __forceinline__ void store_quad(const ConvArgs& a, int64_t vo, int co, floatx4 acc,
+                                           floatx4 bias, bf16x4 mask) {
+    if (co >= a.ys) return;
+    bf16x4 o;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        float val = acc[i] + bias[i];
+        if (a.relu) val = fmaxf(val, 0.f);
+        if (co + i >= a.cout || (a.omask && !((float)mask[i] > 0.f))) val = 0.f;
+        o[i] = (__bf16)val;
+    }
+    *(bf16x4*)(a.out + vo * a.ys + co) = o;
+}
+
+__device__ __forceinline__ bf16x4 mask_quad(const ConvArgs& a, int64_t vo, int co) {
+    return a.omask && co < a.ys ? *(const bf16x4*)(a.omask + vo * a.ys + co) : bf16x4{};
+}
 
 // One block: MT * 16 voxels x (NSUB * 16) output channels, channel group
 // blockIdx.y.  Each weight fragment is loaded once and used for the MT
@@ -148,7 +182,7 @@ __global__ void __launch_bounds__(64 * KS) k_conv(ConvArgs a) {
         for (int j = 0; j < NSUB; ++j)
 #pragma unroll
             for (int m = 0; m < MT; ++m)
-                acc[m][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av[m], bv[j], acc[m][j], 0, 0, 0);
+                acc[m][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(bv[j], av[m], acc[m][j], 0, 0, 0);
     };
     if constexpr (MT == 1) {
         if (nst > 0) {
@@ -187,26 +221,17 @@ __global__ void __launch_bounds__(64 * KS) k_conv(ConvArgs a) {
 #pragma unroll
                 for (int j = 0; j < NSUB; ++j) acc[m][j] += part[w][m * NSUB + j][lane];
     }
+    // D rows 4q .. 4q+3 are output channels, column r the voxel
 #pragma unroll
-    for (int m = 0; m < MT; ++m)
+    for (int m = 0; m < MT; ++m) {
+        const int64_t vo = vb + m * 16 + r;
+        if (vo >= M) continue;
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const int64_t vo = vb + m * 16 + q * 4 + i;
-            if (vo >= M) continue;
-#pragma unroll
-            for (int j = 0; j < NSUB; ++j) {
-                const int co = cobase + j * 16 + r;
-                if (co < a.ys) {
-                    float val = 0.f;
-                    if (co < a.cout) {
-                        val = acc[m][j][i] + (a.bias ? a.bias[co] : 0.f);
-                        if (a.relu) val = fmaxf(val, 0.f);
-                        if (a.omask && !((float)a.omask[vo * a.ys + co] > 0.f)) val = 0.f;
-                    }
-                    a.out[vo * a.ys + co] = (__bf16)val;
-                }
-            }
+        for (int j = 0; j < NSUB; ++j) {
+            const int co = cobase + j * 16 + q * 4;
+            store_quad(a, vo, co, acc[m][j], bias_quad(a, co), mask_quad(a, vo, co));
         }
+    }
 }
 
 struct WgradArgs {
@@ -1442,17 +1467,14 @@ __global__ void __launch_bounds__(64 * kCvPlanes)
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int r = lane & 15, q = lane >> 4, hi = q >> 1;
     const int lg = a.lg, G = 1 << lg;
-    const int nbx = G >> 4, nby = G >> 2, nbz = G / kCvPlanes;
     // blocks i, i + 8, ... run on one XCD (dispatch is round-robin over the
     // eight): give each XCD a contiguous range of bricks, whose halos overlap
     // in its L2 (the grid's x size is a multiple of 8 for G >= 16)
-    int64_t bid = (int64_t)(blockIdx.x % 8) * (gridDim.x / 8) + blockIdx.x / 8;
-    const int x0 = (int)(bid % nbx) * 16;
-    bid /= nbx;
-    const int y0 = (int)(bid % nby) * 4;
-    bid /= nby;
-    const int z0 = (int)(bid % nbz) * kCvPlanes;
-    const int smp = (int)(bid / nbz);
+    const uint32_t bid = (blockIdx.x % 8) * (gridDim.x / 8) + blockIdx.x / 8;
+    const int x0 = (int)(bid & ((1u << (lg - 4)) - 1)) * 16;
+    const int y0 = (int)((bid >> (lg - 4)) & ((1u << (lg - 2)) - 1)) * 4;
+    const int z0 = (int)((bid >> (2 * lg - 6)) & ((1u << (lg - 3)) - 1)) * kCvPlanes;
+    const int smp = (int)(bid >> (3 * lg - 9));
     const int cobase = blockIdx.y * NSUB * 16;
     floatx4 acc[4][NSUB];
 #pragma unroll
@@ -1471,56 +1493,86 @@ __global__ void __launch_bounds__(64 * kCvPlanes)
     const char* wlb = (const char*)wl;
     // Loads go through range-checked buffer resources: a position outside
     // the grid (or the tensor, or a weight item of the zero slot or padding)
-    // reads past the end and lands as zeros.
+    // gets an offset with bit 31 set, reads past the end and lands as zeros.
+    // The lane's items are decoded once, before the chunk loop: item i is
+    // voxel tid / 2 + 256 i of the halo (channel half tid % 2), 4 cells, 2 rows
+    // and 2 planes on from item i - 1, with carries.  vox: the voxel's number,
+    // bit 31 where there is none.
+    // (Decoded per chunk with divisions, the copies' addresses took more of
+    // the vector units than the products of the matrix cores.)
+    constexpr int kHaloIt = (kCvHaloItems + kThreads - 1) / kThreads;
+    constexpr int kWIt = (kWBuf + kThreads - 1) / kThreads;
+    static_assert(kThreads / 2 == 2 * 108 + 2 * 18 + 4, "the items' stride");
     const int h = lg - 1;
-    for (int c0 = 0; c0 < a.cin; c0 += 16) {
-        const bool lo = c0 < a.c1s;  // x1's channels, else x2's (c1s is then a multiple of 16)
-        const int chans = lo ? a.c1s : a.c2;
-        const int hl = lo ? lg : h;  // the tensor's grid: 2^hl cells a side
-        const int sh = lo ? 0 : 1;   // coarse tensor: the fine cell's parent
-        const int64_t vs = (int64_t)1 << (3 * hl);
-        const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(
-            const_cast<__bf16*>((lo ? a.x1 : a.x2) + (int64_t)smp * vs * chans), (short)0,
-            (int)(uint32_t)(vs * chans * 2), 0x00020000);
-        const int cloc = lo ? c0 : c0 - a.c1s;
-        const int wv = __builtin_amdgcn_readfirstlane(wave);
-        // halo item t (voxel t / 2, channel half t % 2) lands at LDS byte 16 t
+    const int half = tid & 1;
+    uint32_t vox[kHaloIt], wofs[kWIt];
+    {
+        int hx = (tid >> 1) % 18, hy = ((tid >> 1) / 18) % 6, hz = (tid >> 1) / 108;
+        const bool no_half = half * 8 >= a.cin;  // 8 input channels: the upper half is zeros
 #pragma unroll
-        for (int i = 0; i < (kCvHaloItems + kThreads - 1) / kThreads; ++i) {
-            const int tb = i * kThreads + wv * 64;
-            if (tb >= kCvHaloItems) continue;
-            const int t = tb + lane;
-            const int half = t & 1, hv = t >> 1;
-            const int hx = hv % 18, hy = (hv / 18) % 6, hz = hv / 108;
+        for (int i = 0; i < kHaloIt; ++i) {
             const int xx = x0 + hx - 1, yy = y0 + hy - 1, zz = z0 + hz - 1;
-            const bool ok = t < kCvHaloItems && c0 + half * 8 < a.cin && (unsigned)xx < (unsigned)G &&
-                            (unsigned)yy < (unsigned)G && (unsigned)zz < (unsigned)G;
-            const uint32_t vox = ((uint32_t)(zz >> sh) << (2 * hl)) + ((uint32_t)(yy >> sh) << hl) +
-                                 (uint32_t)(xx >> sh);
-            const uint32_t off = ((vox * (uint32_t)chans + (uint32_t)(cloc + half * 8)) * 2u) |
-                                 ((uint32_t)!ok << 31);
-            __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (lds_void_ptr)&xs[tb * 8], 16, off, 0, 0, 0);
+            const bool ok = i * kThreads + tid < kCvHaloItems && !no_half &&
+                            (unsigned)xx < (unsigned)G && (unsigned)yy < (unsigned)G &&
+                            (unsigned)zz < (unsigned)G;
+            vox[i] = ok ? ((uint32_t)zz << (2 * lg)) + ((uint32_t)yy << lg) + (uint32_t)xx
+                        : 0x80000000u;
+            hx += 4;
+            if (hx >= 18) hx -= 18, ++hy;
+            hy += 2;
+            if (hy >= 6) hy -= 6, ++hz;
+            hz += 2;
         }
-        const __amdgpu_buffer_rsrc_t rw = __builtin_amdgcn_make_buffer_rsrc(
-            const_cast<__bf16*>(a.w), (short)0, (int)(uint32_t)((int64_t)a.wrows * a.kpad * 2),
-            0x00020000);
         // weight item t: row t / 58 (output channel cobase + row), slot s =
         // (t % 58) / 2 (tap s / 2 for even s, the paired tap for odd s), 8
         // channels of half t % 2; items 56, 57 of a row are padding.  (With 8
         // input channels the upper half holds the next tap's weights, which
         // meet zero inputs, and stays inside the row since 27 * 8 + 8 <= kpad.)
 #pragma unroll
-        for (int i = 0; i < (kWBuf + kThreads - 1) / kThreads; ++i) {
-            const int tb = i * kThreads + wv * 64;
-            if (tb >= kWBuf) continue;
-            const int t = tb + lane;
+        for (int i = 0; i < kWIt; ++i) {
+            const int t = i * kThreads + tid;
             const int row = t / kCvWItemsRow, rem = t - row * kCvWItemsRow;
-            const int slot = rem >> 1, half = rem & 1, p = slot >> 1;
+            const int slot = rem >> 1, p = slot >> 1;
             const int tap = (slot & 1) ? cv_pair_tap(p) : p;
             const bool ok = t < kWItems && rem < 2 * kCvSlots && tap >= 0 && cobase + row < a.wrows;
-            const uint32_t off =
-                ((uint32_t)((cobase + row) * a.kpad + tap * a.cin + c0 + half * 8) * 2u) |
-                ((uint32_t)!ok << 31);
+            wofs[i] = ok ? (uint32_t)((cobase + row) * a.kpad + tap * a.cin + (rem & 1) * 8) * 2u
+                         : 0x80000000u;
+        }
+    }
+    const int wv = __builtin_amdgcn_readfirstlane(wave);
+    for (int c0 = 0; c0 < a.cin; c0 += 16) {
+        const bool lo = c0 < a.c1s;  // x1's channels, else x2's (c1s is then a multiple of 16)
+        const int chans = lo ? a.c1s : a.c2;
+        const int hl = lo ? lg : h;  // the tensor's grid: 2^hl cells a side
+        const int64_t vs = (int64_t)1 << (3 * hl);
+        const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(
+            const_cast<__bf16*>((lo ? a.x1 : a.x2) + (int64_t)smp * vs * chans), (short)0,
+            (int)(uint32_t)(vs * chans * 2), 0x00020000);
+        const int cloc = lo ? c0 : c0 - a.c1s;
+        // halo item t (voxel t / 2, channel half t % 2) lands at LDS byte 16 t
+        // (voxel numbers are below 2^24: 24-bit products)
+#pragma unroll
+        for (int i = 0; i < kHaloIt; ++i) {
+            const int tb = i * kThreads + wv * 64;
+            if (tb >= kCvHaloItems) continue;
+            uint32_t v = vox[i];
+            if (!lo) {  // the coarse tensor: the cell's parent
+                const uint32_t hm = (1u << h) - 1;
+                v = (v & 0x80000000u) | ((v >> (2 * lg + 1) & hm) << (2 * h)) |
+                    ((v >> (lg + 1) & hm) << h) | (v >> 1 & hm);
+            }
+            const uint32_t off = (__umul24(v, (uint32_t)chans * 2u) +
+                                  (uint32_t)(cloc + half * 8) * 2u) | (v & 0x80000000u);
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (lds_void_ptr)&xs[tb * 8], 16, off, 0, 0, 0);
+        }
+        const __amdgpu_buffer_rsrc_t rw = __builtin_amdgcn_make_buffer_rsrc(
+            const_cast<__bf16*>(a.w), (short)0, (int)(uint32_t)((int64_t)a.wrows * a.kpad * 2),
+            0x00020000);
+#pragma unroll
+        for (int i = 0; i < kWIt; ++i) {
+            const int tb = i * kThreads + wv * 64;
+            if (tb >= kWBuf) continue;
+            const uint32_t off = wofs[i] + (uint32_t)c0 * 2u;
             __builtin_amdgcn_raw_ptr_buffer_load_lds(rw, (lds_void_ptr)&wl[tb * 8], 16, off, 0, 0, 0);
         }
         // this wave's copies have landed (vmcnt 0; expcnt and lgkmcnt left at their maxima)
@@ -1542,32 +1594,23 @@ __global__ void __launch_bounds__(64 * kCvPlanes)
             for (int m = 0; m < 4; ++m)
 #pragma unroll
                 for (int j = 0; j < NSUB; ++j)
-                    acc[m][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av[m], bv[j], acc[m][j], 0, 0, 0);
+                    acc[m][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(bv[j], av[m], acc[m][j], 0, 0, 0);
         }
         __syncthreads();
     }
-    // D rows 4q .. 4q+3 are x offsets, column r an output channel
+    // D rows 4q .. 4q+3 are output channels, column r the voxel x0 + r
+    const int64_t vfirst = ((((int64_t)smp << lg) + z0 + wave) << (2 * lg)) +
+                           ((int64_t)y0 << lg) + x0 + r;
 #pragma unroll
-    for (int m = 0; m < 4; ++m) {
-        const int64_t vrow = ((((int64_t)smp << lg) + z0 + wave) << (2 * lg)) +
-                             ((int64_t)(y0 + m) << lg) + x0;
+    for (int j = 0; j < NSUB; ++j) {
+        const int co = cobase + j * 16 + q * 4;
+        const floatx4 bias = bias_quad(a, co);
+        bf16x4 mask[4];
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const int64_t vo = vrow + q * 4 + i;
+        for (int m = 0; m < 4; ++m) mask[m] = mask_quad(a, vfirst + ((int64_t)m << lg), co);
 #pragma unroll
-            for (int j = 0; j < NSUB; ++j) {
-                const int co = cobase + j * 16 + r;
-                if (co < a.ys) {
-                    float val = 0.f;
-                    if (co < a.cout) {
-                        val = acc[m][j][i] + (a.bias ? a.bias[co] : 0.f);
-                        if (a.relu) val = fmaxf(val, 0.f);
-                        if (a.omask && !((float)a.omask[vo * a.ys + co] > 0.f)) val = 0.f;
-                    }
-                    a.out[vo * a.ys + co] = (__bf16)val;
-                }
-            }
-        }
+        for (int m = 0; m < 4; ++m)
+            store_quad(a, vfirst + ((int64_t)m << lg), co, acc[m][j], bias, mask[m]);
     }
 }
 
@@ -1659,16 +1702,14 @@ k_conv_small(ConvArgs a, float* __restrict__ part) {
 #pragma unroll
         for (int m = 0; m < 4; ++m) av[m] = *(const bf16x8*)(xsb + va + (toff + m * 20) * kCvVox * 2);
 #pragma unroll
-        for (int m = 0; m < 4; ++m) acc[m] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av[m], bv, acc[m], 0, 0, 0);
+        for (int m = 0; m < 4; ++m) acc[m] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(bv, av[m], acc[m], 0, 0, 0);
     }
-    // D rows 4q .. 4q+3 of tile m are voxels 16 m + 4 q + i of the plane, column r a channel
+    // D rows 4q .. 4q+3 of tile m are output channels, column r the plane's voxel 16 m + r
     const int Cp = gridDim.y * 16;
     float* pp = part + ((int64_t)chunk * a.n + smp) * 512 * Cp;
 #pragma unroll
     for (int m = 0; m < 4; ++m)
-#pragma unroll
-        for (int i = 0; i < 4; ++i)
-            pp[(int64_t)(wave * 64 + 16 * m + 4 * q + i) * Cp + cobase + r] = acc[m][i];
+        *(floatx4*)(pp + (int64_t)(wave * 64 + 16 * m + r) * Cp + cobase + 4 * q) = acc[m];
 }
 
 // out[v][co] = (ReLU)(bias + sum over the nch input groups of the partials,
