@@ -24,6 +24,7 @@
 #include <stdint.h>
 
 #include <algorithm>
+#include <atomic>
 
 #include "nn_internal.hpp"
 
@@ -1421,107 +1422,140 @@ __global__ void k_cf_to_cl(const float* __restrict__ x, int n, int64_t V, int c,
 
 // Forward / input-gradient convolution on LDS-staged bricks (3x3x3 taps,
 // BF16 output, grids of at least 16 cells, input channels a multiple of 16,
-// or 8 with no second tensor).  A block of 8 waves computes 16 x 4 x 8 output
-// voxels (wave w the plane z0 + w, its four 16-voxel row tiles y0 .. y0 + 3)
-// for NSUB * 16 output channels.  Per 16 input channels the block copies the
-// 18 x 6 x 10 input halo (channels-last, 32 bytes per voxel: lane r reads
-// voxel r and its second 8 channels sit 16 bytes on, which the LDS serves
-// without bank conflicts) and the chunk's weights into LDS with direct-to-LDS
-// buffer loads (no register staging, every load of the chunk in flight at
-// once), so every A fragment (8 channels of one voxel for one tap) is one LDS
-// read.  A k step of 32 takes two taps of the 16 channels, paired so that
-// the second lies a fixed displacement from the first within each group of
-// steps (two planes on, two rows on, two voxels on, or a slot of zero
-// weights): a lane's LDS addresses are then a base register per group plus
-// a compile-time offset, with no per-step index arithmetic.
+// or 8 with no second tensor).  A block of 8 WY waves computes bricks of 16 x
+// 4 WY x 8 output voxels (wave w the plane z0 + w % 8, the four 16-voxel row
+// tiles from y0 + 4 (w / 8)) for NSUB * 16 output channels.  A step takes 16
+// input channels of a brick: the 18 x (4 WY + 2) x 10 input halo
+// (channels-last, 32 bytes per voxel: lane r reads voxel r and its second 8
+// channels sit 16 bytes on, which the LDS serves without bank conflicts) and
+// the chunk's weights, copied into LDS with direct-to-LDS buffer loads, so
+// every fragment is one LDS read.  A k step of 32 takes two taps of the 16
+// channels, paired so that the second lies a fixed displacement from the first
+// within each group of steps (two planes on, two rows on, two voxels on, or a
+// slot of zero weights): a lane's LDS addresses are then a base register per
+// group plus a compile-time offset, with no per-step index arithmetic.
+//
+// A block walks a range of bricks with two halo buffers: the copies of step
+// s + 1 are in flight during the products of step s.  What had bound the
+// one-brick-a-block form of this kernel was each block's chain of launch,
+// address decode, copy round trip and stores (64^3, batch 8, 16 -> 16
+// channels: 46 us, of which 28 with neither copies nor products), at 25% of
+// the matrix cores, 25% of the LDS and 46% of HBM.
 constexpr int kCvVox = 16;                  // LDS elements per voxel
-constexpr int kCvPlanes = 8;                // output planes (waves) per block
-constexpr int kCvHalo = 18 * 6 * (kCvPlanes + 2);  // halo voxels
-constexpr int kCvHaloItems = 2 * kCvHalo;   // 16-byte halo items of a chunk
-constexpr int kCvHaloBuf = kCvHaloItems + 16;  // + the tail of the last partial wave
+constexpr int kCvPlanes = 8;                // output planes per brick
 constexpr int kCvSlots = 28;                // 27 taps + a zero-weight slot
 constexpr int kCvWItemsRow = 2 * kCvSlots + 2;  // 16-byte weight items per row (+ 32 B pad)
 constexpr int kCvWRow = 8 * kCvWItemsRow;   // elements per LDS weight row (928 B, 32 mod 64)
 
 // Step p (0..13) of the k loop takes tap p in lanes q < 2 and tap
-// cv_pair_tap(p) in lanes q >= 2 (-1: the zero slot); cv_pair_shift(p) is
-// the second tap's halo position minus the first's, in voxels.
+// cv_pair_tap(p) in lanes q >= 2 (-1: the zero slot), two planes, two rows or
+// two voxels on (or anywhere, with zero weights).
 __device__ constexpr int cv_pair_tap(int p) {
     return p <= 8 ? p + 18 : p <= 11 ? p + 6 : p == 12 ? 14 : -1;
 }
-__device__ constexpr int cv_pair_shift(int p) {
-    return p <= 8 ? 2 * 108 : p <= 11 ? 2 * 18 : p == 12 ? 2 : 0;
-}
-// halo position of tap t = (dz + 1) * 9 + (dy + 1) * 3 + dx + 1, relative to
-// the output voxel's (-1, -1, -1) neighbour
-__device__ constexpr int cv_tap_offset(int t) { return (t / 9) * 108 + ((t / 3) % 3) * 18 + t % 3; }
 
-template <int NSUB>
-__global__ void __launch_bounds__(64 * kCvPlanes)
-    __attribute__((amdgpu_waves_per_eu(NSUB == 1 ? 6 : 4))) k_conv_brick(ConvArgs a) {
-    constexpr int kThreads = 64 * kCvPlanes;
-    constexpr int kWItems = NSUB * 16 * kCvWItemsRow;
-    constexpr int kWBuf = (kWItems + 63) / 64 * 64;  // whole waves of 16-byte items
-    __shared__ __attribute__((aligned(16))) __bf16 xs[kCvHaloBuf * 8];
-    __shared__ __attribute__((aligned(16))) __bf16 wl[kWBuf * 8];
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+// Direct-to-LDS copy of 16 bytes per lane, from byte off of the buffer (zeros
+// past its end) to LDS byte `lds` (the wave's, in a scalar) plus 16 times the
+// lane.  Written as an instruction because the compiler, which cannot tell the
+// two halo buffers apart across the loop, would wait for the copies of the
+// next step before every LDS read of this one; it has no register result.
+// The waits are the caller's: copies_landed.
+typedef int intx4 __attribute__((ext_vector_type(4)));
+__device__ __forceinline__ intx4 buffer_words(const void* base, uint32_t bytes) {
+    const uint64_t p = (uint64_t)base;
+    return intx4{__builtin_amdgcn_readfirstlane((int)(uint32_t)p),
+                 __builtin_amdgcn_readfirstlane((int)(uint32_t)(p >> 32) & 0xFFFF),
+                 __builtin_amdgcn_readfirstlane((int)bytes), 0x00020000};
+}
+__device__ __forceinline__ void copy_to_lds(intx4 rsrc, uint32_t lds, uint32_t off) {
+    __asm__ volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds"
+                     :
+                     : "s"(lds), "v"(off), "s"(rsrc)
+                     : "memory");
+}
+// Waits until at most `later` of this wave's vector-memory operations are
+// outstanding (they finish in order) and its LDS reads are done, then for the
+// block's other waves.
+template <int later>
+__device__ __forceinline__ void copies_landed() {
+    static_assert(later < 16, "low bits of the count");
+    __asm__ volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" : : "n"(later) : "memory");
+}
+
+template <int NSUB, int WY, bool ONE>
+struct CvShape {
+    static constexpr int rows = 4 * WY + 2;        // halo rows
+    static constexpr int plane = 18 * rows;        // halo voxels per plane
+    static constexpr int items = 2 * plane * (kCvPlanes + 2);  // 16-byte halo items
+    static constexpr int buf = (items + 63) / 64 * 64;
+    static constexpr int threads = 64 * kCvPlanes * WY;
+    static constexpr int halo_it = (items + threads - 1) / threads;
+    static constexpr int witems = NSUB * 16 * kCvWItemsRow;
+    static constexpr int wbuf = (witems + 63) / 64 * 64;
+    static constexpr int weight_it = (wbuf + threads - 1) / threads;
+    static constexpr int wsets = ONE ? 1 : 2;      // weight buffers
+    static constexpr int lds_items = 2 * buf + wsets * wbuf;
+    static_assert(lds_items * 16 <= 160 * 1024, "one block's LDS");
+};
+
+// ONE: one step a brick (at most 16 input channels), so the weights are
+// copied once.  EPI: what the results take (kPlain; kBias: bias and ReLU;
+// kMask: 0 where the mask is not positive).  work: bricks in all, per: bricks
+// per block.  The output channels are a multiple of 16.
+//
+// Everything outside the products is kept short, for it takes the issue slots
+// of all waves in step: addresses are a lane register plus scalars, and the
+// results have no branches.  (With general results and per-item address
+// arithmetic, 184 vector and 272 scalar instructions a wave and step beside
+// the 56 products, the same walk took 41-43 us instead of 30-33.)
+enum { kPlain, kBias, kMask };
+
+template <int NSUB, int WY, bool ONE, int EPI>
+__global__ void __launch_bounds__(64 * kCvPlanes * WY)
+k_conv_brick(ConvArgs a, int work, int per) {
+    using C = CvShape<NSUB, WY, ONE>;
+    typedef unsigned uintx2 __attribute__((ext_vector_type(2)));
+    __shared__ __attribute__((aligned(16))) __bf16 lds[C::lds_items * 8];
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int r = lane & 15, q = lane >> 4, hi = q >> 1;
-    const int lg = a.lg, G = 1 << lg;
+    const int lg = a.lg, h = lg - 1, G = 1 << lg;
     // blocks i, i + 8, ... run on one XCD (dispatch is round-robin over the
-    // eight): give each XCD a contiguous range of bricks, whose halos overlap
-    // in its L2 (the grid's x size is a multiple of 8 for G >= 16)
-    const uint32_t bid = (blockIdx.x % 8) * (gridDim.x / 8) + blockIdx.x / 8;
-    const int x0 = (int)(bid & ((1u << (lg - 4)) - 1)) * 16;
-    const int y0 = (int)((bid >> (lg - 4)) & ((1u << (lg - 2)) - 1)) * 4;
-    const int z0 = (int)((bid >> (2 * lg - 6)) & ((1u << (lg - 3)) - 1)) * kCvPlanes;
-    const int smp = (int)(bid >> (3 * lg - 9));
+    // eight): give each XCD contiguous ranges of bricks, whose halos overlap
+    // in its L2
+    const int nb = (int)gridDim.x;
+    const int range = nb % 8 ? (int)blockIdx.x : (int)(blockIdx.x % 8) * (nb / 8) + (int)blockIdx.x / 8;
+    const int b0 = range * per, b1 = b0 + per < work ? b0 + per : work;
+    if (b0 >= b1) return;
     const int cobase = blockIdx.y * NSUB * 16;
-    floatx4 acc[4][NSUB];
-#pragma unroll
-    for (int m = 0; m < 4; ++m)
-#pragma unroll
-        for (int j = 0; j < NSUB; ++j) acc[m][j] = floatx4{0.f, 0.f, 0.f, 0.f};
-    const int ch = (q & 1) * 8;
-    // LDS byte addresses of this lane: A (halo) per shift group, B (weights)
-    const uint32_t lb = (uint32_t)(wave * 108 + r);
-    const uint32_t vA0 = ((lb + hi * 2 * 108) * kCvVox + ch) * 2;
-    const uint32_t vA1 = ((lb + hi * 2 * 18) * kCvVox + ch) * 2;
-    const uint32_t vA2 = ((lb + hi * 2) * kCvVox + ch) * 2;
-    const uint32_t vA3 = (lb * kCvVox + ch) * 2;
-    const uint32_t vB = (uint32_t)(r * kCvWRow + hi * 16 + ch) * 2;
-    const char* xsb = (const char*)xs;
-    const char* wlb = (const char*)wl;
-    // Loads go through range-checked buffer resources: a position outside
-    // the grid (or the tensor, or a weight item of the zero slot or padding)
-    // gets an offset with bit 31 set, reads past the end and lands as zeros.
-    // The lane's items are decoded once, before the chunk loop: item i is
-    // voxel tid / 2 + 256 i of the halo (channel half tid % 2), 4 cells, 2 rows
-    // and 2 planes on from item i - 1, with carries.  vox: the voxel's number,
-    // bit 31 where there is none.
-    // (Decoded per chunk with divisions, the copies' addresses took more of
-    // the vector units than the products of the matrix cores.)
-    constexpr int kHaloIt = (kCvHaloItems + kThreads - 1) / kThreads;
-    constexpr int kWIt = (kWBuf + kThreads - 1) / kThreads;
-    static_assert(kThreads / 2 == 2 * 108 + 2 * 18 + 4, "the items' stride");
-    const int h = lg - 1;
+    const int chunks = ONE ? 1 : a.cin / 16;
+    // The lane's copy items, decoded once: item i is voxel tid / 2 + i threads
+    // / 2 of the halo (channel half tid % 2).  fine, coarse: its byte in x1 (in
+    // x2, at its parent) from the halo's first voxel; side: the sides of the
+    // halo it lies on (a brick at that side of the grid reads zeros there).
+    // Items that read zeros take offsets with bit 31 set (samples are below
+    // 2^31 bytes): past the buffer's end.
+    constexpr int kHalf = C::threads / 2;
+    constexpr uint32_t kOutside = 0x80000000u;
     const int half = tid & 1;
-    uint32_t vox[kHaloIt], wofs[kWIt];
+    uint32_t fine[C::halo_it], coarse[C::halo_it], side[C::halo_it], wofs[C::weight_it];
     {
-        int hx = (tid >> 1) % 18, hy = ((tid >> 1) / 18) % 6, hz = (tid >> 1) / 108;
-        const bool no_half = half * 8 >= a.cin;  // 8 input channels: the upper half is zeros
+        int hx = (tid >> 1) % 18, hy = ((tid >> 1) / 18) % C::rows, hz = (tid >> 1) / C::plane;
 #pragma unroll
-        for (int i = 0; i < kHaloIt; ++i) {
-            const int xx = x0 + hx - 1, yy = y0 + hy - 1, zz = z0 + hz - 1;
-            const bool ok = i * kThreads + tid < kCvHaloItems && !no_half &&
-                            (unsigned)xx < (unsigned)G && (unsigned)yy < (unsigned)G &&
-                            (unsigned)zz < (unsigned)G;
-            vox[i] = ok ? ((uint32_t)zz << (2 * lg)) + ((uint32_t)yy << lg) + (uint32_t)xx
-                        : 0x80000000u;
-            hx += 4;
+        for (int i = 0; i < C::halo_it; ++i) {
+            const bool never = i * C::threads + tid >= C::items || half * 8 >= a.cin;
+            const int v1 = (hz << (2 * lg)) + (hy << lg) + hx;
+            const int v2 = ((hz + 1) >> 1 << (2 * h)) + ((hy + 1) >> 1 << h) + ((hx + 1) >> 1);
+            fine[i] = never ? kOutside : (uint32_t)(v1 * a.c1s + half * 8) * 2u;
+            coarse[i] = never ? kOutside : (uint32_t)(v2 * a.c2 + half * 8) * 2u;
+            side[i] = (uint32_t)((hx == 0) | (hx == 17) << 1 | (hy == 0) << 2 |
+                                 (hy == C::rows - 1) << 3 | (hz == 0) << 4 |
+                                 (hz == kCvPlanes + 1) << 5 | never << 6);
+            hx += kHalf % 18;
             if (hx >= 18) hx -= 18, ++hy;
-            hy += 2;
-            if (hy >= 6) hy -= 6, ++hz;
-            hz += 2;
+            hy += kHalf % C::plane / 18;
+            if (hy >= C::rows) hy -= C::rows, ++hz;
+            hz += kHalf / C::plane;
         }
         // weight item t: row t / 58 (output channel cobase + row), slot s =
         // (t % 58) / 2 (tap s / 2 for even s, the paired tap for odd s), 8
@@ -1529,88 +1563,208 @@ __global__ void __launch_bounds__(64 * kCvPlanes)
         // input channels the upper half holds the next tap's weights, which
         // meet zero inputs, and stays inside the row since 27 * 8 + 8 <= kpad.)
 #pragma unroll
-        for (int i = 0; i < kWIt; ++i) {
-            const int t = i * kThreads + tid;
+        for (int i = 0; i < C::weight_it; ++i) {
+            const int t = i * C::threads + tid;
             const int row = t / kCvWItemsRow, rem = t - row * kCvWItemsRow;
             const int slot = rem >> 1, p = slot >> 1;
             const int tap = (slot & 1) ? cv_pair_tap(p) : p;
-            const bool ok = t < kWItems && rem < 2 * kCvSlots && tap >= 0 && cobase + row < a.wrows;
+            const bool ok = t < C::witems && rem < 2 * kCvSlots && tap >= 0;
             wofs[i] = ok ? (uint32_t)((cobase + row) * a.kpad + tap * a.cin + (rem & 1) * 8) * 2u
-                         : 0x80000000u;
+                         : kOutside;
         }
     }
-    const int wv = __builtin_amdgcn_readfirstlane(wave);
-    for (int c0 = 0; c0 < a.cin; c0 += 16) {
-        const bool lo = c0 < a.c1s;  // x1's channels, else x2's (c1s is then a multiple of 16)
-        const int chans = lo ? a.c1s : a.c2;
-        const int hl = lo ? lg : h;  // the tensor's grid: 2^hl cells a side
-        const int64_t vs = (int64_t)1 << (3 * hl);
-        const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(
-            const_cast<__bf16*>((lo ? a.x1 : a.x2) + (int64_t)smp * vs * chans), (short)0,
-            (int)(uint32_t)(vs * chans * 2), 0x00020000);
-        const int cloc = lo ? c0 : c0 - a.c1s;
-        // halo item t (voxel t / 2, channel half t % 2) lands at LDS byte 16 t
-        // (voxel numbers are below 2^24: 24-bit products)
+    // What a brick's copies and results take from its place, in scalars: the
+    // sample, the first voxel (out: of the brick; fine, coarse: of the halo, in
+    // x1 and x2) and the sides of the grid it lies at.  Bricks run x fastest,
+    // then y, z, sample.  (Comparisons as sign bits: as truth values the
+    // compiler takes them through vector registers.)
+    struct Place {
+        int smp, out, fine, coarse;
+        uint32_t sides;
+    };
+    auto place = [&](int b) __attribute__((always_inline)) {
+        constexpr int ly = WY == 2 ? 3 : 2;
+        const int x0 = (b & ((1 << (lg - 4)) - 1)) * 16;
+        b >>= lg - 4;
+        const int y0 = (b & ((1 << (lg - ly)) - 1)) * (4 * WY);
+        b >>= lg - ly;
+        const int z0 = (b & ((1 << (lg - 3)) - 1)) * kCvPlanes;
+        auto negative = [](int v) { return (uint32_t)v >> 31; };
+        Place o;
+        o.smp = b >> (lg - 3);
+        o.out = (z0 << (2 * lg)) + (y0 << lg) + x0;
+        o.fine = ((z0 - 1) << (2 * lg)) + ((y0 - 1) << lg) + x0 - 1;
+        o.coarse = ((z0 / 2 - 1) << (2 * h)) + ((y0 / 2 - 1) << h) + x0 / 2 - 1;
+        o.sides = negative(x0 - 1) | negative(G - 17 - x0) << 1 | negative(y0 - 1) << 2 |
+                  negative(G - 4 * WY - 1 - y0) << 3 | negative(z0 - 1) << 4 |
+                  negative(G - kCvPlanes - 1 - z0) << 5 | 64u;
+        return o;
+    };
+    const uint32_t lds0 = (uint32_t)(uintptr_t)(lds_void_ptr)&lds[0];
+    const intx4 rw = buffer_words(a.w, (uint32_t)((int64_t)a.wrows * a.kpad * 2));
+    const __bf16 *x1 = a.x1, *x2 = a.x2;  // held in scalars, not fetched again each step
+    __asm__ volatile("" : "+s"(x1), "+s"(x2));
+    const int64_t sample1 = (int64_t)a.c1s << (3 * lg), sample2 = (int64_t)a.c2 << (3 * h);
+    // the copies of a step into halo buffer (and weight buffer) `to`
+    auto issue = [&](const Place& o, int chunk, int to, bool weights) __attribute__((always_inline)) {
+        const int c0 = chunk * 16;
+        const uint32_t dst = lds0 + (uint32_t)(to * C::buf) * 16u;
+        auto halo = [&](const uint32_t (&item)[C::halo_it], const __bf16* x, int64_t sample,
+                        int first, int chans, int c) __attribute__((always_inline)) {
+            const intx4 rs = buffer_words(x + o.smp * sample, (uint32_t)(sample * 2));
+            const uint32_t from = (uint32_t)(first * chans + c) * 2u;
 #pragma unroll
-        for (int i = 0; i < kHaloIt; ++i) {
-            const int tb = i * kThreads + wv * 64;
-            if (tb >= kCvHaloItems) continue;
-            uint32_t v = vox[i];
-            if (!lo) {  // the coarse tensor: the cell's parent
-                const uint32_t hm = (1u << h) - 1;
-                v = (v & 0x80000000u) | ((v >> (2 * lg + 1) & hm) << (2 * h)) |
-                    ((v >> (lg + 1) & hm) << h) | (v >> 1 & hm);
+            for (int i = 0; i < C::halo_it; ++i) {
+                const int tb = i * C::threads + wave * 64;
+                if (tb >= C::items) continue;
+                const uint32_t v = item[i] + from;
+                const uint32_t off = side[i] & o.sides ? kOutside : v;
+                copy_to_lds(rs, dst + (uint32_t)tb * 16u, off);
             }
-            const uint32_t off = (__umul24(v, (uint32_t)chans * 2u) +
-                                  (uint32_t)(cloc + half * 8) * 2u) | (v & 0x80000000u);
-            __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (lds_void_ptr)&xs[tb * 8], 16, off, 0, 0, 0);
-        }
-        const __amdgpu_buffer_rsrc_t rw = __builtin_amdgcn_make_buffer_rsrc(
-            const_cast<__bf16*>(a.w), (short)0, (int)(uint32_t)((int64_t)a.wrows * a.kpad * 2),
-            0x00020000);
+        };
+        if (ONE || c0 < a.c1s)  // x1's channels, else x2's (c1s is then a multiple of 16)
+            halo(fine, x1, sample1, o.fine, a.c1s, c0);
+        else
+            halo(coarse, x2, sample2, o.coarse, a.c2, c0 - a.c1s);
+        if (!weights) return;
+        const uint32_t wdst = lds0 + (uint32_t)(2 * C::buf + (ONE ? 0 : to * C::wbuf)) * 16u;
 #pragma unroll
-        for (int i = 0; i < kWIt; ++i) {
-            const int tb = i * kThreads + wv * 64;
-            if (tb >= kWBuf) continue;
+        for (int i = 0; i < C::weight_it; ++i) {
+            const int tb = i * C::threads + wave * 64;
+            if (tb >= C::wbuf) continue;
             const uint32_t off = wofs[i] + (uint32_t)c0 * 2u;
-            __builtin_amdgcn_raw_ptr_buffer_load_lds(rw, (lds_void_ptr)&wl[tb * 8], 16, off, 0, 0, 0);
+            copy_to_lds(rw, wdst + (uint32_t)tb * 16u, off);
         }
-        // this wave's copies have landed (vmcnt 0; expcnt and lgkmcnt left at their maxima)
-        __builtin_amdgcn_s_waitcnt((7 << 4) | (15 << 8));
-        __syncthreads();
+    };
+    floatx4 acc[4][NSUB];
+    const int ch = (q & 1) * 8;
+    // LDS byte addresses of this lane: A (weights), B (halo) per shift group
+    const uint32_t lb = (uint32_t)((wave & 7) * C::plane + (wave >> 3) * 4 * 18 + r);
+    const uint32_t vB0 = ((lb + hi * 2 * C::plane) * kCvVox + ch) * 2;
+    const uint32_t vB1 = ((lb + hi * 2 * 18) * kCvVox + ch) * 2;
+    const uint32_t vB2 = ((lb + hi * 2) * kCvVox + ch) * 2;
+    const uint32_t vB3 = (lb * kCvVox + ch) * 2;
+    uint32_t vA = (uint32_t)(2 * C::buf * 16 + (r * kCvWRow + hi * 16 + ch) * 2);
+    __asm__ volatile("" : "+v"(vA));  // (as a constant it would pass the reads' 16-bit offsets)
+    // D rows 4q .. 4q+3 are output channels, column r the voxel x0 + r: the
+    // lane's byte from the brick's first voxel, per tile a row further
+    const uint32_t vout =
+        (uint32_t)(((((wave & 7) << (2 * lg)) + ((wave >> 3) * 4 << lg) + r) * a.ys) + cobase + 4 * q) * 2u;
+    const uint32_t row_bytes = (uint32_t)a.ys * 2u << lg;
+    const int64_t sample_out = (int64_t)a.ys << (3 * lg);
+    floatx4 bias[NSUB];
+    if constexpr (EPI == kBias) {
 #pragma unroll
-        for (int p = 0; p < 14; ++p) {
-            const int d = cv_pair_shift(p);
-            const uint32_t va = d == 2 * 108 ? vA0 : d == 2 * 18 ? vA1 : d == 2 ? vA2 : vA3;
-            const int toff = cv_tap_offset(p);
-            bf16x8 bv[NSUB], av[4];
+        for (int j = 0; j < NSUB; ++j)
 #pragma unroll
-            for (int j = 0; j < NSUB; ++j)
-                bv[j] = *(const bf16x8*)(wlb + vB + (j * 16 * kCvWRow + p * 32) * 2);
-#pragma unroll
-            for (int m = 0; m < 4; ++m)
-                av[m] = *(const bf16x8*)(xsb + va + (toff + m * 18) * kCvVox * 2);
-#pragma unroll
-            for (int m = 0; m < 4; ++m)
-#pragma unroll
-                for (int j = 0; j < NSUB; ++j)
-                    acc[m][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(bv[j], av[m], acc[m][j], 0, 0, 0);
-        }
-        __syncthreads();
+            for (int i = 0; i < 4; ++i) bias[j][i] = a.bias[cobase + j * 16 + 4 * q + i];
     }
-    // D rows 4q .. 4q+3 are output channels, column r the voxel x0 + r
-    const int64_t vfirst = ((((int64_t)smp << lg) + z0 + wave) << (2 * lg)) +
-                           ((int64_t)y0 << lg) + x0 + r;
-#pragma unroll
-    for (int j = 0; j < NSUB; ++j) {
-        const int co = cobase + j * 16 + q * 4;
-        const floatx4 bias = bias_quad(a, co);
-        bf16x4 mask[4];
-#pragma unroll
-        for (int m = 0; m < 4; ++m) mask[m] = mask_quad(a, vfirst + ((int64_t)m << lg), co);
+    const float floor = a.relu ? 0.f : -INFINITY;
+    auto clear = [&]() __attribute__((always_inline)) {
 #pragma unroll
         for (int m = 0; m < 4; ++m)
-            store_quad(a, vfirst + ((int64_t)m << lg), co, acc[m][j], bias, mask[m]);
+#pragma unroll
+            for (int j = 0; j < NSUB; ++j) acc[m][j] = floatx4{0.f, 0.f, 0.f, 0.f};
+    };
+    clear();
+    int chunk = 0, set = 0;
+    bool stored = false;  // whether the step before ended a brick
+    Place o = place(b0);
+    issue(o, 0, 0, true);
+    for (int b = b0; b < b1;) {
+        // this step's copies have landed (only the last brick's stores were
+        // issued after them), and every wave is done with the other buffer
+        if (stored)
+            copies_landed<4 * NSUB>();
+        else
+            copies_landed<0>();
+        const bool last = ONE || chunk + 1 == chunks;
+        const uint32_t first = vout + (uint32_t)o.out * (uint32_t)a.ys * 2u;
+        // the mask is loaded ahead of the products
+        uintx2 mask[EPI == kMask ? 4 * NSUB : 1];
+        if constexpr (EPI == kMask) {
+            if (last) {
+                const __amdgpu_buffer_rsrc_t rm = __builtin_amdgcn_make_buffer_rsrc(
+                    const_cast<__bf16*>(a.omask + o.smp * sample_out), (short)0,
+                    (int)(uint32_t)(sample_out * 2), 0x00020000);
+#pragma unroll
+                for (int m = 0; m < 4; ++m)
+#pragma unroll
+                    for (int j = 0; j < NSUB; ++j) {
+                        const uint32_t off = first + m * row_bytes + j * 32;
+                        mask[m * NSUB + j] = __builtin_amdgcn_raw_buffer_load_b64(rm, off, 0, 0);
+                    }
+            }
+        }
+        const char* xsb = (const char*)lds + set * C::buf * 16;
+        const char* wlb = (const char*)lds + (ONE ? 0 : set * C::wbuf * 16);
+        auto products = [&](int p0, int p1) __attribute__((always_inline)) {
+#pragma unroll
+            for (int p = p0; p < p1; ++p) {
+                const uint32_t vb = p <= 8 ? vB0 : p <= 11 ? vB1 : p == 12 ? vB2 : vB3;
+                // tap p's halo position
+                const int toff = (p / 9) * C::plane + ((p / 3) % 3) * 18 + p % 3;
+                bf16x8 av[NSUB], bv[4];
+#pragma unroll
+                for (int j = 0; j < NSUB; ++j)
+                    av[j] = *(const bf16x8*)(wlb + vA + (j * 16 * kCvWRow + p * 32) * 2);
+#pragma unroll
+                for (int m = 0; m < 4; ++m)
+                    bv[m] = *(const bf16x8*)(xsb + vb + (toff + m * 18) * kCvVox * 2);
+#pragma unroll
+                for (int m = 0; m < 4; ++m)
+#pragma unroll
+                    for (int j = 0; j < NSUB; ++j)
+                        acc[m][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av[j], bv[m], acc[m][j],
+                                                                            0, 0, 0);
+                // (reads of many k steps ahead would spill with three groups' results)
+                if constexpr (NSUB == 3) __builtin_amdgcn_sched_barrier(0);
+            }
+        };
+        // With several chunks a brick the next step's copies are issued after
+        // the first products, so that the scalar work for them runs beside the
+        // matrix cores (48 channels at 64^3 88 -> 86 us); with one, where the
+        // stores of every step make memory the bound, before them (16 -> 48
+        // channels 73 us, 78 after).
+        constexpr int kAhead = ONE ? 0 : 2;
+        products(0, kAhead);
+        int nbk = b, nch = chunk + 1;
+        Place on = o;
+        if (last) {
+            nbk = b + 1;
+            nch = 0;
+            on = place(nbk);
+        }
+        if (nbk < b1) issue(on, nch, set ^ 1, !ONE);
+        products(kAhead, 14);
+        if (last) {
+            const __amdgpu_buffer_rsrc_t ro = __builtin_amdgcn_make_buffer_rsrc(
+                a.out + o.smp * sample_out, (short)0, (int)(uint32_t)(sample_out * 2), 0x00020000);
+#pragma unroll
+            for (int m = 0; m < 4; ++m)
+#pragma unroll
+                for (int j = 0; j < NSUB; ++j) {
+                    bf16x4 v;
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) {
+                        float t = acc[m][j][i];
+                        if constexpr (EPI == kBias) t = fmaxf(t + bias[j][i], floor);
+                        if constexpr (EPI == kMask) {
+                            const bf16x4 k = __builtin_bit_cast(bf16x4, mask[m * NSUB + j]);
+                            t = (float)k[i] > 0.f ? t : 0.f;
+                        }
+                        v[i] = (__bf16)t;
+                    }
+                    const uint32_t off = first + m * row_bytes + j * 32;
+                    __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(uintx2, v), ro, off, 0, 0);
+                }
+            clear();
+        }
+        stored = last;
+        o = on;
+        b = nbk;
+        chunk = nch;
+        set ^= 1;
     }
 }
 
@@ -1756,6 +1910,67 @@ hipError_t launch_conv_mt(const ConvArgs& a, int coutp, hipStream_t s) {
     return hipGetLastError();
 }
 
+// Compute units of the current device (asked once per device; 256 if the
+// runtime cannot say).
+int compute_units() {
+    static std::atomic<int> known[64];
+    int dev = 0, cus = 0;
+    if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return 256;
+    cus = known[dev].load(std::memory_order_relaxed);
+    if (cus > 0) return cus;
+    if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
+        cus <= 0)
+        return 256;
+    known[dev].store(cus, std::memory_order_relaxed);
+    return cus;
+}
+
+// Bricks of 8 rows (1024 threads) when they give every compute unit one, else
+// of 4 rows; about one block per compute unit (its LDS holds one), each
+// walking the same number of bricks.
+template <int NSUB, int WY, bool ONE>
+hipError_t launch_conv_wy(const ConvArgs& a, int groups, int64_t bricks, hipStream_t s) {
+    const int64_t most = std::max<int64_t>(1, compute_units() / groups);
+    const int64_t per = (bricks + most - 1) / most;
+    const dim3 grid((unsigned)((bricks + per - 1) / per), groups), block(64 * kCvPlanes * WY);
+    const int w = (int)bricks, p = (int)per;
+    if (a.omask)
+        hipLaunchKernelGGL((k_conv_brick<NSUB, WY, ONE, kMask>), grid, block, 0, s, a, w, p);
+    else if (a.bias)
+        hipLaunchKernelGGL((k_conv_brick<NSUB, WY, ONE, kBias>), grid, block, 0, s, a, w, p);
+    else
+        hipLaunchKernelGGL((k_conv_brick<NSUB, WY, ONE, kPlain>), grid, block, 0, s, a, w, p);
+    return hipGetLastError();
+}
+
+// Whether the brick kernel covers the convolution.  (8 input channels, the
+// first layer, take a 16-channel group whose upper half reads zeros; its
+// weight rows there hold the next tap's weights, which multiply those zeros,
+// and stay inside the row since 27 * 8 + 8 <= kpad.)
+bool conv_brick_covers(const ConvArgs& a, int coutp) {
+    return a.taps == 27 && a.lg >= 4 && a.kpad >= 27 * a.cin &&
+           (a.cin % 16 == 0 || (a.cin == 8 && a.c2 == 0)) && (a.c2 == 0 || a.c1s % 16 == 0) &&
+           a.cout == coutp && a.ys == coutp && !(a.omask && a.bias) && (a.bias || !a.relu);
+}
+
+hipError_t launch_conv_brick(const ConvArgs& args, int coutp, hipStream_t s) {
+    ConvArgs a = args;
+    a.wrows = coutp;
+    const int sub = coutp / 16;
+    const int64_t G = (int64_t)1 << a.lg, tall = a.n * (G / 16) * (G / 8) * (G / kCvPlanes);
+    if (a.cin <= 16) {
+        // three output groups share a step's halo where they are what there is
+        if (sub % 3 == 0 && tall * (sub / 3) >= compute_units())
+            return launch_conv_wy<3, 2, true>(a, sub / 3, tall, s);
+        if (tall * sub >= compute_units()) return launch_conv_wy<1, 2, true>(a, sub, tall, s);
+        return launch_conv_wy<1, 1, true>(a, sub, 2 * tall, s);
+    }
+    if (sub % 3 == 0 && 2 * tall * (sub / 3) >= compute_units())
+        return launch_conv_wy<3, 1, false>(a, sub / 3, 2 * tall, s);
+    if (tall * sub >= compute_units()) return launch_conv_wy<1, 2, false>(a, sub, tall, s);
+    return launch_conv_wy<1, 1, false>(a, sub, 2 * tall, s);
+}
+
 // Four voxel tiles per wave when that still leaves at least 2048 blocks (so
 // each weight fragment serves 64 voxels).  Otherwise one tile, and the k
 // range is split over 2 or 4 waves per block when there are fewer than
@@ -1779,29 +1994,8 @@ hipError_t launch_conv(const ConvArgs& a, int coutp, float* scratch, int64_t scr
                            a.out);
         return hipGetLastError();
     }
+    if (conv_brick_covers(a, coutp)) return launch_conv_brick(a, coutp, s);
     const int nsub = sub % 4 == 0 ? 4 : sub % 3 == 0 ? 3 : sub % 2 == 0 ? 2 : 1;
-    // (8 input channels, the first layer, take a 16-channel group whose upper
-    // half reads zeros; its weight rows there hold the next tap's weights,
-    // which multiply those zeros, and stay inside the row since 27 * 8 + 8 <=
-    // kpad.)
-    if (a.taps == 27 && a.lg >= 4 && a.kpad >= 27 * a.cin &&
-        (a.cin % 16 == 0 || (a.cin == 8 && a.c2 == 0)) && (a.c2 == 0 || a.c1s % 16 == 0)) {
-        // one output-channel group per block (more blocks, fewer registers),
-        // except for 3 groups of 16 on grids of 32 and more, where one block
-        // serving all three was faster (measured: 48 channels on 64^3 243
-        // against 257 us, 96 on 32^3 75 against 98 us; 32 channels 40 -> 36 us)
-        const int64_t G = (int64_t)1 << a.lg;
-        const int nb = a.lg >= 5 && nsub == 3 ? 3 : 1;
-        const dim3 grid((unsigned)((G / 16) * (G / 4) * (G / kCvPlanes) * a.n), sub / nb);
-        const dim3 block(64 * kCvPlanes);
-        ConvArgs b = a;
-        b.wrows = coutp;
-        if (nb == 3)
-            hipLaunchKernelGGL(k_conv_brick<3>, grid, block, 0, s, b);
-        else
-            hipLaunchKernelGGL(k_conv_brick<1>, grid, block, 0, s, b);
-        return hipGetLastError();
-    }
     const int64_t waves4 = (int64_t)ceil_div(M, 64) * (sub / nsub);
     if (waves4 >= 2048) return launch_conv_mt<4, 1>(a, coutp, s);
     const int64_t waves1 = (int64_t)ceil_div(M, 16) * (sub / nsub);
