@@ -103,53 +103,52 @@ __device__ __forceinline__ bf16x4 mask_quad(const ConvArgs& a, int64_t vo, int c
     return a.omask && co < a.ys ? *(const bf16x4*)(a.omask + vo * a.ys + co) : bf16x4{};
 }
 
-// One block: MT * 16 voxels x (NSUB * 16) output channels, channel group
-// blockIdx.y.  Each weight fragment is loaded once and used for the MT
-// voxel tiles.  The KS waves of a block split the k range (wave w takes
-// every KS-th step of 32 from step w) and add their partial sums through
-// LDS; this keeps enough waves in flight on the coarse grids.
-template <int NSUB, int MT, int KS>
+// One block: 16 voxels x (NSUB * 16) output channels, channel group
+// blockIdx.y.  The KS waves of a block split the k range (wave w takes every
+// KS-th step of 32 from step w) and add their partial sums through LDS; this
+// keeps enough waves in flight on the coarse grids.
+//
+// Each wave is one chain of loads (one voxel and NSUB weight fragments a step,
+// from the memory-side cache: about 0.6 us), so kDepth steps' fragments are in
+// flight in as many register sets.  With two sets and four output groups a
+// wave the 4-cell layers of 128 channels took 17-19 us a launch, the
+// concatenated layer on 8 cells 26 (each step waited for its loads).
+// WIDE: the input channels are a multiple of 32 and the tensors are below 2 GB,
+// so a step lies in one tap and its addresses are a lane register plus scalars
+// (range-checked buffer loads; a tap outside the grid reads past the end, as
+// zeros).
+constexpr int conv_depth(int nsub) { return nsub == 1 ? 8 : nsub == 2 ? 6 : 3; }
+
+template <int NSUB, int KS, bool WIDE>
 __global__ void __launch_bounds__(64 * KS) k_conv(ConvArgs a) {
+    constexpr int kDepth = conv_depth(NSUB);
     const int lane = threadIdx.x & 63, r = lane & 15, q = lane >> 4;
-    const int wave = threadIdx.x >> 6;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int lg = a.lg, G = 1 << lg;
     const int64_t V = (int64_t)1 << (3 * lg);
     const int64_t M = (int64_t)a.n * V;
-    const int64_t vb = (int64_t)blockIdx.x * (16 * MT);
+    const int64_t vo = (int64_t)blockIdx.x * 16 + r;  // the lane's voxel
     const int cobase = blockIdx.y * NSUB * 16;
-    bool vok[MT];
-    int vs[MT], vz[MT], vy[MT], vx[MT];
+    const bool vok = vo < M;
+    const int64_t vc = vok ? vo : 0;
+    const int vs = (int)(vc >> (3 * lg));
+    const int rem = (int)(vc & (V - 1));
+    const int vz = rem >> (2 * lg), vy = (rem >> lg) & (G - 1), vx = rem & (G - 1);
+    floatx4 acc[NSUB];
 #pragma unroll
-    for (int m = 0; m < MT; ++m) {
-        const int64_t v = vb + m * 16 + r;
-        vok[m] = v < M;
-        const int64_t vc = vok[m] ? v : 0;
-        vs[m] = (int)(vc >> (3 * lg));
-        const int rem = (int)(vc & (V - 1));
-        vz[m] = rem >> (2 * lg);
-        vy[m] = (rem >> lg) & (G - 1);
-        vx[m] = rem & (G - 1);
-    }
-    floatx4 acc[MT][NSUB];
-#pragma unroll
-    for (int m = 0; m < MT; ++m)
-#pragma unroll
-        for (int j = 0; j < NSUB; ++j) acc[m][j] = floatx4{0.f, 0.f, 0.f, 0.f};
+    for (int j = 0; j < NSUB; ++j) acc[j] = floatx4{0.f, 0.f, 0.f, 0.f};
     // Wave w takes the k steps w, w + KS, ...: nst of them; at step s the
     // lane's 8 k values start at kw + 32 KS s.  The fragments of a step are
-    // A (MT voxel tiles, 8 channels of one tap per lane) and B (NSUB weight
-    // tiles).  With one voxel tile two register sets take turns: the loads of
-    // step s + 1 go into one while the matrix cores work on step s in the
-    // other.  The loop body has no branches (a lane outside the grid loads
-    // voxel 0 and takes zeros; a step past the last reloads the last one's
-    // addresses with a zero A fragment, so its products add 0), so the
-    // compiler keeps the loads ahead of the products and the waits cover
-    // only the step in use.
+    // the voxels (8 channels of one tap per lane) and NSUB weight tiles.  The
+    // loop body has no branches (a lane outside the grid loads voxel 0 and
+    // takes zeros; a step past the last reloads the last one's addresses with
+    // zero voxels, so its products add 0), so the compiler keeps the loads
+    // ahead of the products and the waits cover only the step in use.
     const int kw = q * 8 + 32 * wave;
-    const int nst = kw < a.kpad ? (a.kpad - 1 - kw) / (32 * KS) + 1 : 0;
+    const int nst = 32 * wave < a.kpad ? (a.kpad / 32 - 1 - wave) / KS + 1 : 0;  // (kpad: whole steps)
     const float icin = 1.f / (float)a.cin;
     const int h = lg - 1;
-    auto load_step = [&](int st, bf16x8* av, bf16x8* bv) __attribute__((always_inline)) {
+    auto load_any = [&](int st, bf16x8& av, bf16x8* bv) __attribute__((always_inline)) {
         const bool live = st < nst;
         const int k = kw + (live ? st : nst - 1) * (32 * KS);
         // tap = k / cin (exact: k < 2^13, so (k + 0.5) / cin is far from an integer)
@@ -159,79 +158,113 @@ __global__ void __launch_bounds__(64 * KS) k_conv(ConvArgs a) {
                   dx = t27 ? tap % 3 - 1 : 0;
         const bool lo = c < a.c1s;
         const __bf16* base = lo ? a.x1 : a.x2;
+        const int zz = vz + dz, yy = vy + dy, xx = vx + dx;
+        const bool ok = live && vok && k < a.K && (unsigned)zz < (unsigned)G &&
+                        (unsigned)yy < (unsigned)G && (unsigned)xx < (unsigned)G;
+        const int zc = ok ? zz : 0, yc = ok ? yy : 0, xc = ok ? xx : 0;
+        const int64_t off =
+            lo ? (((int64_t)vs << (3 * lg)) + (zc << (2 * lg)) + (yc << lg) + xc) * a.c1s + c
+               : (((int64_t)vs << (3 * h)) + ((zc >> 1) << (2 * h)) + ((yc >> 1) << h) + (xc >> 1)) *
+                         a.c2 + (c - a.c1s);
+        const bf16x8 v = *(const bf16x8*)(base + off);
 #pragma unroll
-        for (int m = 0; m < MT; ++m) {
-            const int zz = vz[m] + dz, yy = vy[m] + dy, xx = vx[m] + dx;
-            const bool ok = live && vok[m] && k < a.K && (unsigned)zz < (unsigned)G &&
-                            (unsigned)yy < (unsigned)G && (unsigned)xx < (unsigned)G;
-            const int zc = ok ? zz : 0, yc = ok ? yy : 0, xc = ok ? xx : 0;
-            const int64_t off =
-                lo ? (((int64_t)vs[m] << (3 * lg)) + ((int64_t)zc << (2 * lg)) +
-                      ((int64_t)yc << lg) + xc) * a.c1s + c
-                   : (((int64_t)vs[m] << (3 * h)) + ((int64_t)(zc >> 1) << (2 * h)) +
-                      ((int64_t)(yc >> 1) << h) + (xc >> 1)) * a.c2 + (c - a.c1s);
-            const bf16x8 v = *(const bf16x8*)(base + off);
-#pragma unroll
-            for (int i = 0; i < 8; ++i) av[m][i] = ok ? v[i] : (__bf16)0.f;
-        }
+        for (int i = 0; i < 8; ++i) av[i] = ok ? v[i] : (__bf16)0.f;
 #pragma unroll
         for (int j = 0; j < NSUB; ++j)
             bv[j] = *(const bf16x8*)(a.w + (int64_t)(cobase + j * 16 + r) * a.kpad + k);
     };
-    auto products = [&](const bf16x8* av, const bf16x8* bv) __attribute__((always_inline)) {
-#pragma unroll
-        for (int j = 0; j < NSUB; ++j)
-#pragma unroll
-            for (int m = 0; m < MT; ++m)
-                acc[m][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(bv[j], av[m], acc[m][j], 0, 0, 0);
-    };
-    if constexpr (MT == 1) {
-        if (nst > 0) {
-            bf16x8 a0[MT], b0[NSUB], a1[MT], b1[NSUB];
-            load_step(0, a0, b0);
-            for (int st = 0; st < nst; st += 2) {
-                load_step(st + 1, a1, b1);
-                products(a0, b0);
-                load_step(st + 2, a0, b0);
-                products(a1, b1);
+    // bit t: tap t of this voxel lies in the grid
+    uint32_t inside = 0;
+    const __bf16 *x1 = a.x1, *x2 = a.c2 ? a.x2 : a.x1;
+    const __amdgpu_buffer_rsrc_t r1 = __builtin_amdgcn_make_buffer_rsrc(
+        const_cast<__bf16*>(x1), (short)0, (int)(uint32_t)(M * a.c1s * 2), 0x00020000);
+    const __amdgpu_buffer_rsrc_t r2 = __builtin_amdgcn_make_buffer_rsrc(
+        const_cast<__bf16*>(x2), (short)0, (int)(uint32_t)((M >> 3) * a.c2 * 2), 0x00020000);
+    const __amdgpu_buffer_rsrc_t rw = __builtin_amdgcn_make_buffer_rsrc(
+        const_cast<__bf16*>(a.w), (short)0, (int)(uint32_t)((cobase + NSUB * 16) * a.kpad * 2),
+        0x00020000);
+    const uint32_t wbase = (uint32_t)((cobase + r) * a.kpad + q * 8) * 2u;
+    const uint32_t vbase = (uint32_t)(vc * a.c1s + q * 8) * 2u;
+    if constexpr (WIDE) {
+        if (a.taps == 27) {
+            for (int t = 0; t < 27; ++t) {
+                const int zz = vz + t / 9 - 1, yy = vy + (t / 3) % 3 - 1, xx = vx + t % 3 - 1;
+                const bool ok = vok && (unsigned)zz < (unsigned)G && (unsigned)yy < (unsigned)G &&
+                                (unsigned)xx < (unsigned)G;
+                inside |= (uint32_t)ok << t;
             }
+        } else {
+            inside = vok;
         }
-    } else {
-        // four voxel tiles: a second register set would cost more occupancy
-        // than its prefetch gains (measured), so each step loads and uses one
-        for (int st = 0; st < nst; ++st) {
-            bf16x8 a0[MT], b0[NSUB];
-            load_step(st, a0, b0);
-            products(a0, b0);
+    }
+    const int nall = a.kpad / 32;  // (WIDE: K = kpad)
+    auto load_wide = [&](int st, bf16x8& av, bf16x8* bv) __attribute__((always_inline)) {
+        const bool live = st < nst;
+        const int k = 32 * (live ? wave + KS * st : nall - 1);
+        const int tap = (int)(((float)k + 0.5f) * icin), c = k - tap * a.cin;
+        const bool t27 = a.taps == 27;
+        const int dz = t27 ? tap / 9 - 1 : 0, dy = t27 ? (tap / 3) % 3 - 1 : 0,
+                  dx = t27 ? tap % 3 - 1 : 0;
+        const bool ok = live && (inside >> tap & 1u);
+        typedef unsigned uintx4 __attribute__((ext_vector_type(4)));
+        uintx4 v;
+        if (c < a.c1s) {
+            const uint32_t off = vbase + (uint32_t)(((dz << (2 * lg)) + (dy << lg) + dx) * a.c1s + c) * 2u;
+            const uint32_t o = ok ? off : 0x80000000u;
+            v = __builtin_amdgcn_raw_buffer_load_b128(r1, o, 0, 0);
+        } else {
+            const uint32_t par = ((uint32_t)vs << (3 * h)) + ((uint32_t)(vz + dz) >> 1 << (2 * h)) +
+                                 ((uint32_t)(vy + dy) >> 1 << h) + ((uint32_t)(vx + dx) >> 1);
+            const uint32_t off = (par * (uint32_t)a.c2 + (uint32_t)(c - a.c1s + q * 8)) * 2u;
+            const uint32_t o = ok ? off : 0x80000000u;
+            v = __builtin_amdgcn_raw_buffer_load_b128(r2, o, 0, 0);
+        }
+        av = __builtin_bit_cast(bf16x8, v);
+#pragma unroll
+        for (int j = 0; j < NSUB; ++j) {
+            const uint32_t o = wbase + (uint32_t)(j * 16 * a.kpad + k) * 2u;
+            bv[j] = __builtin_bit_cast(bf16x8, __builtin_amdgcn_raw_buffer_load_b128(rw, o, 0, 0));
+        }
+    };
+    auto load_step = [&](int st, bf16x8& av, bf16x8* bv) __attribute__((always_inline)) {
+        if constexpr (WIDE)
+            load_wide(st, av, bv);
+        else
+            load_any(st, av, bv);
+    };
+    if (nst > 0) {
+        bf16x8 av[kDepth], bv[kDepth][NSUB];
+#pragma unroll
+        for (int d = 0; d < kDepth; ++d) load_step(d, av[d], bv[d]);
+        for (int st = 0; st < nst; st += kDepth) {
+#pragma unroll
+            for (int d = 0; d < kDepth; ++d) {
+#pragma unroll
+                for (int j = 0; j < NSUB; ++j)
+                    acc[j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(bv[d][j], av[d], acc[j], 0, 0, 0);
+                load_step(st + d + kDepth, av[d], bv[d]);
+            }
         }
     }
     if constexpr (KS > 1) {
-        __shared__ floatx4 part[KS - 1][MT * NSUB][64];
+        __shared__ floatx4 part[KS - 1][NSUB][64];
         if (wave > 0) {
 #pragma unroll
-            for (int m = 0; m < MT; ++m)
-#pragma unroll
-                for (int j = 0; j < NSUB; ++j) part[wave - 1][m * NSUB + j][lane] = acc[m][j];
+            for (int j = 0; j < NSUB; ++j) part[wave - 1][j][lane] = acc[j];
         }
         __syncthreads();
         if (wave > 0) return;
 #pragma unroll
         for (int w = 0; w < KS - 1; ++w)
 #pragma unroll
-            for (int m = 0; m < MT; ++m)
-#pragma unroll
-                for (int j = 0; j < NSUB; ++j) acc[m][j] += part[w][m * NSUB + j][lane];
+            for (int j = 0; j < NSUB; ++j) acc[j] += part[w][j][lane];
     }
     // D rows 4q .. 4q+3 are output channels, column r the voxel
+    if (!vok) return;
 #pragma unroll
-    for (int m = 0; m < MT; ++m) {
-        const int64_t vo = vb + m * 16 + r;
-        if (vo >= M) continue;
-#pragma unroll
-        for (int j = 0; j < NSUB; ++j) {
-            const int co = cobase + j * 16 + q * 4;
-            store_quad(a, vo, co, acc[m][j], bias_quad(a, co), mask_quad(a, vo, co));
-        }
+    for (int j = 0; j < NSUB; ++j) {
+        const int co = cobase + j * 16 + q * 4;
+        store_quad(a, vo, co, acc[j], bias_quad(a, co), mask_quad(a, vo, co));
     }
 }
 
@@ -1895,18 +1928,30 @@ int64_t conv_small_floats(const ConvArgs& a, int coutp) {
     return (int64_t)(a.cin / 16) * a.n * 512 * coutp;
 }
 
-template <int MT, int KS>
-hipError_t launch_conv_mt(const ConvArgs& a, int coutp, hipStream_t s) {
-    const int64_t M = (int64_t)a.n << (3 * a.lg);
+// Output groups a wave: one while the waves are few (each is then a short
+// chain with eight steps in flight), more where the blocks already fill the
+// chip and a voxel fragment should serve several groups.
+template <int KS>
+hipError_t launch_conv_ks(const ConvArgs& a, int coutp, hipStream_t s) {
+    const int64_t tiles = ceil_div((int64_t)a.n << (3 * a.lg), 16);
     const int sub = coutp / 16;
-    const int nsub = sub % 4 == 0 ? 4 : sub % 3 == 0 ? 3 : sub % 2 == 0 ? 2 : 1;
-    const dim3 grid(ceil_div(M, 16 * MT), sub / nsub), block(64 * KS);
+    const int64_t waves = tiles * sub * KS;
+    const int nsub = waves > 2048 && sub % 4 == 0 ? 4 : waves > 1024 && sub % 2 == 0 ? 2 : 1;
+    const int64_t M = (int64_t)a.n << (3 * a.lg);
+    const bool wide = a.cin % 32 == 0 && a.c1s % 32 == 0 && a.K == a.kpad &&
+                      M * std::max(a.c1s, a.c2) * 2 < ((int64_t)1 << 31);
+    const dim3 grid((unsigned)tiles, sub / nsub), block(64 * KS);
+#define LBMNN_CONV(N)                                                                        \
+    if (wide)                                                                                \
+        hipLaunchKernelGGL((k_conv<N, KS, true>), grid, block, 0, s, a);                     \
+    else                                                                                     \
+        hipLaunchKernelGGL((k_conv<N, KS, false>), grid, block, 0, s, a)
     switch (nsub) {
-        case 4: hipLaunchKernelGGL((k_conv<4, MT, KS>), grid, block, 0, s, a); break;
-        case 3: hipLaunchKernelGGL((k_conv<3, MT, KS>), grid, block, 0, s, a); break;
-        case 2: hipLaunchKernelGGL((k_conv<2, MT, KS>), grid, block, 0, s, a); break;
-        default: hipLaunchKernelGGL((k_conv<1, MT, KS>), grid, block, 0, s, a); break;
+        case 4: LBMNN_CONV(4); break;
+        case 2: LBMNN_CONV(2); break;
+        default: LBMNN_CONV(1); break;
     }
+#undef LBMNN_CONV
     return hipGetLastError();
 }
 
@@ -1971,11 +2016,10 @@ hipError_t launch_conv_brick(const ConvArgs& args, int coutp, hipStream_t s) {
     return launch_conv_wy<1, 1, false>(a, sub, 2 * tall, s);
 }
 
-// Four voxel tiles per wave when that still leaves at least 2048 blocks (so
-// each weight fragment serves 64 voxels).  Otherwise one tile, and the k
-// range is split over 2 or 4 waves per block when there are fewer than
-// 4096 or 1024 blocks and at least two steps of 32 per wave (8 waves were
-// measured no faster on the 8^3 layers).
+// The tiled kernel's k range is split over 2 or 4 waves per block when there
+// are fewer than 4096 or 1024 (voxel tile, up to four output groups) pairs and
+// at least two steps of 32 per wave (8 waves were measured no faster on the
+// 8^3 layers).
 hipError_t launch_conv(const ConvArgs& a, int coutp, float* scratch, int64_t scratch_floats,
                        hipStream_t s) {
     const int64_t M = (int64_t)a.n << (3 * a.lg);
@@ -1996,13 +2040,11 @@ hipError_t launch_conv(const ConvArgs& a, int coutp, float* scratch, int64_t scr
     }
     if (conv_brick_covers(a, coutp)) return launch_conv_brick(a, coutp, s);
     const int nsub = sub % 4 == 0 ? 4 : sub % 3 == 0 ? 3 : sub % 2 == 0 ? 2 : 1;
-    const int64_t waves4 = (int64_t)ceil_div(M, 64) * (sub / nsub);
-    if (waves4 >= 2048) return launch_conv_mt<4, 1>(a, coutp, s);
     const int64_t waves1 = (int64_t)ceil_div(M, 16) * (sub / nsub);
     const int ksteps = a.kpad / 32;
-    if (waves1 < 1024 && ksteps >= 8) return launch_conv_mt<1, 4>(a, coutp, s);
-    if (waves1 < 4096 && ksteps >= 4) return launch_conv_mt<1, 2>(a, coutp, s);
-    return launch_conv_mt<1, 1>(a, coutp, s);
+    if (waves1 < 1024 && ksteps >= 8) return launch_conv_ks<4>(a, coutp, s);
+    if (waves1 < 4096 && ksteps >= 4) return launch_conv_ks<2>(a, coutp, s);
+    return launch_conv_ks<1>(a, coutp, s);
 }
 
 }  // namespace

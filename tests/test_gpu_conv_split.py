@@ -62,3 +62,28 @@ def test_gradient_of_a_batch_is_the_mean_of_its_samples(net, targets, n):
     log("relative difference", err)
     assert err < 1e-5
     assert abs(loss - total) < 1e-12 * abs(total) + 1e-15
+
+
+@pytest.mark.parametrize("n", [9, 40, 64])
+def test_tiled_kernel_groups_on_small_grids(n):
+    """Grids of 8 cells and less (the tiled kernel: one, two or four output
+    groups a wave, the k range over 4, 2 or 1 waves, by the number of tiles):
+    each sample of a batch against its own single call, whose path the oracle
+    checks.  Where the k range is split differently, FP32 sums differ in their
+    last bits and a BF16 result in its last place now and then: 2^-8 of a value,
+    through 15 layers below 2e-2 of the output's norm."""
+    from paper_1710_04751_amd import network
+    log("case: tiled kernel groups", n)
+    lra = [3.0 + 3.0 * i / n for i in range(n)]
+    a = network.WarmStartNet(8, n)
+    b = network.WarmStartNet(8, 1)
+    theta = torch.from_numpy(network.init_params(11))
+    a.set_params(theta)
+    b.set_params(theta)
+    out = a.forward(lra)
+    for i in (0, n // 2, n - 1):
+        one = b.forward([lra[i]])[0]
+        err = float((out[i] - one).norm() / one.norm())
+        assert err < 2e-2, (i, err)
+    a.close()
+    b.close()
