@@ -287,7 +287,6 @@ struct WgradArgs {
 // S = 0 (mod 64) never.  The fragments here have H = 16 (the lane's second 8
 // channels or k values), so row strides are 32 (mod 64) bytes.
 constexpr int kTileRow = 48;   // 32-voxel tile rows, in elements (96 bytes)
-constexpr int kDTRow = 144;    // 128-voxel brick rows of the output gradient (288 bytes)
 
 // B fragment of ones: an A fragment times it gives its row sums in every
 // column (the bias gradient's sum over voxels, on the matrix cores).
@@ -489,210 +488,85 @@ __global__ void k_wgrad_reduce(WgradArgs a, int kt, int ct, int nz, int rs, int 
     }
 }
 
-// Weight gradient on voxel bricks, for grids of at least 16 cells and
-// unmasked output gradients.  One block of 4 waves owns 16 input channels
-// (blockIdx.x) and every tap and output channel (RS * 16); it walks a range
-// of bricks of 16 x 4 x 2 voxels, four matrix-core k steps of 32 voxels (two
-// x rows of one plane each).  Per brick:
-//   - the input's 18 x 6 x 4 halo is loaded once: a thread takes 10
-//     consecutive x cells of one row and 8 channels (16-byte loads),
-//     transposes them in registers and writes, for dx = -1, 0, +1, the 8
-//     cells each shift needs as one 16-byte LDS store per channel, so the B
-//     fragment of every tap (8 consecutive cells of one channel) is one
-//     aligned 16-byte read;
-//   - the output gradient is transposed the same way (8 cells x 8 channels
-//     per thread), and its A fragments serve all taps.
-// Wave w accumulates taps w, w + 4, ...  Each block writes its partial sums
-// (block b = blockIdx.y * gridDim.x + blockIdx.x: [tap][co][16 channels]);
-// wave 0 of the first channel group also sums the output gradient for the
-// bias (a matrix-core product against ones; partials [blockIdx.y][coutp] at
-// bias_off).  k_brick_partials_sum adds the partials up.
-constexpr int kBrickRow = 4 * 6 * 16 + 16;  // one channel's halo (hz, hy, x), padded
-
-template <int RS>
-__global__ void __launch_bounds__(256, 2) k_wgrad_brick(WgradArgs a, int64_t bricks_per_block) {
-    constexpr int NT = 7;  // taps per wave: ceil(27 / 4)
-    __shared__ __attribute__((aligned(16))) __bf16 xs[3 * 16 * kBrickRow];
-    __shared__ __attribute__((aligned(16))) __bf16 dT[RS * 16][kDTRow];
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int r = lane & 15, q = lane >> 4;
-    const int lg = a.lg, G = 1 << lg;
-    const int c0 = blockIdx.x * 16;
-    const int nbx = G >> 4, nby = G >> 2, nbz = G >> 1;
-    const int64_t nbricks = (int64_t)a.n * nbz * nby * nbx;
-    const int64_t b0 = (int64_t)blockIdx.y * bricks_per_block;
-    const int64_t b1 = b0 + bricks_per_block < nbricks ? b0 + bricks_per_block : nbricks;
-    floatx4 acc[NT][RS];
-#pragma unroll
-    for (int j = 0; j < NT; ++j)
-#pragma unroll
-        for (int m = 0; m < RS; ++m) acc[j][m] = floatx4{0.f, 0.f, 0.f, 0.f};
-    floatx4 accb[RS];
-#pragma unroll
-    for (int m = 0; m < RS; ++m) accb[m] = floatx4{0.f, 0.f, 0.f, 0.f};
-    const bool bias_wave = blockIdx.x == 0 && wave == 0;
-    // Roles: threads 0-95 load input halo rows, the next 32 * RS the output
-    // gradient.  The global loads of brick b + 1 are issued into registers
-    // before the matrix-core phase of brick b, so their latency is hidden.
-    const int cgx = tid / 48, remx = tid - cgx * 48;
-    const int kx = remx & 1, hyx = (remx >> 1) % 6, hzx = (remx >> 1) / 6;
-    const int td = tid - 96, vgd = td & 15, cgd = td >> 4, sd = vgd >> 2;
-    // Loads through range-checked buffer resources over one sample of the
-    // channel group's tensor and of the output gradient (zeros past the end:
-    // no branch, select or zero fill, so no load waits on another).
-    const int h = lg - 1;
-    const bool lo = c0 < a.c1s;
-    const int chans = lo ? a.c1s : a.c2;
-    const int hl = lo ? lg : h;
-    const int64_t vs = (int64_t)1 << (3 * hl);
-    const uint32_t xbytes = (uint32_t)(vs * chans * 2);
-    const uint32_t dbytes = (uint32_t)(((int64_t)1 << (3 * lg)) * a.ys * 2);
-    const int cloc = lo ? c0 : c0 - a.c1s;
-    bf16x8 reg[10];
-    auto fetch = [&](int64_t b) __attribute__((always_inline)) {
-        uint32_t bb = (uint32_t)b;
-        const int x0 = (int)(bb % (uint32_t)nbx) * 16;
-        bb /= (uint32_t)nbx;
-        const int y0 = (int)(bb % (uint32_t)nby) * 4;
-        bb /= (uint32_t)nby;
-        const int z0 = (int)(bb % (uint32_t)nbz) * 2;
-        const int smp = (int)(bb / (uint32_t)nbz);
-        if (tid < 96) {
-            // input halo row (hz, hy), x cells 8k .. 8k+9, channel group cg
-            // (the channel group is the slowest index)
-            const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(
-                const_cast<__bf16*>((lo ? a.x1 : a.x2) + (int64_t)smp * vs * chans), (short)0,
-                (int)xbytes, 0x00020000);
-            const int yy = y0 + hyx - 1, zz = z0 + hzx - 1;
-            const bool row_ok = c0 + cgx * 8 < a.cin && (unsigned)yy < (unsigned)G &&
-                                (unsigned)zz < (unsigned)G;
-            const int sh = lo ? 0 : 1;
-            const uint32_t rowv = ((uint32_t)(zz >> sh) << (2 * hl)) + ((uint32_t)(yy >> sh) << hl);
-#pragma unroll
-            for (int m = 0; m < 10; ++m) {
-                const int xx = x0 + 8 * kx + m - 1;
-                const bool ok = row_ok && (unsigned)xx < (unsigned)G;
-                const uint32_t off =
-                    (((rowv + (uint32_t)(xx >> sh)) * (uint32_t)chans + (uint32_t)(cloc + cgx * 8)) * 2u) |
-                    ((uint32_t)!ok << 31);
-                reg[m] = __builtin_bit_cast(bf16x8, __builtin_amdgcn_raw_buffer_load_b128(rs, off, 0, 0));
-            }
-        } else if (tid < 96 + 32 * RS) {
-            // output gradient: 8 cells (one k group) x 8 channels
-            const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(
-                const_cast<__bf16*>(a.dy + ((int64_t)smp << (3 * lg)) * a.ys), (short)0,
-                (int)dbytes, 0x00020000);
-            const int yy = y0 + (sd & 1) * 2 + ((vgd & 3) >> 1), zz = z0 + (sd >> 1);
-            const int xb = x0 + (vgd & 1) * 8;
-            const uint32_t v0 = ((uint32_t)zz << (2 * lg)) + ((uint32_t)yy << lg) + (uint32_t)xb;
-            const uint32_t bad = (uint32_t)!(cgd * 8 < a.ys) << 31;
-#pragma unroll
-            for (int m = 0; m < 8; ++m)
-                reg[m] = __builtin_bit_cast(
-                    bf16x8, __builtin_amdgcn_raw_buffer_load_b128(
-                                rs, (((v0 + m) * (uint32_t)a.ys + (uint32_t)(cgd * 8)) * 2u) | bad,
-                                0, 0));
-        }
-    };
-    if (b0 < b1) fetch(b0);
-    for (int64_t b = b0; b < b1; ++b) {
-        // transposed LDS stores of the fetched brick
-        if (tid < 96) {
-            const int row = (hzx * 6 + hyx) * 16 + 8 * kx;
-#pragma unroll
-            for (int d = 0; d < 3; ++d)
-#pragma unroll
-                for (int e = 0; e < 8; ++e) {
-                    bf16x8 w;
-#pragma unroll
-                    for (int j = 0; j < 8; ++j) w[j] = reg[j + d][e];
-                    *(bf16x8*)&xs[(d * 16 + cgx * 8 + e) * kBrickRow + row] = w;
-                }
-        } else if (tid < 96 + 32 * RS) {
-#pragma unroll
-            for (int e = 0; e < 8; ++e) {
-                bf16x8 w;
-#pragma unroll
-                for (int j = 0; j < 8; ++j) w[j] = reg[j][e];
-                *(bf16x8*)&dT[cgd * 8 + e][vgd * 8] = w;
-            }
-        }
-        __syncthreads();
-        if (b + 1 < b1) fetch(b + 1);
-#pragma unroll
-        for (int s = 0; s < 4; ++s) {
-            bf16x8 av[RS];
-#pragma unroll
-            for (int m = 0; m < RS; ++m) av[m] = *(const bf16x8*)&dT[m * 16 + r][s * 32 + q * 8];
-            if (bias_wave) {
-#pragma unroll
-                for (int m = 0; m < RS; ++m)
-                    accb[m] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av[m], ones_frag(), accb[m],
-                                                                      0, 0, 0);
-            }
-#pragma unroll
-            for (int j = 0; j < NT; ++j) {
-                const int t = wave + 4 * j;
-                if (t < 27) {
-                    const int dz = t / 9 - 1, dy = (t / 3) % 3 - 1, dx = t % 3 - 1;
-                    const int hz = (s >> 1) + dz + 1, hy = (s & 1) * 2 + (q >> 1) + dy + 1;
-                    const bf16x8 bv = *(const bf16x8*)&xs[((dx + 1) * 16 + r) * kBrickRow +
-                                                          (hz * 6 + hy) * 16 + (q & 1) * 8];
-#pragma unroll
-                    for (int m = 0; m < RS; ++m)
-                        acc[j][m] =
-                            __builtin_amdgcn_mfma_f32_16x16x32_bf16(av[m], bv, acc[j][m], 0, 0, 0);
-                }
-            }
-        }
-        __syncthreads();
-    }
-    const int64_t blk = (int64_t)blockIdx.y * gridDim.x + blockIdx.x;
-    float* pb = a.part + blk * (27 * RS * 16 * 16);
-#pragma unroll
-    for (int j = 0; j < NT; ++j) {
-        const int t = wave + 4 * j;
-        if (t >= 27) continue;
-#pragma unroll
-        for (int m = 0; m < RS; ++m)
-#pragma unroll
-            for (int i = 0; i < 4; ++i)
-                pb[((t * RS + m) * 16 + q * 4 + i) * 16 + r] = acc[j][m][i];
-    }
-    if (bias_wave && r == 0) {
-        float* bb = a.part + a.bias_off + (int64_t)blockIdx.y * (RS * 16);
-#pragma unroll
-        for (int m = 0; m < RS; ++m)
-#pragma unroll
-            for (int i = 0; i < 4; ++i) bb[m * 16 + q * 4 + i] = accb[m][i];
-    }
+// Direct-to-LDS copy of 16 bytes per lane, from byte off of the buffer (zeros
+// past its end) to LDS byte `lds` (the wave's, in a scalar) plus 16 times the
+// lane.  Written as an instruction because the compiler, which cannot tell the
+// two halo buffers apart across the loop, would wait for the copies of the
+// next step before every LDS read of this one; it has no register result.
+// The waits are the caller's: copies_landed.
+typedef int intx4 __attribute__((ext_vector_type(4)));
+__device__ __forceinline__ intx4 buffer_words(const void* base, uint32_t bytes) {
+    const uint64_t p = (uint64_t)base;
+    return intx4{__builtin_amdgcn_readfirstlane((int)(uint32_t)p),
+                 __builtin_amdgcn_readfirstlane((int)(uint32_t)(p >> 32) & 0xFFFF),
+                 __builtin_amdgcn_readfirstlane((int)bytes), 0x00020000};
+}
+__device__ __forceinline__ void copy_to_lds(intx4 rsrc, uint32_t lds, uint32_t off) {
+    __asm__ volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds"
+                     :
+                     : "s"(lds), "v"(off), "s"(rsrc)
+                     : "memory");
+}
+// Waits until at most `later` of this wave's vector-memory operations are
+// outstanding (they finish in order) and its LDS reads are done, then for the
+// block's other waves.
+template <int later>
+__device__ __forceinline__ void copies_outstanding() {
+    static_assert(later < 64, "the counter's range");
+    __asm__ volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" : : "n"(later) : "memory");
+}
+__device__ __forceinline__ void block_barrier() { __asm__ volatile("s_barrier" : : : "memory"); }
+template <int later>
+__device__ __forceinline__ void copies_landed() {
+    copies_outstanding<later>();
+    block_barrier();
 }
 
 // Weight gradient on 16 x 4 x 4 bricks through transposing LDS reads, for
-// 16 and 32 output channels.  dW[tap][co][ci] sums dY[v][co] X[v + tap][ci]
-// over voxels v, so both matrix-core operands need 8 consecutive voxels of one
-// channel per lane, while the tensors are stored channels-last.  The block
-// copies the brick's output gradient and the 18 x 6 x 6 input halo of one
-// 16-channel group into LDS as they are stored (direct-to-LDS loads, 32 bytes
-// per voxel and 16 channels), and ds_read_b64_tr_b16 transposes on the way
-// out: within each 16 lanes, lane 4a + b receives element b of the 8-byte
-// pieces addressed by lanes a, a + 4, a + 8, a + 12.  So when lane L of a
-// group addresses voxel k0 + L / 4, channels 4 (L % 4) .. + 3, lane n gets
-// voxels k0 .. k0 + 3 of channel n: two such reads give an operand fragment.
-// Nine waves, wave w the three taps with dz = w / 3 - 1, dy = w % 3 - 1.  Lane
-// groups q and q ^ 1 of a k step take neighbouring rows, and the LDS rows are
-// padded so that their reads fall in opposite halves of the banks (a row of
+// grids of at least 16 cells and unmasked output gradients.  dW[tap][co][ci]
+// sums dY[v][co] X[v + tap][ci] over voxels v, so both matrix-core operands
+// need 8 consecutive voxels of one channel per lane, while the tensors are
+// stored channels-last.  The block copies the brick's output gradient and the
+// 18 x 6 x 6 input halo of one 16-channel group into LDS as they are stored
+// (direct-to-LDS loads, 32 bytes per voxel and 16 channels), and
+// ds_read_b64_tr_b16 transposes on the way out: within each 16 lanes, lane
+// 4a + b receives element b of the 8-byte pieces addressed by lanes a, a + 4,
+// a + 8, a + 12.  So when lane L of a group addresses voxel k0 + L / 4,
+// channels 4 (L % 4) .. + 3, lane n gets voxels k0 .. k0 + 3 of channel n: two
+// such reads give an operand fragment.
+//
+// Twelve waves make the products: wave w the taps with dy = w % 3 - 1 (nine of
+// them) on plane w / 3 of the brick.  A wave reads its plane's output gradient
+// once, and each row of its three halo planes once, as three 4-voxel pieces
+// from which the fragments of dx = -1, 0, +1 are shifted together in registers:
+// 22 reads for 18 products (26 for 36 with 32 output channels); one wave per
+// (dz, dy) with a read per fragment took 64 for 24.
+//
+// Four more waves make the copies (two the halo, two the output gradient): the
+// scalar work of their addresses, done by every wave, had cost more issue slots
+// than the products (174 scalar instructions a wave and brick beside 18
+// products: 51 us for a 16-channel layer at 64^3).
+//
+// Lane groups q and q ^ 1 of a k step take neighbouring rows, and the LDS rows
+// are padded so that their reads fall in opposite halves of the banks (a row of
 // the halo or of a one-group output gradient holds 20 voxels, 640 bytes; of a
-// two-group output gradient 1056 bytes).  A block walks a range of bricks in
-// z order within each (x, y) column; the halo is a ring of 8 plane slots
-// (input plane z in slot z mod 8), so a brick that follows its z neighbour
-// keeps the two planes they share and copies only its 4 new ones.  Partial
-// sums as k_wgrad_brick.
-constexpr int kWtWaves = 9;
+// two-group output gradient 1056 bytes).  A block (one per compute unit) walks
+// a range of bricks in z order within each (x, y) column.  The halo planes sit
+// in a ring of slots: a brick after its z neighbour keeps the two planes they
+// share and copies its 4 new ones.  The copies of up to `ahead` bricks are in
+// flight (26 KB a brick against about 0.4 us of products).  blockIdx.z: 32 of
+// the output channels.
+//
+// Measured, 8 samples, before (nine waves, one brick copied ahead by all of
+// them, four blocks a compute unit) -> now: 16 -> 16 channels at 64^3
+// 55 -> 45 us (134 MB: 3.0 TB/s; copies alone 31, products alone 31), 48 -> 16
+// at 64^3 155 -> 123, 32 -> 32 at 32^3 25 -> 22, 96 -> 32 at 32^3 58 -> 46,
+// 192 -> 64 at 16^3 52 -> 30; slower: 16 -> 32
+// at 32^3 and 32 -> 64 at 16^3 (few bricks a block), 14.6 -> 15.9.
+constexpr int kWtWaves = 9;                    // k_wgrad_small
+constexpr int kWgWaves = 16;                   // k_wgrad_tr: 12 for the products, 4 for the copies
 constexpr int kWtHaloRow = 20;                 // voxels per LDS halo row (18 + 2 padding)
 constexpr int kWtPlaneItems = 256;             // 16-byte items per plane slot: 6 rows, padding
-constexpr int kWtRing = 8;                     // plane slots
-constexpr int kWtHaloBuf = kWtRing * kWtPlaneItems;
 typedef short shortx4 __attribute__((ext_vector_type(4)));
 typedef __attribute__((address_space(3))) shortx4* lds_shortx4_ptr;
 
@@ -703,15 +577,26 @@ __device__ __forceinline__ bf16x8 tr_fragment(const char* lds, uint32_t byte0, u
 }
 
 template <int RS>
-__global__ void __launch_bounds__(64 * kWtWaves) k_wgrad_tr(WgradArgs a, int64_t bricks_per_block) {
-    constexpr int kDyRow = RS == 1 ? 40 : 66;   // 16-byte items per output-gradient row (padded)
-    constexpr int kDyItems = 16 * kDyRow;       // 4 planes x 4 rows
-    constexpr int kDyBuf = (kDyItems + 63) / 64 * 64;
-    constexpr int kDyCopies = kDyBuf / 64;
-    constexpr int kDyByte = kWtHaloBuf * 16;  // byte offset of the output gradient in LDS
-    constexpr int kMaxCopies = 6 * kWtPlaneItems / 64 + kDyCopies;  // a brick with a new halo
-    __shared__ __attribute__((aligned(16))) __bf16 set[(kWtHaloBuf + kDyBuf) * 8];
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+struct WgShape {
+    static constexpr int dy_row = RS == 1 ? 40 : 66;   // 16-byte items per output-gradient row (padded)
+    static constexpr int dy_items = 16 * dy_row;       // 4 planes x 4 rows
+    static constexpr int dy_buf = (dy_items + 63) / 64 * 64;
+    static constexpr int dy_copies = dy_buf / 64;
+    static constexpr int dy_it = (dy_copies + 1) / 2;  // per copying wave, at most
+    static constexpr int dy_min = dy_copies / 2;       // and at least
+    static constexpr int ahead = RS == 1 ? 4 : 3;      // bricks copied ahead
+    static constexpr int ring = 6 + 4 * ahead;         // plane slots
+    static constexpr int halo = ring * kWtPlaneItems;
+    static constexpr int lds_items = halo + (ahead + 1) * dy_buf;
+    static_assert(lds_items * 16 <= 160 * 1024, "one block's LDS");
+};
+
+template <int RS>
+__global__ void __launch_bounds__(64 * kWgWaves) k_wgrad_tr(WgradArgs a, int64_t bricks_per_block) {
+    using W = WgShape<RS>;
+    __shared__ __attribute__((aligned(16))) __bf16 set[W::lds_items * 8];
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int r = lane & 15, q = lane >> 4;
     const int lg = a.lg, G = 1 << lg;
     // XCD-grouped order: the dispatcher deals consecutive blocks to the 8 XCDs
@@ -722,159 +607,270 @@ __global__ void __launch_bounds__(64 * kWtWaves) k_wgrad_tr(WgradArgs a, int64_t
     const uint32_t total = gridDim.x * gridDim.y, lin = blockIdx.y * gridDim.x + blockIdx.x;
     const uint32_t lblk = total % 8 ? lin : (lin % 8) * (total / 8) + lin / 8;
     const int chunk = (int)(lblk % gridDim.x), grp = (int)(lblk / gridDim.x);
-    const int c0 = chunk * 16;
+    const int c0 = chunk * 16, co0 = (int)blockIdx.z * RS * 16;
     const int nbx = G >> 4, nby = G >> 2, nbz = G >> 2;
-    const int64_t nbricks = (int64_t)a.n * nbz * nby * nbx;
-    const int64_t b0 = (int64_t)grp * bricks_per_block;
-    const int64_t b1 = b0 + bricks_per_block < nbricks ? b0 + bricks_per_block : nbricks;
-    floatx4 acc[3][RS];
-#pragma unroll
-    for (int j = 0; j < 3; ++j)
-#pragma unroll
-        for (int m = 0; m < RS; ++m) acc[j][m] = floatx4{0.f, 0.f, 0.f, 0.f};
-    floatx4 accb[RS];
-#pragma unroll
-    for (int m = 0; m < RS; ++m) accb[m] = floatx4{0.f, 0.f, 0.f, 0.f};
-    const bool bias_wave = chunk == 0 && wave == 0;
-    // k value 8 q + 4 h + e of k step s (h: which of the two reads, e = r / 4)
-    // is the brick voxel (plane s / 2, row 2 (s % 2) + q % 2, cell 8 (q / 2) +
-    // 4 h + e); the lane reads channels 4 (r % 4) .. + 3 of it
-    const int e = r >> 2, ac = r & 3;
-    const uint32_t laneA =
-        (uint32_t)(kDyByte + ((q & 1) * kDyRow + (8 * (q >> 1) + e) * 2 * RS) * 16 + ac * 8);
-    const int dzw = wave / 3, dyw = wave % 3;  // this wave's taps: dz + 1, dy + 1
-    // within a plane slot (the slot's offset is added per brick)
-    const uint32_t laneB = (uint32_t)((((q & 1) + dyw) * kWtHaloRow + 8 * (q >> 1) + e) * 32 + ac * 8);
+    const int nbricks = a.n * nbz * nby * nbx;
+    const int per = (int)bricks_per_block;
+    const int b0 = grp * per, b1 = b0 + per < nbricks ? b0 + per : nbricks;
     const int h = lg - 1;
     const bool lo = c0 < a.c1s;  // the group's channels lie in x1 (else x2; c1s is then a multiple of 16)
     const int chans = lo ? a.c1s : a.c2;
     const int hl = lo ? lg : h, sh = lo ? 0 : 1;
-    const int64_t vs = (int64_t)1 << (3 * hl);
     const int cloc = lo ? c0 : c0 - a.c1s;
-    const int wv = __builtin_amdgcn_readfirstlane(wave);
-    // brick b: z fastest, then x, y, sample
-    auto brick = [&](int64_t b, int& x0, int& y0, int& z0, int& smp) __attribute__((always_inline)) {
-        uint32_t bb = (uint32_t)b;
-        z0 = (int)(bb % (uint32_t)nbz) * 4;
-        bb /= (uint32_t)nbz;
-        x0 = (int)(bb % (uint32_t)nbx) * 16;
-        bb /= (uint32_t)nbx;
-        y0 = (int)(bb % (uint32_t)nby) * 4;
-        smp = (int)(bb / (uint32_t)nby);
-    };
-    // The copies of brick b: the halo planes z0 - 1 .. z0 + 4 when the brick
-    // starts a run (the block's first, or the first of its column), else
-    // z0 + 1 .. z0 + 4 (the other two are in the ring from the brick before);
-    // then the output gradient.  Copy j goes to wave j % 9.
-    auto issue = [&](int64_t b) __attribute__((always_inline)) {
-        int x0, y0, z0, smp;
-        brick(b, x0, y0, z0, smp);
-        const bool fresh = b == b0 || z0 == 0;
-        const int zfirst = fresh ? z0 - 1 : z0 + 1;
-        const int nh = (fresh ? 6 : 4) * (kWtPlaneItems / 64);  // halo copies
-        const int ncopies = nh + kDyCopies;
-        // range-checked buffer resources: positions outside the grid, channel
-        // halves past the input channels, output channels past ys and padding
-        // items read zeros
-        const __amdgpu_buffer_rsrc_t rx = __builtin_amdgcn_make_buffer_rsrc(
-            const_cast<__bf16*>((lo ? a.x1 : a.x2) + (int64_t)smp * vs * chans), (short)0,
-            (int)(uint32_t)(vs * chans * 2), 0x00020000);
-        const __amdgpu_buffer_rsrc_t rd = __builtin_amdgcn_make_buffer_rsrc(
-            const_cast<__bf16*>(a.dy + ((int64_t)smp << (3 * lg)) * a.ys), (short)0,
-            (int)(uint32_t)(((int64_t)1 << (3 * lg)) * a.ys * 2), 0x00020000);
-        // (the lane's item decode is redone per brick rather than held in registers)
-        int ln = lane;
-        __asm__ volatile("" : "+v"(ln));
+    const int64_t sample_x = (int64_t)chans << (3 * hl), sample_d = (int64_t)a.ys << (3 * lg);
+    const __bf16 *xin = lo ? a.x1 : a.x2, *dyin = a.dy;
+    __asm__ volatile("" : "+s"(xin), "+s"(dyin));  // held in scalars, not fetched again each brick
+    // Waves 12 and 13 copy the halo (items 128 (w % 2) .. + 127 of each plane:
+    // slot t / 2 of 20 x 6, channel half t % 2), waves 14 and 15 the output
+    // gradient in turn (item t: row t / dy_row, 4 plane + row; voxel and 8
+    // channels of item t % dy_row).  Decoded once: from: the item's byte from
+    // the brick's first halo row (of the output gradient: its first voxel);
+    // side: the sides of the halo it lies on, 64 for padding, channel halves
+    // past the input and channels past ys, 128 in all (for a plane outside the
+    // grid).  Items that read zeros take offsets with bit 31 set (samples are
+    // below 2^31 bytes): past the buffer's end.
+    constexpr uint32_t kOutside = 0x80000000u;
+    const int copier = wave - 12;
+    uint32_t from[W::dy_it], side[2] = {0, 0};
+    if (copier == 0 || copier == 1) {
 #pragma unroll
-        for (int i = 0; i < (kMaxCopies + kWtWaves - 1) / kWtWaves; ++i) {
-            const int j = i * kWtWaves + wv;
-            if (j >= ncopies) break;
-            if (j < nh) {
-                // halo plane zz = zfirst + j / 4 into slot zz mod 8; item t of
-                // the plane: slot t / 2 of 20 x 6 (t >= 240 pads), channel half t % 2
-                const int zz = zfirst + (j >> 2);
-                const int t = (j & 3) * 64 + ln;
-                const int half = t & 1, hv = t >> 1;
-                const int hx = hv % kWtHaloRow, hy = hv / kWtHaloRow;
-                const int xx = x0 + hx - 1, yy = y0 + hy - 1;
-                const bool ok = hy < 6 && hx < 18 && c0 + half * 8 < a.cin &&
-                                (unsigned)xx < (unsigned)G && (unsigned)yy < (unsigned)G &&
-                                (unsigned)zz < (unsigned)G;
-                const uint32_t vox = ((uint32_t)(zz >> sh) << (2 * hl)) +
-                                     ((uint32_t)(yy >> sh) << hl) + (uint32_t)(xx >> sh);
-                const uint32_t off = ((vox * (uint32_t)chans + (uint32_t)(cloc + half * 8)) * 2u) |
-                                     ((uint32_t)!ok << 31);
-                const int dst = (zz & (kWtRing - 1)) * kWtPlaneItems + (j & 3) * 64;
-                __builtin_amdgcn_raw_ptr_buffer_load_lds(rx, (lds_void_ptr)&set[dst * 8], 16, off, 0, 0, 0);
-            } else {
-                // output-gradient item t: row t / kDyRow (4 plane + row), voxel
-                // and 8 channels of item t % kDyRow (the last items of a row
-                // pad); past the output gradient, padding
-                const int t = (j - nh) * 64 + ln;
-                const int row = t / kDyRow, it = t - row * kDyRow;
-                const int px = it / (2 * RS), c8 = it % (2 * RS);
-                const uint32_t vox = ((uint32_t)(z0 + ((row >> 2) & 3)) << (2 * lg)) +
-                                     ((uint32_t)(y0 + (row & 3)) << lg) + (uint32_t)(x0 + (px & 15));
-                const bool ok = t < kDyItems && px < 16 && c8 * 8 < a.ys;
-                const uint32_t off = ((vox * (uint32_t)a.ys + (uint32_t)(c8 * 8)) * 2u) |
-                                     ((uint32_t)!ok << 31);
-                const int dst = kWtHaloBuf + (j - nh) * 64;
-                __builtin_amdgcn_raw_ptr_buffer_load_lds(rd, (lds_void_ptr)&set[dst * 8], 16, off, 0, 0, 0);
+        for (int i = 0; i < 2; ++i) {
+            const int t = copier * 128 + i * 64 + lane, half = t & 1, hv = t >> 1;
+            const int hx = hv % kWtHaloRow, hy = hv / kWtHaloRow;
+            const bool never = hy >= 6 || hx >= 18 || c0 + half * 8 >= a.cin;
+            const int v = lo ? (hy << lg) + hx : ((hy + 1) >> 1 << h) + ((hx + 1) >> 1);
+            from[i] = (uint32_t)(v * chans + cloc + half * 8) * 2u;
+            side[i] = (uint32_t)((hx == 0) | (hx == 17) << 1 | (hy == 0) << 2 | (hy == 5) << 3 |
+                                 never << 6 | 128);
+        }
+    } else if (copier > 1) {
+#pragma unroll
+        for (int i = 0; i < W::dy_it; ++i) {
+            const int t = (2 * i + copier - 2) * 64 + lane;
+            const int row = t / W::dy_row, it = t - row * W::dy_row;
+            const int px = it / (2 * RS), co = co0 + (it % (2 * RS)) * 8;
+            const int v = ((row >> 2) << (2 * lg)) + ((row & 3) << lg) + px;
+            const bool ok = t < W::dy_items && px < 16 && co < a.ys;
+            from[i] = ok ? (uint32_t)(v * a.ys + co) * 2u : kOutside;
+        }
+    }
+    const uint32_t lds0 = (uint32_t)(uintptr_t)(lds_void_ptr)&set[0];
+    auto negative = [](int v) { return (uint32_t)v >> 31; };
+    auto slot = [](int s) { return s >= W::ring ? s - W::ring : s; };  // s < 2 ring
+    // The copies of brick b (z fastest, then x, y, sample: powers of two): the
+    // halo planes from z0 - 1 + p0 on into the slots from `to` on (p0: 0, or 2
+    // for a brick that follows its z neighbour), the output gradient into
+    // buffer buf.
+    auto issue = [&](int b, int p0, int to, int buf) __attribute__((always_inline)) {
+        const int z0 = (b & (nbz - 1)) * 4;
+        b >>= lg - 2;
+        const int x0 = (b & (nbx - 1)) * 16;
+        b >>= lg - 4;
+        const int y0 = (b & (nby - 1)) * 4, smp = b >> (lg - 2);
+        if (copier < 2) {
+            const intx4 rx = buffer_words(xin + smp * sample_x, (uint32_t)(sample_x * 2));
+            const uint32_t edges = negative(x0 - 1) | negative(G - 17 - x0) << 1 | negative(y0 - 1) << 2 |
+                                   negative(G - 5 - y0) << 3 | 64u;
+            const int row0 = (((y0 >> sh) - 1) << hl) + (x0 >> sh) - 1;
+            for (int p = p0; p < 6; ++p) {
+                const int zz = z0 - 1 + p;
+                const uint32_t sides = edges | (negative(zz) | negative(G - 1 - zz)) << 7;
+                const uint32_t first = (uint32_t)(((zz >> sh) << (2 * hl)) + row0) * (uint32_t)chans * 2u;
+                const uint32_t dst =
+                    lds0 + (uint32_t)(slot(to + p - p0) * kWtPlaneItems + copier * 128) * 16u;
+#pragma unroll
+                for (int i = 0; i < 2; ++i) {
+                    const uint32_t v = from[i] + first;
+                    const uint32_t off = side[i] & sides ? kOutside : v;
+                    copy_to_lds(rx, dst + i * 1024, off);
+                }
+            }
+        } else {
+            const intx4 rd = buffer_words(dyin + smp * sample_d, (uint32_t)(sample_d * 2));
+            const uint32_t first = (uint32_t)((z0 << (2 * lg)) + (y0 << lg) + x0) * (uint32_t)a.ys * 2u;
+            const uint32_t dst = lds0 + (uint32_t)(W::halo + buf * W::dy_buf) * 16u;
+#pragma unroll
+            for (int i = 0; i < W::dy_it; ++i) {
+                const int c = 2 * i + copier - 2;
+                if (c >= W::dy_copies) continue;
+                const uint32_t off = from[i] + first;
+                copy_to_lds(rd, dst + (uint32_t)c * 1024u, off);
             }
         }
     };
-    // products of brick b: k step s reads halo plane z0 - 1 + s / 2 + dz + 1
-    auto products = [&](int64_t b) __attribute__((always_inline)) {
-        const char* sb = (const char*)set;
-        const int z0 = (int)((uint32_t)b % (uint32_t)nbz) * 4;
-        uint32_t bp[4];  // the lane's base in the slot of the plane of steps 2 p, 2 p + 1
+    // k value 8 q + 4 i + e of a step (i: which piece, e = r / 4) is the voxel
+    // (row 2 rp + q % 2, cell 8 (q / 2) + 4 i + e) of its plane; the lane reads
+    // channels 4 (r % 4) .. + 3 of it
+    const int e = r >> 2, ac = r & 3;
+    const int dyw = wave % 3, plane = wave / 3;  // this wave's dy + 1 and plane (waves 0 .. 11)
+    const uint32_t laneA = (uint32_t)(W::halo * 16 + ((q & 1) * W::dy_row + (8 * (q >> 1) + e) * 2 * RS) * 16 +
+                                      ac * 8 + plane * 4 * W::dy_row * 16);
+    const uint32_t laneB = (uint32_t)((((q & 1) + dyw) * kWtHaloRow + 8 * (q >> 1) + e) * 32 + ac * 8);
+    floatx4 acc[3][3][RS];
 #pragma unroll
-        for (int p = 0; p < 4; ++p) {
-            bp[p] = laneB + (uint32_t)(((z0 - 1 + dzw + p) & (kWtRing - 1)) * kWtPlaneItems * 16);
-            __asm__ volatile("" : "+v"(bp[p]));
+    for (int z = 0; z < 3; ++z)
+#pragma unroll
+        for (int x = 0; x < 3; ++x)
+#pragma unroll
+            for (int m = 0; m < RS; ++m) acc[z][x][m] = floatx4{0.f, 0.f, 0.f, 0.f};
+    floatx4 accb[RS];
+#pragma unroll
+    for (int m = 0; m < RS; ++m) accb[m] = floatx4{0.f, 0.f, 0.f, 0.f};
+    const bool bias_wave = chunk == 0 && dyw == 0;
+    auto products = [&](int base, int buf) __attribute__((always_inline)) {
+        const char* sb = (const char*)set;
+        const uint32_t la = laneA + (uint32_t)(buf * W::dy_buf * 16);
+        bf16x8 av[2][RS];
+#pragma unroll
+        for (int rp = 0; rp < 2; ++rp)
+#pragma unroll
+            for (int m = 0; m < RS; ++m) {
+                const uint32_t at = la + 2 * rp * W::dy_row * 16 + m * 32;
+                av[rp][m] = tr_fragment(sb, at, at + 4 * 32 * RS);
+            }
+        if (bias_wave) {
+#pragma unroll
+            for (int rp = 0; rp < 2; ++rp)
+#pragma unroll
+                for (int m = 0; m < RS; ++m)
+                    accb[m] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av[rp][m], ones_frag(), accb[m],
+                                                                      0, 0, 0);
         }
 #pragma unroll
-        for (int s = 0; s < 8; ++s) {
-            const int ra = ((s >> 1) * 4 + 2 * (s & 1)) * kDyRow * 16;  // the step's first row
-            const int vb = 2 * (s & 1) * kWtHaloRow;  // slot of the step's first cell in its plane
-            bf16x8 av[RS];
+        for (int z = 0; z < 3; ++z) {  // dz + 1: halo plane `plane` + z
+            const uint32_t lb = laneB + (uint32_t)(slot(base + plane + z) * kWtPlaneItems * 16);
+#pragma unroll
+            for (int rp = 0; rp < 2; ++rp) {
+                typedef uint32_t uintx2 __attribute__((ext_vector_type(2)));
+                typedef uint32_t uintx4 __attribute__((ext_vector_type(4)));
+                uint32_t w[6];  // 12 voxels of the row, two a word
+#pragma unroll
+                for (int i = 0; i < 3; ++i) {
+                    const uintx2 d = __builtin_bit_cast(
+                        uintx2, __builtin_amdgcn_ds_read_tr16_b64_v4i16(
+                                    (lds_shortx4_ptr)(sb + lb + (2 * rp * kWtHaloRow + 4 * i) * 32)));
+                    w[2 * i] = d[0];
+                    w[2 * i + 1] = d[1];
+                }
+                uintx4 f[3];
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    f[0][i] = w[i];
+                    f[1][i] = __builtin_amdgcn_alignbit(w[i + 1], w[i], 16);
+                    f[2][i] = w[i + 1];
+                }
+#pragma unroll
+                for (int x = 0; x < 3; ++x)
+#pragma unroll
+                    for (int m = 0; m < RS; ++m)
+                        acc[z][x][m] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+                            av[rp][m], __builtin_bit_cast(bf16x8, f[x]), acc[z][x][m], 0, 0, 0);
+            }
+        }
+    };
+    // A brick's first halo plane is 4 ring slots on from its z neighbour's, 6 on
+    // at the start of a column; its slots are free again once the next brick's
+    // products start.
+    auto follows = [&](int b) { return b > b0 && (b & (nbz - 1)) != 0; };
+    if (copier >= 0) {
+        int next = b0, end = 0, wslot = 0, wbuf = 0;  // next brick, ring position (counting up), slot, buffer
+        int base = 0;                                 // position of the current brick's first plane
+        for (int b = b0; b < b1; ++b) {
+            // copy ahead as far as the ring and the buffers go: once under way,
+            // one brick (whose slots the last brick has left)
+            auto fill = [&]() __attribute__((always_inline)) {
+                while (next < b1 && next - b <= W::ahead) {
+                    const bool f = follows(next);
+                    const int planes = f ? 4 : 6;
+                    if (end + planes - base > W::ring) break;
+                    issue(next, f ? 2 : 0, wslot, wbuf);
+                    end += planes;
+                    wslot = slot(wslot + planes);
+                    wbuf = wbuf == W::ahead ? 0 : wbuf + 1;
+                    ++next;
+                }
+            };
+            if (b == b0) fill();
+            // the brick's copies have landed: later ones of this wave, at least
+            // 8 (dy_min) for each brick copied after it, may be outstanding
+            const int later = next - b - 1;
+            if (copier < 2) {
+                if (later >= 4) copies_outstanding<32>();
+                else if (later == 3) copies_outstanding<24>();
+                else if (later == 2) copies_outstanding<16>();
+                else if (later == 1) copies_outstanding<8>();
+                else copies_outstanding<0>();
+            } else {
+                if (later >= 4) copies_outstanding<4 * W::dy_min>();
+                else if (later == 3) copies_outstanding<3 * W::dy_min>();
+                else if (later == 2) copies_outstanding<2 * W::dy_min>();
+                else if (later == 1) copies_outstanding<W::dy_min>();
+                else copies_outstanding<0>();
+            }
+            block_barrier();
+            if (b > b0) fill();
+            base += follows(b + 1) ? 4 : 6;
+        }
+    } else {
+        int bslot = 0, bbuf = 0;
+        for (int b = b0; b < b1; ++b) {
+            copies_landed<0>();  // (none of its own: its LDS reads are done)
+            products(bslot, bbuf);
+            bslot = slot(bslot + (follows(b + 1) ? 4 : 6));
+            bbuf = bbuf == W::ahead ? 0 : bbuf + 1;
+        }
+    }
+    // The four planes' sums: planes 2 and 3 through LDS to 0 and 1, then 1 to 0.
+    constexpr int kSums = 9 * RS + RS;
+    static_assert(6 * kSums * 64 <= W::lds_items, "the sums fit");
+    floatx4* red = (floatx4*)set;
+    auto put = [&](int at) __attribute__((always_inline)) {
+        floatx4* p = red + (at * 3 + dyw) * kSums * 64 + lane;
+#pragma unroll
+        for (int z = 0; z < 3; ++z)
+#pragma unroll
+            for (int x = 0; x < 3; ++x)
+#pragma unroll
+                for (int m = 0; m < RS; ++m) p[((z * 3 + x) * RS + m) * 64] = acc[z][x][m];
+#pragma unroll
+        for (int m = 0; m < RS; ++m) p[(9 * RS + m) * 64] = accb[m];
+    };
+    auto add = [&](int at) __attribute__((always_inline)) {
+        const floatx4* p = red + (at * 3 + dyw) * kSums * 64 + lane;
+#pragma unroll
+        for (int z = 0; z < 3; ++z)
+#pragma unroll
+            for (int x = 0; x < 3; ++x)
+#pragma unroll
+                for (int m = 0; m < RS; ++m) acc[z][x][m] += p[((z * 3 + x) * RS + m) * 64];
+#pragma unroll
+        for (int m = 0; m < RS; ++m) accb[m] += p[(9 * RS + m) * 64];
+    };
+    __syncthreads();
+    if (plane == 2 || plane == 3) put(plane - 2);
+    __syncthreads();
+    if (plane < 2) add(plane);
+    __syncthreads();
+    if (plane == 1) put(0);
+    __syncthreads();
+    if (plane != 0) return;
+    add(0);
+    const int rst = a.coutp / 16, m0 = (int)blockIdx.z * RS;
+    const int64_t blk = (int64_t)grp * gridDim.x + chunk;
+    float* pb = a.part + blk * (27 * rst * 16 * 16);
+#pragma unroll
+    for (int z = 0; z < 3; ++z)
+#pragma unroll
+        for (int x = 0; x < 3; ++x) {
+            const int t = z * 9 + dyw * 3 + x;
 #pragma unroll
             for (int m = 0; m < RS; ++m)
-                av[m] = tr_fragment(sb, laneA + ra + m * 32, laneA + ra + 4 * 32 * RS + m * 32);
-            if (bias_wave) {
 #pragma unroll
-                for (int m = 0; m < RS; ++m)
-                    accb[m] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av[m], ones_frag(), accb[m], 0, 0, 0);
-            }
-#pragma unroll
-            for (int dx = 0; dx < 3; ++dx) {
-                const uint32_t base = bp[s >> 1];
-                const bf16x8 bv = tr_fragment(sb, base + (vb + dx) * 32, base + (vb + dx + 4) * 32);
-#pragma unroll
-                for (int m = 0; m < RS; ++m)
-                    acc[dx][m] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av[m], bv, acc[dx][m], 0, 0, 0);
-            }
+                for (int k = 0; k < 4; ++k)
+                    pb[((t * rst + m0 + m) * 16 + q * 4 + k) * 16 + r] = acc[z][x][m][k];
         }
-    };
-    for (int64_t b = b0; b < b1; ++b) {
-        issue(b);
-        __builtin_amdgcn_s_waitcnt((7 << 4) | (15 << 8));  // vmcnt 0: this wave's copies landed
-        __syncthreads();
-        products(b);
-        __syncthreads();
-    }
-    const int64_t blk = (int64_t)grp * gridDim.x + chunk;
-    float* pb = a.part + blk * (27 * RS * 16 * 16);
-#pragma unroll
-    for (int dx = 0; dx < 3; ++dx) {
-        const int t = wave * 3 + dx;
-#pragma unroll
-        for (int m = 0; m < RS; ++m)
-#pragma unroll
-            for (int k = 0; k < 4; ++k) pb[((t * RS + m) * 16 + q * 4 + k) * 16 + r] = acc[dx][m][k];
-    }
     if (bias_wave && r == 0) {
-        float* bb = a.part + a.bias_off + (int64_t)grp * (RS * 16);
+        float* bb = a.part + a.bias_off + (int64_t)grp * (rst * 16) + m0 * 16;
 #pragma unroll
         for (int m = 0; m < RS; ++m)
 #pragma unroll
@@ -1485,34 +1481,6 @@ constexpr int kCvWRow = 8 * kCvWItemsRow;   // elements per LDS weight row (928 
 // two voxels on (or anywhere, with zero weights).
 __device__ constexpr int cv_pair_tap(int p) {
     return p <= 8 ? p + 18 : p <= 11 ? p + 6 : p == 12 ? 14 : -1;
-}
-
-// Direct-to-LDS copy of 16 bytes per lane, from byte off of the buffer (zeros
-// past its end) to LDS byte `lds` (the wave's, in a scalar) plus 16 times the
-// lane.  Written as an instruction because the compiler, which cannot tell the
-// two halo buffers apart across the loop, would wait for the copies of the
-// next step before every LDS read of this one; it has no register result.
-// The waits are the caller's: copies_landed.
-typedef int intx4 __attribute__((ext_vector_type(4)));
-__device__ __forceinline__ intx4 buffer_words(const void* base, uint32_t bytes) {
-    const uint64_t p = (uint64_t)base;
-    return intx4{__builtin_amdgcn_readfirstlane((int)(uint32_t)p),
-                 __builtin_amdgcn_readfirstlane((int)(uint32_t)(p >> 32) & 0xFFFF),
-                 __builtin_amdgcn_readfirstlane((int)bytes), 0x00020000};
-}
-__device__ __forceinline__ void copy_to_lds(intx4 rsrc, uint32_t lds, uint32_t off) {
-    __asm__ volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds"
-                     :
-                     : "s"(lds), "v"(off), "s"(rsrc)
-                     : "memory");
-}
-// Waits until at most `later` of this wave's vector-memory operations are
-// outstanding (they finish in order) and its LDS reads are done, then for the
-// block's other waves.
-template <int later>
-__device__ __forceinline__ void copies_landed() {
-    static_assert(later < 16, "low bits of the count");
-    __asm__ volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" : : "n"(later) : "memory");
 }
 
 template <int NSUB, int WY, bool ONE>
@@ -2212,8 +2180,8 @@ int64_t wgrad_tr_resident(int rs) {
         hipError_t e = hipGetDevice(&dev);
         if (e == hipSuccess) e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
         if (e == hipSuccess)
-            e = rs == 2 ? hipOccupancyMaxActiveBlocksPerMultiprocessor(&per, k_wgrad_tr<2>, 64 * kWtWaves, 0)
-                        : hipOccupancyMaxActiveBlocksPerMultiprocessor(&per, k_wgrad_tr<1>, 64 * kWtWaves, 0);
+            e = rs == 2 ? hipOccupancyMaxActiveBlocksPerMultiprocessor(&per, k_wgrad_tr<2>, 64 * kWgWaves, 0)
+                        : hipOccupancyMaxActiveBlocksPerMultiprocessor(&per, k_wgrad_tr<1>, 64 * kWgWaves, 0);
         c = e == hipSuccess && cus > 0 && per > 0 ? (int64_t)cus * std::min(per, 2) : 512;
     }
     return c;
@@ -2249,11 +2217,10 @@ WgradPlan wgrad_plan(const ConvGeom& g, int relu) {
     if (p.brick) {
         p.rs = g.coutp / 16;
         p.chunks = ceil_div(g.cin, 16);
-        // bricks of 16 x 4 x 4 voxels (k_wgrad_tr) or 16 x 4 x 2 (k_wgrad_brick)
-        const int64_t nbricks = M / (p.rs == 4 ? 128 : 256);
+        const int64_t nbricks = M / 256;  // 16 x 4 x 4 voxels
         const int64_t blk_floats = (int64_t)27 * g.coutp * 16;
-        // k_wgrad_tr: one generation of resident blocks
-        const int64_t blocks = p.rs == 4 ? kPartBlocks : wgrad_tr_resident(p.rs);
+        // one generation of resident blocks (64 output channels: two a range)
+        const int64_t blocks = p.rs == 4 ? wgrad_tr_resident(2) / 2 : wgrad_tr_resident(p.rs);
         const int64_t cap = std::max<int64_t>(
             1, std::min<int64_t>(blocks, kPartFloats / blk_floats) / p.chunks);
         const int64_t groups = std::max<int64_t>(1, std::min<int64_t>(nbricks, cap));
@@ -2371,12 +2338,11 @@ hipError_t conv_backward_weight(const ConvGeom& g, const __bf16* x1, const __bf1
         return launch_partials_sum(a, p.chunks, p.groups, p.rs, dw, db, s);
     }
     if (p.brick) {
-        const dim3 grid(p.chunks, p.groups);
-        switch (p.rs) {
-            case 4: hipLaunchKernelGGL(k_wgrad_brick<4>, grid, dim3(256), 0, s, a, p.per); break;
-            case 2: hipLaunchKernelGGL(k_wgrad_tr<2>, grid, dim3(64 * kWtWaves), 0, s, a, p.per); break;
-            default: hipLaunchKernelGGL(k_wgrad_tr<1>, grid, dim3(64 * kWtWaves), 0, s, a, p.per); break;
-        }
+        const dim3 grid(p.chunks, p.groups, p.rs == 4 ? 2 : 1), block(64 * kWgWaves);
+        if (p.rs == 1)
+            hipLaunchKernelGGL(k_wgrad_tr<1>, grid, block, 0, s, a, p.per);
+        else
+            hipLaunchKernelGGL(k_wgrad_tr<2>, grid, block, 0, s, a, p.per);
         hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
         return launch_partials_sum(a, p.chunks, p.groups, p.rs, dw, db, s);
