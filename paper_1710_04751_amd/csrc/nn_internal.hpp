@@ -44,10 +44,12 @@ hipError_t pack_weights(int layers, const ConvGeom* g, const float* theta, const
 int64_t conv_scratch_floats(const ConvGeom& g);
 
 // out = conv(x1, x2) + bias, ReLU if relu; BF16 channels-last [n][v][ys].
+// pool (may be null): pool_forward of out, by the convolution itself on grids
+// of 16 cells and more.
 // scratch: scratch_floats device floats (conv_scratch_floats(g) or more), or
 // null (the tiled kernel then runs on 8-cell grids).
 hipError_t conv_forward(const ConvGeom& g, const __bf16* x1, const __bf16* x2, const __bf16* wp,
-                        const float* bias, int relu, __bf16* out, float* scratch,
+                        const float* bias, int relu, __bf16* out, __bf16* pool, float* scratch,
                         int64_t scratch_floats, hipStream_t s);
 
 // Input gradient: dx[n][v][cin] = sum over taps and co of dy at the
@@ -58,6 +60,16 @@ hipError_t conv_forward(const ConvGeom& g, const __bf16* x1, const __bf16* x2, c
 hipError_t conv_backward_data(const ConvGeom& g, const __bf16* dy, const __bf16* wt,
                               const __bf16* dxmask, __bf16* dx, float* scratch,
                               int64_t scratch_floats, hipStream_t s);
+
+// Input gradient of a layer with concatenated inputs: of the first c1s
+// channels into dcat, concat_skip_channels(g) channels per cell (the others
+// undefined), of the upsampled c2 channels as upsample_backward leaves it into
+// dup, masked by upmask.  On grids of 16 cells and more the convolution adds
+// the upsampled channels up itself and dcat has only the first c1s.
+int concat_skip_channels(const ConvGeom& g);
+hipError_t conv_backward_concat(const ConvGeom& g, const __bf16* dy, const __bf16* wt,
+                                const __bf16* upmask, __bf16* dcat, __bf16* dup, float* scratch,
+                                int64_t scratch_floats, hipStream_t s);
 
 // Weight and bias gradients, written into the master layout:
 // dw[co][tap][ci] = sum_v dpre[v][co] x(v + tap)[ci], db[co] = sum_v

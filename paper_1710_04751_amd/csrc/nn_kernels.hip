@@ -70,6 +70,13 @@ struct ConvArgs {
     const __bf16* omask;  // outputs where omask <= 0 are written as 0
     int32_t n, lg, taps, c1s, c2, cin, K, kpad, cout, ys, relu;
     int32_t wrows;        // rows of the packed weight w (set by launch_conv)
+    // The brick kernel's second result, on the grid of half the cells (null:
+    // none).  With a bias: the averages of 2 x 2 x 2 results.  Without: the
+    // sums over 2 x 2 x 2 of the channels from `split` on (a multiple of 16),
+    // 0 where lowmask is not positive; out then has the first `split` only.
+    __bf16* low = nullptr;
+    const __bf16* lowmask = nullptr;
+    int32_t split = 0;
 };
 
 // The convolutions' results: lane (r, q) has channels co .. co + 3 (co a
@@ -1453,7 +1460,9 @@ __global__ void k_cf_to_cl(const float* __restrict__ x, int n, int64_t V, int c,
 // BF16 output, grids of at least 16 cells, input channels a multiple of 16,
 // or 8 with no second tensor).  A block of 8 WY waves computes bricks of 16 x
 // 4 WY x 8 output voxels (wave w the plane z0 + w % 8, the four 16-voxel row
-// tiles from y0 + 4 (w / 8)) for NSUB * 16 output channels.  A step takes 16
+// tiles from y0 + 4 (w / 8), whose taps share most of their halo rows; where
+// 2 x 2 x 2 cells are added up, rows y0 + 2 (w / 4), + 1 of planes z0 + 2 (w %
+// 4), + 1) for NSUB * 16 output channels.  A step takes 16
 // input channels of a brick: the 18 x (4 WY + 2) x 10 input halo
 // (channels-last, 32 bytes per voxel: lane r reads voxel r and its second 8
 // channels sit 16 bytes on, which the LDS serves without bank conflicts) and
@@ -1501,15 +1510,26 @@ struct CvShape {
 
 // ONE: one step a brick (at most 16 input channels), so the weights are
 // copied once.  EPI: what the results take (kPlain; kBias: bias and ReLU;
-// kMask: 0 where the mask is not positive).  work: bricks in all, per: bricks
-// per block.  The output channels are a multiple of 16.
+// kMask: 0 where the mask is not positive; kBiasPool: kBias, and averages over
+// 2 x 2 x 2 to a.low; kUp: the first a.split channels as kPlain, of the others
+// only their sums over 2 x 2 x 2 to a.low, 0 where a.lowmask is not positive).
+// work: bricks in all, per: bricks per block.  The output channels are a
+// multiple of 16.
+//
+// kBiasPool and kUp take the pooling and the gradient of the upsampling out of
+// their own passes over memory, for the sums of four tiles of a wave and of
+// lane pairs: the additions are those passes', of the rounded results and in
+// their order.  8 samples: at 64^3 with the pooling 37 us (32 and 13 apart), 16
+// -> 16 + 32 with the upsampling's gradient 72 us (71 and 35 apart: 134 MB less
+// written and read, now the products' and sums' issue slots), 32 -> 32 + 64 at
+// 32^3 48 (45 and 10); the skip's gradient, now dense, is read in 35 us (63).
 //
 // Everything outside the products is kept short, for it takes the issue slots
 // of all waves in step: addresses are a lane register plus scalars, and the
 // results have no branches.  (With general results and per-item address
 // arithmetic, 184 vector and 272 scalar instructions a wave and step beside
 // the 56 products, the same walk took 41-43 us instead of 30-33.)
-enum { kPlain, kBias, kMask };
+enum { kPlain, kBias, kMask, kBiasPool, kUp };
 
 template <int NSUB, int WY, bool ONE, int EPI>
 __global__ void __launch_bounds__(64 * kCvPlanes * WY)
@@ -1640,7 +1660,11 @@ k_conv_brick(ConvArgs a, int work, int per) {
     floatx4 acc[4][NSUB];
     const int ch = (q & 1) * 8;
     // LDS byte addresses of this lane: A (weights), B (halo) per shift group
-    const uint32_t lb = (uint32_t)((wave & 7) * C::plane + (wave >> 3) * 4 * 18 + r);
+    constexpr bool kCells = EPI == kBiasPool || EPI == kUp;
+    const int wz = kCells ? (wave & 3) * 2 : wave & 7, wy = kCells ? (wave >> 2) * 2 : (wave >> 3) * 4;
+    auto row = [](int m) { return kCells ? m & 1 : m; };  // of tile m, from the wave's first
+    auto plane = [](int m) { return kCells ? m >> 1 : 0; };
+    const uint32_t lb = (uint32_t)(wz * C::plane + wy * 18 + r);
     const uint32_t vB0 = ((lb + hi * 2 * C::plane) * kCvVox + ch) * 2;
     const uint32_t vB1 = ((lb + hi * 2 * 18) * kCvVox + ch) * 2;
     const uint32_t vB2 = ((lb + hi * 2) * kCvVox + ch) * 2;
@@ -1648,13 +1672,19 @@ k_conv_brick(ConvArgs a, int work, int per) {
     uint32_t vA = (uint32_t)(2 * C::buf * 16 + (r * kCvWRow + hi * 16 + ch) * 2);
     __asm__ volatile("" : "+v"(vA));  // (as a constant it would pass the reads' 16-bit offsets)
     // D rows 4q .. 4q+3 are output channels, column r the voxel x0 + r: the
-    // lane's byte from the brick's first voxel, per tile a row further
+    // lane's byte from the brick's first voxel (tile 0)
     const uint32_t vout =
-        (uint32_t)(((((wave & 7) << (2 * lg)) + ((wave >> 3) * 4 << lg) + r) * a.ys) + cobase + 4 * q) * 2u;
-    const uint32_t row_bytes = (uint32_t)a.ys * 2u << lg;
+        (uint32_t)((((wz << (2 * lg)) + (wy << lg) + r) * a.ys) + cobase + 4 * q) * 2u;
+    const uint32_t row_bytes = (uint32_t)a.ys * 2u << lg, plane_bytes = row_bytes << lg;
     const int64_t sample_out = (int64_t)a.ys << (3 * lg);
+    // in a.low: the even lanes' byte from the brick's first coarse voxel
+    const int lows = EPI == kUp ? a.cout - a.split : a.cout;
+    const uint32_t vlow =
+        r & 1 ? kOutside
+              : (uint32_t)((((wave & 3) << (2 * h)) + ((wave >> 2) << h) + (r >> 1)) * lows + 4 * q) * 2u;
+    const int64_t sample_low = (int64_t)lows << (3 * h);
     floatx4 bias[NSUB];
-    if constexpr (EPI == kBias) {
+    if constexpr (EPI == kBias || EPI == kBiasPool) {
 #pragma unroll
         for (int j = 0; j < NSUB; ++j)
 #pragma unroll
@@ -1675,14 +1705,18 @@ k_conv_brick(ConvArgs a, int work, int per) {
     for (int b = b0; b < b1;) {
         // this step's copies have landed (only the last brick's stores were
         // issued after them), and every wave is done with the other buffer
-        if (stored)
-            copies_landed<4 * NSUB>();
-        else
+        if (!stored)
             copies_landed<0>();
+        else if (EPI == kUp && cobase >= a.split)
+            copies_landed<NSUB>();
+        else
+            copies_landed<EPI == kUp ? NSUB + 3 : EPI == kBiasPool ? 5 * NSUB : 4 * NSUB>();
         const bool last = ONE || chunk + 1 == chunks;
         const uint32_t first = vout + (uint32_t)o.out * (uint32_t)a.ys * 2u;
         // the mask is loaded ahead of the products
-        uintx2 mask[EPI == kMask ? 4 * NSUB : 1];
+        uintx2 mask[EPI == kMask ? 4 * NSUB : NSUB];
+        const int olow = o.coarse + (1 << (2 * h)) + (1 << h) + 1;  // the brick's first coarse voxel
+        const uint32_t first_low = vlow + (uint32_t)olow * (uint32_t)lows * 2u;
         if constexpr (EPI == kMask) {
             if (last) {
                 const __amdgpu_buffer_rsrc_t rm = __builtin_amdgcn_make_buffer_rsrc(
@@ -1692,9 +1726,22 @@ k_conv_brick(ConvArgs a, int work, int per) {
                 for (int m = 0; m < 4; ++m)
 #pragma unroll
                     for (int j = 0; j < NSUB; ++j) {
-                        const uint32_t off = first + m * row_bytes + j * 32;
+                        const uint32_t off = first + row(m) * row_bytes + plane(m) * plane_bytes + j * 32;
                         mask[m * NSUB + j] = __builtin_amdgcn_raw_buffer_load_b64(rm, off, 0, 0);
                     }
+            }
+        }
+        if constexpr (EPI == kUp) {
+            if (last) {
+                const __amdgpu_buffer_rsrc_t rm = __builtin_amdgcn_make_buffer_rsrc(
+                    const_cast<__bf16*>(a.lowmask + o.smp * sample_low), (short)0,
+                    (int)(uint32_t)(sample_low * 2), 0x00020000);
+#pragma unroll
+                for (int j = 0; j < NSUB; ++j) {
+                    const int c = cobase + j * 16 - a.split;  // (of a.out's channels: not used)
+                    const uint32_t off = first_low + (uint32_t)(c < 0 ? 0 : c) * 2u;
+                    mask[j] = __builtin_amdgcn_raw_buffer_load_b64(rm, off, 0, 0);
+                }
             }
         }
         const char* xsb = (const char*)lds + set * C::buf * 16;
@@ -1711,7 +1758,7 @@ k_conv_brick(ConvArgs a, int work, int per) {
                     av[j] = *(const bf16x8*)(wlb + vA + (j * 16 * kCvWRow + p * 32) * 2);
 #pragma unroll
                 for (int m = 0; m < 4; ++m)
-                    bv[m] = *(const bf16x8*)(xsb + vb + (toff + m * 18) * kCvVox * 2);
+                    bv[m] = *(const bf16x8*)(xsb + vb + (toff + row(m) * 18 + plane(m) * C::plane) * kCvVox * 2);
 #pragma unroll
                 for (int m = 0; m < 4; ++m)
 #pragma unroll
@@ -1726,8 +1773,9 @@ k_conv_brick(ConvArgs a, int work, int per) {
         // the first products, so that the scalar work for them runs beside the
         // matrix cores (48 channels at 64^3 88 -> 86 us); with one, where the
         // stores of every step make memory the bound, before them (16 -> 48
-        // channels 73 us, 78 after).
-        constexpr int kAhead = ONE ? 0 : 2;
+        // channels 73 us, 78 after); not with kUp, which stores less (75 us
+        // before, 72 after).
+        constexpr int kAhead = ONE && EPI != kUp ? 0 : 2;
         products(0, kAhead);
         int nbk = b, nch = chunk + 1;
         Place on = o;
@@ -1741,24 +1789,79 @@ k_conv_brick(ConvArgs a, int work, int per) {
         if (last) {
             const __amdgpu_buffer_rsrc_t ro = __builtin_amdgcn_make_buffer_rsrc(
                 a.out + o.smp * sample_out, (short)0, (int)(uint32_t)(sample_out * 2), 0x00020000);
+            auto result = [&](int m, int j) __attribute__((always_inline)) {
+                bf16x4 v;
 #pragma unroll
-            for (int m = 0; m < 4; ++m)
+                for (int i = 0; i < 4; ++i) {
+                    float t = acc[m][j][i];
+                    if constexpr (EPI == kBias || EPI == kBiasPool) t = fmaxf(t + bias[j][i], floor);
+                    if constexpr (EPI == kMask) {
+                        const bf16x4 k = __builtin_bit_cast(bf16x4, mask[m * NSUB + j]);
+                        t = (float)k[i] > 0.f ? t : 0.f;
+                    }
+                    v[i] = (__bf16)t;
+                }
+                return v;
+            };
+            auto store = [&](int m, int j, bf16x4 v) __attribute__((always_inline)) {
+                const uint32_t off = first + row(m) * row_bytes + plane(m) * plane_bytes + j * 32;
+                __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(uintx2, v), ro, off, 0, 0);
+            };
+            // a coarse voxel's sum, in the even lanes: the lane's value and its
+            // neighbour's in x, tile after tile (y, then z)
+            auto add = [&](floatx4& sum, bf16x4 v) __attribute__((always_inline)) {
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    const float t = (float)v[i];
+                    sum[i] += t;
+                    sum[i] += dpp_moved<0xF5, 0xF>(t);  // quad_perm [1, 1, 3, 3]
+                }
+            };
+            auto store_low = [&](bf16x4 v, int c) __attribute__((always_inline)) {
+                const __amdgpu_buffer_rsrc_t rl = __builtin_amdgcn_make_buffer_rsrc(
+                    a.low + o.smp * sample_low, (short)0, (int)(uint32_t)(sample_low * 2), 0x00020000);
+                const uint32_t off = first_low + (uint32_t)c * 2u;
+                __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(uintx2, v), rl, off, 0, 0);
+            };
+            if constexpr (EPI == kBiasPool) {
 #pragma unroll
                 for (int j = 0; j < NSUB; ++j) {
-                    bf16x4 v;
+                    floatx4 sum = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-                    for (int i = 0; i < 4; ++i) {
-                        float t = acc[m][j][i];
-                        if constexpr (EPI == kBias) t = fmaxf(t + bias[j][i], floor);
-                        if constexpr (EPI == kMask) {
-                            const bf16x4 k = __builtin_bit_cast(bf16x4, mask[m * NSUB + j]);
-                            t = (float)k[i] > 0.f ? t : 0.f;
-                        }
-                        v[i] = (__bf16)t;
+                    for (int m = 0; m < 4; ++m) {
+                        const bf16x4 v = result(m, j);
+                        store(m, j, v);
+                        add(sum, v);
                     }
-                    const uint32_t off = first + m * row_bytes + j * 32;
-                    __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(uintx2, v), ro, off, 0, 0);
+                    bf16x4 p;
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) p[i] = (__bf16)(sum[i] * 0.125f);
+                    store_low(p, cobase + j * 16);
                 }
+            } else if constexpr (EPI == kUp) {
+#pragma unroll
+                for (int j = 0; j < NSUB; ++j) {
+                    const int c = cobase + j * 16 - a.split;
+                    if (c < 0) {
+#pragma unroll
+                        for (int m = 0; m < 4; ++m) store(m, j, result(m, j));
+                    } else {
+                        floatx4 sum = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                        for (int m = 0; m < 4; ++m) add(sum, result(m, j));
+                        const bf16x4 k = __builtin_bit_cast(bf16x4, mask[j]);
+                        bf16x4 v;
+#pragma unroll
+                        for (int i = 0; i < 4; ++i) v[i] = (float)k[i] > 0.f ? (__bf16)sum[i] : (__bf16)0.f;
+                        store_low(v, c);
+                    }
+                }
+            } else {
+#pragma unroll
+                for (int m = 0; m < 4; ++m)
+#pragma unroll
+                    for (int j = 0; j < NSUB; ++j) store(m, j, result(m, j));
+            }
             clear();
         }
         stored = last;
@@ -1947,7 +2050,11 @@ hipError_t launch_conv_wy(const ConvArgs& a, int groups, int64_t bricks, hipStre
     const int64_t per = (bricks + most - 1) / most;
     const dim3 grid((unsigned)((bricks + per - 1) / per), groups), block(64 * kCvPlanes * WY);
     const int w = (int)bricks, p = (int)per;
-    if (a.omask)
+    if (a.low && a.bias)
+        hipLaunchKernelGGL((k_conv_brick<NSUB, WY, ONE, kBiasPool>), grid, block, 0, s, a, w, p);
+    else if (a.low)
+        hipLaunchKernelGGL((k_conv_brick<NSUB, WY, ONE, kUp>), grid, block, 0, s, a, w, p);
+    else if (a.omask)
         hipLaunchKernelGGL((k_conv_brick<NSUB, WY, ONE, kMask>), grid, block, 0, s, a, w, p);
     else if (a.bias)
         hipLaunchKernelGGL((k_conv_brick<NSUB, WY, ONE, kBias>), grid, block, 0, s, a, w, p);
@@ -2075,7 +2182,7 @@ hipError_t pack_weights(int layers, const ConvGeom* g, const float* theta, const
 }
 
 hipError_t conv_forward(const ConvGeom& g, const __bf16* x1, const __bf16* x2, const __bf16* wp,
-                        const float* bias, int relu, __bf16* out, float* scratch,
+                        const float* bias, int relu, __bf16* out, __bf16* pool, float* scratch,
                         int64_t scratch_floats, hipStream_t s) {
     if (!x1 || !wp || !out || (g.c2 > 0 && (!x2 || g.lg < 1)) || g.c1s % 8 || g.c2 % 8)
         return hipErrorInvalidValue;
@@ -2097,13 +2204,18 @@ hipError_t conv_forward(const ConvGeom& g, const __bf16* x1, const __bf16* x2, c
     a.cout = g.cout;
     a.ys = g.ys;
     a.relu = relu;
-    return launch_conv(a, g.coutp, scratch, scratch_floats, s);
+    if (pool && conv_brick_covers(a, g.coutp)) {
+        a.low = pool;
+        pool = nullptr;
+    }
+    const hipError_t e = launch_conv(a, g.coutp, scratch, scratch_floats, s);
+    return e == hipSuccess && pool ? pool_forward(g.n, g.lg, g.ys, out, pool, s) : e;
 }
 
-hipError_t conv_backward_data(const ConvGeom& g, const __bf16* dy, const __bf16* wt,
-                              const __bf16* dxmask, __bf16* dx, float* scratch,
-                              int64_t scratch_floats, hipStream_t s) {
-    if (!dy || !wt || !dx) return hipErrorInvalidValue;
+namespace {
+
+ConvArgs backward_args(const ConvGeom& g, const __bf16* dy, const __bf16* wt, const __bf16* dxmask,
+                       __bf16* dx) {
     ConvArgs a;
     a.x1 = dy;
     a.x2 = nullptr;
@@ -2122,7 +2234,39 @@ hipError_t conv_backward_data(const ConvGeom& g, const __bf16* dy, const __bf16*
     a.cout = g.cin;
     a.ys = g.cin;
     a.relu = 0;
-    return launch_conv(a, g.cinp, scratch, scratch_floats, s);
+    return a;
+}
+
+// Whether the brick kernel sums the upsampled channels' gradients itself.
+bool concat_fused(const ConvGeom& g) {
+    return g.c1s % 16 == 0 && conv_brick_covers(backward_args(g, nullptr, nullptr, nullptr, nullptr), g.cinp);
+}
+
+}  // namespace
+
+hipError_t conv_backward_data(const ConvGeom& g, const __bf16* dy, const __bf16* wt,
+                              const __bf16* dxmask, __bf16* dx, float* scratch,
+                              int64_t scratch_floats, hipStream_t s) {
+    if (!dy || !wt || !dx) return hipErrorInvalidValue;
+    return launch_conv(backward_args(g, dy, wt, dxmask, dx), g.cinp, scratch, scratch_floats, s);
+}
+
+int concat_skip_channels(const ConvGeom& g) { return concat_fused(g) ? g.c1s : g.cin; }
+
+hipError_t conv_backward_concat(const ConvGeom& g, const __bf16* dy, const __bf16* wt,
+                                const __bf16* upmask, __bf16* dcat, __bf16* dup, float* scratch,
+                                int64_t scratch_floats, hipStream_t s) {
+    if (!dy || !wt || !upmask || !dcat || !dup || g.c2 < 1) return hipErrorInvalidValue;
+    ConvArgs a = backward_args(g, dy, wt, nullptr, dcat);
+    if (concat_fused(g)) {
+        a.low = dup;
+        a.lowmask = upmask;
+        a.split = a.ys = g.c1s;
+        return launch_conv_brick(a, g.cinp, s);
+    }
+    const hipError_t e = launch_conv(a, g.cinp, scratch, scratch_floats, s);
+    if (e != hipSuccess) return e;
+    return upsample_backward(g.n, g.lg, g.c2, dcat, g.cin, g.c1s, upmask, dup, s);
 }
 
 int64_t conv_scratch_floats(const ConvGeom& g) {

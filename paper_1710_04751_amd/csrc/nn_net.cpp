@@ -210,15 +210,10 @@ lbm_status forward(lbm_nn* nn, int n, const float* log10_ra) {
         const ConvGeom g = nn->geom(l, n);
         const __bf16 *x1, *x2;
         layer_inputs(nn, l, &x1, &x2);
+        __bf16* pool = l == 1 || l == 3 || l == 5 ? nn->at<__bf16>(L.pool[(l - 1) / 2]) : nullptr;
         NN_TRY(conv_forward(g, x1, x2, nn->at<__bf16>(L.wp[l]), bias_of(nn, l), kDefs[l].relu,
-                            nn->at<__bf16>(L.act[l]), nn->at<float>(L.wpart), L.wpart_floats, s),
+                            nn->at<__bf16>(L.act[l]), pool, nn->at<float>(L.wpart), L.wpart_floats, s),
                "conv forward");
-        if (l == 1 || l == 3 || l == 5) {
-            const int i = (l - 1) / 2;
-            NN_TRY(pool_forward(n, nn->lg(l), kDefs[l].cout, nn->at<__bf16>(L.act[l]),
-                                nn->at<__bf16>(L.pool[i]), s),
-                   "pool");
-        }
     }
     nn->last_n = n;
     return LBM_OK;
@@ -246,6 +241,17 @@ lbm_status backward(lbm_nn* nn, int n) {
                                     nn->at<float>(L.wpart), s),
                "weight grad");
         if (l == 0) break;
+        // (the weight gradient above has finished with wpart: same stream)
+        if (l == 9 || l == 11 || l == 13) {
+            // concatenated inputs: the skip's gradient waits in dcat, the
+            // upsampled half goes to the coarse layer
+            const int i = (13 - l) / 2, src = l == 9 ? 8 : l == 11 ? 10 : 12;
+            NN_TRY(conv_backward_concat(g, dact(l), nn->at<__bf16>(L.wt[l]), act(src),
+                                        nn->at<__bf16>(L.dcat[i]), dact(src),
+                                        nn->at<float>(L.wpart), L.wpart_floats, s),
+                   "concatenation's data grad");
+            continue;
+        }
         // where the input gradient goes, and the ReLU mask it takes there
         __bf16* dx;
         const __bf16* dxmask = nullptr;
@@ -253,25 +259,14 @@ lbm_status backward(lbm_nn* nn, int n) {
             case 2: dx = nn->at<__bf16>(L.dpool[0]); break;
             case 4: dx = nn->at<__bf16>(L.dpool[1]); break;
             case 6: dx = nn->at<__bf16>(L.dpool[2]); break;
-            case 9: dx = nn->at<__bf16>(L.dcat[2]); break;
-            case 11: dx = nn->at<__bf16>(L.dcat[1]); break;
-            case 13: dx = nn->at<__bf16>(L.dcat[0]); break;
             default:
                 dx = dact(l - 1);
                 dxmask = kDefs[l - 1].relu ? act(l - 1) : nullptr;
                 break;
         }
-        // (the weight gradient above has finished with wpart: same stream)
         NN_TRY(conv_backward_data(g, dact(l), nn->at<__bf16>(L.wt[l]), dxmask, dx,
                                   nn->at<float>(L.wpart), L.wpart_floats, s),
                "data grad");
-        if (l == 9 || l == 11 || l == 13) {
-            // the upsampled half of the concatenation -> the coarse layer
-            const int src = l == 9 ? 8 : l == 11 ? 10 : 12;
-            NN_TRY(upsample_backward(n, nn->lg(l), d.c2, dx, g.cin, g.c1s,
-                                     kDefs[src].relu ? act(src) : nullptr, dact(src), s),
-                   "upsample backward");
-        }
         if (l == 2 || l == 4 || l == 6) {
             // pooled input: the encoder layer before it also feeds a skip
             const int i = (l - 2) / 2;
@@ -279,7 +274,7 @@ lbm_status backward(lbm_nn* nn, int n) {
             const ConvGeom gd = nn->geom(dec, n);
             NN_TRY(pool_backward_add(n, nn->lg(l - 1), kDefs[l - 1].cout,
                                      nn->at<__bf16>(L.dpool[i]), nn->at<__bf16>(L.dcat[i]),
-                                     gd.cin, kDefs[l - 1].relu ? act(l - 1) : nullptr,
+                                     concat_skip_channels(gd), kDefs[l - 1].relu ? act(l - 1) : nullptr,
                                      dact(l - 1), s),
                    "pool backward");
         }

@@ -87,3 +87,44 @@ def test_tiled_kernel_groups_on_small_grids(n):
         assert err < 2e-2, (i, err)
     a.close()
     b.close()
+
+
+@pytest.mark.parametrize("grid,n", [(64, 1), (32, 8), (32, 2), (16, 4)])
+def test_pooled_results_are_the_averages(grid, n):
+    """The convolutions before a pooling write its averages themselves (on
+    grids of 16 cells and more).  A network whose layers after the pooling
+    copy their input (centre weight 1 on the diagonal, no bias) shows
+    the pooled values as the next layer's results, which must be the averages
+    of eight BF16 values added in FP32 in (z, y, x) order, rounded once."""
+    import numpy as np
+    from paper_1710_04751_amd import network
+    log("case: pooled results", grid, n)
+    theta = torch.from_numpy(network.init_params(3)).clone()
+    at = 0
+    for name, (cin, cout, edge) in zip(network.LAYER_NAMES, network.LAYER_SHAPES):
+        taps = edge ** 3
+        size = cout * taps * cin
+        if name in ("enc2a", "enc3a", "bota"):
+            w = torch.zeros(cout, taps, cin)
+            for c in range(cin):
+                w[c, 13, c] = 1.0
+            theta[at:at + size] = w.reshape(-1)
+            theta[at + size:at + size + cout] = 0.0
+        at += size + cout
+    assert at == theta.numel()
+    net = network.WarmStartNet(grid, n)
+    net.set_params(theta)
+    net.forward([3.0 + 0.4 * i for i in range(n)])
+    for before, after, c in ((1, 2, 16), (3, 4, 32), (5, 6, 64)):
+        a = net.activation(before, n).cpu()
+        g = a.shape[1]
+        a = a.reshape(n, g // 2, 2, g // 2, 2, g // 2, 2, c)
+        acc = torch.zeros(n, g // 2, g // 2, g // 2, c)
+        for z in range(2):
+            for y in range(2):
+                for x in range(2):
+                    acc = acc + a[:, :, z, :, y, :, x]
+        want = (acc * 0.125).to(torch.bfloat16).float()
+        got = net.activation(after, n).cpu()[..., :c]
+        assert np.array_equal(got.numpy(), want.numpy()), (before, grid)
+    net.close()
