@@ -1249,15 +1249,17 @@ __global__ void k_inputs(int n, int lg, SampleFloats lra, __bf16* __restrict__ x
 // FP32 master weights w[co][ci] and bias b[co].  One thread per voxel.
 constexpr int kHeadIn = 16, kHeadOut = 4, kHeadGrad = kHeadOut * kHeadIn + kHeadOut;
 
-__device__ __forceinline__ void load_head_input(const __bf16* __restrict__ x, int64_t v,
-                                                float* xf) {
-    const bf16x8 lo = *(const bf16x8*)(x + v * kHeadIn);
-    const bf16x8 hi = *(const bf16x8*)(x + v * kHeadIn + 8);
+__device__ __forceinline__ void widen_head_input(bf16x8 lo, bf16x8 hi, float* xf) {
 #pragma unroll
     for (int i = 0; i < 8; ++i) {
         xf[i] = (float)lo[i];
         xf[8 + i] = (float)hi[i];
     }
+}
+
+__device__ __forceinline__ void load_head_input(const __bf16* __restrict__ x, int64_t v,
+                                                float* xf) {
+    widen_head_input(*(const bf16x8*)(x + v * kHeadIn), *(const bf16x8*)(x + v * kHeadIn + 8), xf);
 }
 
 __global__ void __launch_bounds__(256) k_head_forward(int n, int lg, const __bf16* __restrict__ x,
@@ -1310,6 +1312,12 @@ __device__ __forceinline__ float wave_sum_in_last_lane(float v) {
 // its sums (squared error in FP64, the kHeadGrad gradient entries in FP32)
 // are added over the block in a fixed order and written to lpart[b] and
 // gpart[b][kHeadGrad].
+//
+// A voxel's 32 bytes of input and 16 of targets are loaded while the one
+// before is computed; the sample, one for the 256 voxels of a turn, is a
+// scalar (a lane's own index into idx was a load that the targets' loads
+// waited for).  8 samples: 64^3 54 -> 40 us (168 MB: 4.2 TB/s; 2048 blocks 42),
+// 32^3 25 -> 13 with blocks of 512 voxels (2048 before; 1024: 13.3).
 __global__ void __launch_bounds__(256) k_head_backward(
     int n, int lg, const float* __restrict__ tg, SampleInts idx, int64_t stride, float4 ts,
     const __bf16* __restrict__ x, const float* __restrict__ w, const float* __restrict__ b,
@@ -1327,19 +1335,32 @@ __global__ void __launch_bounds__(256) k_head_backward(
     double lsum = 0.0;
     const int64_t v0 = (int64_t)blockIdx.x * chunk;
     const int64_t v1 = v0 + chunk < M ? v0 + chunk : M;
-    for (int64_t v = v0 + threadIdx.x; v < v1; v += blockDim.x) {
-        const int s = (int)(v >> (3 * lg));
-        const int64_t vin = v & (V - 1);
-        float xf[kHeadIn];
-        load_head_input(x, v, xf);
+    // (M, chunk and V are multiples of 256: every thread takes every turn)
+    bf16x8 xlo, xhi;
+    float tv[kHeadOut];
+    auto load = [&](int64_t first) __attribute__((always_inline)) {
+        const int64_t v = first + threadIdx.x;
+        const float* t = tg + (int64_t)idx.v[first >> (3 * lg)] * stride + (v & (V - 1));
+        xlo = *(const bf16x8*)(x + v * kHeadIn);
+        xhi = *(const bf16x8*)(x + v * kHeadIn + 8);
+#pragma unroll
+        for (int c = 0; c < kHeadOut; ++c) tv[c] = t[c * V];
+    };
+    if (v0 < v1) load(v0);
+    for (int64_t first = v0; first < v1; first += 256) {
+        const int64_t v = first + threadIdx.x;
+        float xf[kHeadIn], t[kHeadOut];
+        widen_head_input(xlo, xhi, xf);
+#pragma unroll
+        for (int c = 0; c < kHeadOut; ++c) t[c] = tv[c] * tsc[c];
+        if (first + 256 < v1) load(first + 256);
         float d[kHeadOut];
 #pragma unroll
         for (int c = 0; c < kHeadOut; ++c) {
             float ov = b[c];
 #pragma unroll
             for (int i = 0; i < kHeadIn; ++i) ov = fmaf(w[c * kHeadIn + i], xf[i], ov);
-            const float tv = tg[(int64_t)idx.v[s] * stride + c * V + vin] * tsc[c];
-            const double e = (double)ov - (double)tv;
+            const double e = (double)ov - (double)t[c];
             lsum += e * e;
             d[c] = (float)e * inv;
         }
@@ -2566,7 +2587,7 @@ hipError_t head_forward(const ConvGeom& g, const __bf16* x, const float* w, cons
 
 int head_backward_blocks(const ConvGeom& g) {
     const int64_t M = (int64_t)g.n << (3 * g.lg);
-    return (int)std::min<int64_t>(kHeadBlocks, ceil_div(M, 2048));
+    return (int)std::min<int64_t>(kHeadBlocks, ceil_div(M, 512));
 }
 
 int64_t head_scratch_floats(const ConvGeom& g) {
