@@ -388,20 +388,28 @@ lbm_status lbm_init_macros(lbm_handle* h, const float* ux, const float* uy, cons
     return LBM_OK;
 }
 
-lbm_status lbm_step(lbm_handle* h, int64_t nsteps) {
+// threes: take three steps a launch as long as there are three.
+static lbm_status take_steps(lbm_handle* h, int64_t nsteps, bool threes) {
     if (!h) return fail(LBM_ERR_ARG, "null handle");
     if (h->owner) return fail(LBM_ERR_STATE, "batch members are stepped by lbm_batch_step");
     if (nsteps < 0) return fail(LBM_ERR_ARG, "nsteps must be >= 0");
     const Prec pr = (Prec)h->p.precision;
-    for (int64_t i = 0; i < nsteps; ++i) {
+    for (int64_t i = 0; i < nsteps;) {
         h->c.seed = (uint32_t)h->steps;
-        hipError_t e = launch_step(pr, h->p.thermal_q, h->general, h->geom,
-                                   h->buf(h->cur), h->buf(1 - h->cur), h->c, h->stream);
+        const bool three = threes && nsteps - i >= 3;
+        hipError_t e = (three ? launch_step3 : launch_step)(pr, h->p.thermal_q, h->general, h->geom,
+                                                            h->buf(h->cur), h->buf(1 - h->cur),
+                                                            h->c, h->stream);
         if (e != hipSuccess) return hip_fail(e, "step");
         h->cur = 1 - h->cur;
-        ++h->steps;
+        h->steps += three ? 3 : 1;
+        i += three ? 3 : 1;
     }
     return LBM_OK;
+}
+
+lbm_status lbm_step(lbm_handle* h, int64_t nsteps) {
+    return take_steps(h, nsteps, h && steps_in_threes((Prec)h->p.precision, h->geom));
 }
 
 lbm_status lbm_macros(lbm_handle* h, void* rho, void* ux, void* uy, void* uz, void* T, int fp64) {
@@ -621,10 +629,10 @@ lbm_status lbm_autotune(lbm_handle* h, int32_t steps_per_trial, int32_t* out_bx,
             if (bx * by <= flat) continue;
             flat = bx * by;
         }
-        s = lbm_step(h, 1);  // warm the instruction cache
+        s = take_steps(h, 1, false);  // warm the instruction cache
         if (s != LBM_OK) break;
         e = hipEventRecord(e0, h->stream);
-        if (e == hipSuccess) s = lbm_step(h, steps_per_trial);
+        if (e == hipSuccess) s = take_steps(h, steps_per_trial, false);
         if (e == hipSuccess && s == LBM_OK) e = hipEventRecord(e1, h->stream);
         if (e == hipSuccess && s == LBM_OK) e = hipEventSynchronize(e1);
         float ms = 0;

@@ -77,6 +77,11 @@ inline uint32_t keep_sixteenths(uint64_t bytes) {
 
 hipError_t launch_step(Prec p, int qt, bool general, const Geom& g, StateBuf in,
                        StateBuf out, const Coefs& c, hipStream_t s);
+// Three steps (keyed c.seed, + 1, + 2) in one launch, for boxes where
+// steps_in_threes.
+bool steps_in_threes(Prec p, const Geom& g);
+hipError_t launch_step3(Prec p, int qt, bool general, const Geom& g, StateBuf in, StateBuf out,
+                        const Coefs& c, hipStream_t s);
 hipError_t launch_fill_zero(void* ptr, size_t bytes, hipStream_t s);
 // Rest state: zero-fills state_bytes at state (both buffers), then, with a
 // scalar source, writes the scalar equilibrium at T = -R/2 into st.

@@ -83,6 +83,80 @@ k_step(const S* __restrict__ in, S* __restrict__ out, Geom g, KCoef<R> k) {
                                      p.y0, p.z0, g.nx, g.ny, g.nz, g.gs, k, k.seed);
 }
 
+// Three steps of a small box in one launch.  A block computes the first step
+// of 8 x 8 x 8 cells from the state into LDS, the second of the 6 x 6 x 6
+// inside them from LDS, the third of its own 4 x 4 x 4 from LDS into the other
+// state: the same cell update, over a window of LDS whose rows are 8 cells.
+// A small box leaves most of the chip idle and a launch is a chain of
+// start, loads that miss, arithmetic and stores; the cells computed several
+// times cost less than two more such chains.  Three steps change states once,
+// as one does, so which state is current stays the parity of the steps.
+// Bound by three updates' latency on one or two waves a SIMD.  Us a step, one
+// step a launch -> three: 16^3 FP64 4.0 -> 2.8, FP32 3.75 -> 2.16, FP16 3.97 ->
+// 2.22, FP32 D3Q15 4.7 -> 2.9; 32^3 FP32 4.2 -> 3.5.
+constexpr int kTripleTile = 4, kTripleEdge = 8, kTripleCells = 512;
+
+template <typename R, typename S, int QT, bool HG>
+__global__ void __launch_bounds__(kTripleCells)
+k_step3(const S* __restrict__ in, S* __restrict__ out, Geom g, KCoef<R> k) {
+    __shared__ S lds[(15 + QT) * kTripleCells];
+    const int t = threadIdx.x, lx = t & 7, ly = (t >> 3) & 7, lz = t >> 6;
+    const int X0 = (int)blockIdx.x * kTripleTile - 2, Y0 = (int)blockIdx.y * kTripleTile - 2,
+              Z0 = (int)blockIdx.z * kTripleTile - 2;
+    const int x = X0 + lx, y = Y0 + ly, z = Z0 + lz;
+    const bool inside = x >= 0 && x < g.nx && y >= 0 && y < g.ny && z >= 0 && z < g.nz;
+    const uint32_t cell = ((uint32_t)z * (uint32_t)g.ny + (uint32_t)y) * (uint32_t)g.nx + (uint32_t)x;
+    // whether the cell is at least m cells inside the block's 8 x 8 x 8
+    auto within = [&](int m) __attribute__((always_inline)) {
+        return inside && lx >= m && lx < 8 - m && ly >= m && ly < 8 - m && lz >= m && lz < 8 - m;
+    };
+    // the states' window (as update_cell's: rows from the block's first on)
+    // and that of LDS: own cell, walls where the box has them
+    const idx::Window w = idx::window_of(Z0 < 0 ? 0 : Z0, Y0 < 0 ? 0 : Y0, g.nx, g.ny, g.nz, g.gs,
+                                         15 + QT, (int)sizeof(S));
+    const idx::CellAt c = idx::cell_at(w, x, y, z, g.nx, g.ny, g.nz);
+    idx::Window wl = {};
+    wl.nx = wl.ny = kTripleEdge;
+    wl.gs = 6;
+    wl.gmask = 63;
+    wl.run = kTripleCells;
+    idx::CellAt cl = c;
+    cl.x = lx;
+    cl.y = ly;
+    cl.z = lz;
+    cl.r = (uint32_t)(t >> 3);
+    cl.own = (uint32_t)t;
+    auto load = [&](uint32_t i) __attribute__((always_inline)) { return (R)lds[i]; };
+    auto keep = [&](uint32_t i, R v) __attribute__((always_inline)) { lds[i] = (S)v; };
+    R d[15], gq[QT];
+    if (inside) {
+        const __amdgpu_buffer_rsrc_t ri = pop_rsrc(in + (size_t)w.g0 * w.glen, w.bytes);
+        gather_collide<R, QT, HG>(w, c, [&](uint32_t i) __attribute__((always_inline)) {
+            return Buf<S>::template ld<R, kKeep>(ri, i); }, k, d, gq);
+        put_cell<R, S, QT>(wl, cl, keep, k, k.seed, cell, d, gq);
+    }
+    __syncthreads();
+    if (within(1)) gather_collide<R, QT, HG>(wl, cl, load, k, d, gq);
+    __syncthreads();
+    if (within(1)) put_cell<R, S, QT>(wl, cl, keep, k, k.seed + 1, cell, d, gq);
+    __syncthreads();
+    if (within(2)) {
+        const __amdgpu_buffer_rsrc_t ro = pop_rsrc(out + (size_t)w.g0 * w.glen, w.bytes);
+        gather_collide<R, QT, HG>(wl, cl, load, k, d, gq);
+        put_cell<R, S, QT>(w, c, [&](uint32_t i, R v) __attribute__((always_inline)) {
+            Buf<S>::template st<kKeep>(ro, i, v); }, k, k.seed + 2, cell, d, gq);
+    }
+}
+
+template <typename R, typename S, int QT, bool HG>
+hipError_t step3_impl(const Geom& g, StateBuf in, StateBuf out, const Coefs& c, hipStream_t s) {
+    const KCoef<R> k = make_kcoef<R>(c, QT);
+    auto tiles = [](int n) { return (unsigned)((n + kTripleTile - 1) / kTripleTile); };
+    hipLaunchKernelGGL((k_step3<R, S, QT, HG>), dim3(tiles(g.nx), tiles(g.ny), tiles(g.nz)),
+                       dim3(kTripleCells), 0, s, (const S*)in.F, (S*)out.F, g, k);
+    return hipGetLastError();
+}
+
 template <typename R, typename S, int QT, bool HG>
 hipError_t step_impl(const Geom& g, StateBuf in, StateBuf out, const Coefs& c, hipStream_t s) {
     const KCoef<R> k = make_kcoef<R>(c, QT);
@@ -104,6 +178,25 @@ hipError_t launch_step(Prec p, int qt, bool general, const Geom& g, StateBuf in,
         LBM_DISPATCH_PQ(p, qt, return (step_impl<R, S, Q, true>(g, in, out, c, s)));
     } else {
         LBM_DISPATCH_PQ(p, qt, return (step_impl<R, S, Q, false>(g, in, out, c, s)));
+    }
+}
+
+// While every block of k_step3 runs at once, one a compute unit (256) in FP64,
+// whose 90-123 KB of LDS leave no room for a second, two in FP32 and FP16.  Us
+// a step, one a launch / three: FP64 24^3 (216 blocks) 4.09 / 3.51, D3Q15 5.04 /
+// 4.42, 28^3 (343) 4.36 / 5.75; FP32 32^3 (512) 4.19 / 3.50, D3Q15 4.88 / 4.76,
+// 40^3 (1000) 4.53 / 5.52; FP16 32^3 4.07 / 3.17, 40^3 4.24 / 4.66.
+bool steps_in_threes(Prec p, const Geom& g) {
+    auto tiles = [](int n) { return (int64_t)((n + kTripleTile - 1) / kTripleTile); };
+    return tiles(g.nx) * tiles(g.ny) * tiles(g.nz) <= (p == Prec::FP64 ? 256 : 512);
+}
+
+hipError_t launch_step3(Prec p, int qt, bool general, const Geom& g, StateBuf in, StateBuf out,
+                        const Coefs& c, hipStream_t s) {
+    if (general) {
+        LBM_DISPATCH_PQ(p, qt, return (step3_impl<R, S, Q, true>(g, in, out, c, s)));
+    } else {
+        LBM_DISPATCH_PQ(p, qt, return (step3_impl<R, S, Q, false>(g, in, out, c, s)));
     }
 }
 

@@ -215,25 +215,13 @@ KCoef<R> make_kcoef(const Coefs& c, int qt) {
 // Fused stream-collide update of one cell (shared by the single-cavity and
 // the batched kernels, so both compute bit-identical results)
 // ---------------------------------------------------------------------------
-// (z0, y0): the first row of the block's cells, the same for all of them.
-// seed: the step index keying stochastic rounding (FP16 storage with k.sr).
-// POL: the block's cache policy (Policy).
-template <typename R, typename S, int QT, bool HG, int POL>
-__device__ __forceinline__ void update_cell(const S* __restrict__ in, S* __restrict__ out, int x,
-                                            int y, int z, int y0, int z0, int nxi, int nyi,
-                                            int nzi, int gs, const KCoef<R>& k, uint32_t seed) {
-    constexpr int RQ = 15 + QT;
-    // The block's window starts at the group of row (z0-1, y0-1) and runs to
-    // the end of the state; y0 and z0 are uniform over the block, so the base
-    // is a scalar.  Every offset below is relative to it (lbm_index.hpp).
-    const idx::Window w = idx::window_of(z0, y0, nxi, nyi, nzi, gs, RQ, (int)sizeof(S));
-    const __amdgpu_buffer_rsrc_t ri = pop_rsrc(in + (size_t)w.g0 * w.glen, w.bytes);
-    const __amdgpu_buffer_rsrc_t ro = pop_rsrc(out + (size_t)w.g0 * w.glen, w.bytes);
-    const idx::CellAt c = idx::cell_at(w, x, y, z, nxi, nyi, nzi);
-    R d[15];
+// Gather and collision of the cell c: ld(offset) loads a value of the window
+// w; d and gq get the post-collision populations.
+template <typename R, int QT, bool HG, typename Ld>
+__device__ __forceinline__ void gather_collide(const idx::Window& w, const idx::CellAt& c, Ld ld,
+                                               const KCoef<R>& k, R (&d)[15], R (&gq)[QT]) {
 #pragma unroll
-    for (int a = 0; a < 15; ++a) d[a] = Buf<S>::template ld<R, POL>(ri, idx::flow_load(w, c, a));
-    R gq[QT];
+    for (int a = 0; a < 15; ++a) d[a] = ld(idx::flow_load(w, c, a));
     // Scalar gather: anti-bounce-back across the Dirichlet walls (this rule
     // wins on edges), bounce-back or -- with specular reflection, D3Q15
     // only (on D3Q7 the two coincide) -- the mirrored population across the
@@ -243,7 +231,7 @@ __device__ __forceinline__ void update_cell(const S* __restrict__ in, S* __restr
 #pragma unroll
         for (int a = 0; a < QT; ++a) {
             const idx::ScalarLoad l = idx::scalar_load<QT, SPEC>(w, c, a);
-            R v = Buf<S>::template ld<R, POL>(ri, l.off);
+            R v = ld(l.off);
             if (l.dirichlet) {
                 const int ex = QT == 7 ? EX7[a] : EX15[a];
                 const int ey = QT == 7 ? EY7[a] : EY15[a];
@@ -271,13 +259,20 @@ __device__ __forceinline__ void update_cell(const S* __restrict__ in, S* __restr
         collide_thermal7<R, HG>(gq, ux, uy, uz, k.t);
     else
         collide_thermal15<R, HG>(gq, ux, uy, uz, k.t);
+}
 
+// Stores the cell's populations with st(offset, value); cell: its number in
+// the box, seed: the step index (both key stochastic rounding, FP16 storage
+// with k.sr).
+template <typename R, typename S, int QT, typename St>
+__device__ __forceinline__ void put_cell(const idx::Window& w, const idx::CellAt& c, St st,
+                                         const KCoef<R>& k, uint32_t seed, uint32_t cell,
+                                         const R (&d)[15], const R (&gq)[QT]) {
     if constexpr (std::is_same<S, _Float16>::value) {
         if (k.sr) {
             // The cell's random stream: a hash of (step, cell) seeds a
             // xorshift32 generator (shifts 13, 17, 5; state never 0); each
             // 32-bit word gives the 16 random bits of two stores.
-            const uint32_t cell = ((uint32_t)z * w.ny + (uint32_t)y) * w.nx + (uint32_t)x;
             uint32_t xs = mix32(seed * 0x9e3779b9u ^ cell);
             xs = xs ? xs : 0x9e3779b9u;
             uint32_t rnd[(15 + QT + 1) / 2];
@@ -291,19 +286,40 @@ __device__ __forceinline__ void update_cell(const S* __restrict__ in, S* __restr
             // value 2j takes the high half of word j, value 2j + 1 the low half
 #pragma unroll
             for (int a = 0; a < 15; ++a)
-                Buf<S>::template st<POL>(ro, idx::store_at(w, c, a),
-                           (float)half_stochastic(d[a], rnd[a >> 1] << (16 * (a & 1))));
+                st(idx::store_at(w, c, a), (float)half_stochastic(d[a], rnd[a >> 1] << (16 * (a & 1))));
 #pragma unroll
             for (int a = 0; a < QT; ++a)
-                Buf<S>::template st<POL>(ro, idx::store_at(w, c, 15 + a),
-                           (float)half_stochastic(gq[a], rnd[(a + 15) >> 1] << (16 * ((a + 15) & 1))));
+                st(idx::store_at(w, c, 15 + a),
+                   (float)half_stochastic(gq[a], rnd[(a + 15) >> 1] << (16 * ((a + 15) & 1))));
             return;
         }
     }
 #pragma unroll
-    for (int a = 0; a < 15; ++a) Buf<S>::template st<POL>(ro, idx::store_at(w, c, a), d[a]);
+    for (int a = 0; a < 15; ++a) st(idx::store_at(w, c, a), d[a]);
 #pragma unroll
-    for (int a = 0; a < QT; ++a) Buf<S>::template st<POL>(ro, idx::store_at(w, c, 15 + a), gq[a]);
+    for (int a = 0; a < QT; ++a) st(idx::store_at(w, c, 15 + a), gq[a]);
+}
+
+// (z0, y0): the first row of the block's cells, the same for all of them.
+// seed: the step index keying stochastic rounding (FP16 storage with k.sr).
+// POL: the block's cache policy (Policy).
+template <typename R, typename S, int QT, bool HG, int POL>
+__device__ __forceinline__ void update_cell(const S* __restrict__ in, S* __restrict__ out, int x,
+                                            int y, int z, int y0, int z0, int nxi, int nyi,
+                                            int nzi, int gs, const KCoef<R>& k, uint32_t seed) {
+    // The block's window starts at the group of row (z0-1, y0-1) and runs to
+    // the end of the state; y0 and z0 are uniform over the block, so the base
+    // is a scalar.  Every offset below is relative to it (lbm_index.hpp).
+    const idx::Window w = idx::window_of(z0, y0, nxi, nyi, nzi, gs, 15 + QT, (int)sizeof(S));
+    const __amdgpu_buffer_rsrc_t ri = pop_rsrc(in + (size_t)w.g0 * w.glen, w.bytes);
+    const __amdgpu_buffer_rsrc_t ro = pop_rsrc(out + (size_t)w.g0 * w.glen, w.bytes);
+    const idx::CellAt c = idx::cell_at(w, x, y, z, nxi, nyi, nzi);
+    R d[15], gq[QT];
+    gather_collide<R, QT, HG>(w, c, [&](uint32_t i) __attribute__((always_inline)) {
+        return Buf<S>::template ld<R, POL>(ri, i); }, k, d, gq);
+    put_cell<R, S, QT>(w, c, [&](uint32_t i, R v) __attribute__((always_inline)) {
+        Buf<S>::template st<POL>(ro, i, v); }, k, seed,
+        ((uint32_t)z * w.ny + (uint32_t)y) * w.nx + (uint32_t)x, d, gq);
 }
 
 // update_cell under the block's cache policy; b: the block's number,
