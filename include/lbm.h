@@ -345,10 +345,10 @@ lbm_status lbm_copy_probe(void* dst, const void* src, size_t bytes, void* stream
 /* ------------------------------------------------------------------------
  * Batched form: many independent cavities (any sizes and parameters, one
  * precision, scalar lattice and rate set) advanced together.  One step is
- * one persistent launch over a device list of tiles (a tile is a few whole
- * x-rows of one z-plane of one cavity); each member is updated exactly as
- * by lbm_step.  Steps are replayed from a captured hipGraph.  Converged
- * members leave the tile list (compacted on the device), so the graph is
+ * one persistent launch over a device list of pieces (a block's worth of
+ * consecutive cells of one cavity); each member is updated exactly as by
+ * lbm_step.  Steps are replayed from a captured hipGraph.  Converged
+ * members leave the list (compacted on the device), so the graph is
  * never re-captured for that.
  * ---------------------------------------------------------------------- */
 
@@ -382,7 +382,7 @@ lbm_status lbm_batch_step(lbm_batch* b, int64_t nsteps);
 lbm_status lbm_batch_residuals(lbm_batch* b, double* max_dT, int32_t* status);
 
 /* Set which members take part in later steps (host array of n, 0/1).
- * Rebuilds the device tile list; asynchronous. */
+ * Rebuilds the device list of pieces; asynchronous. */
 lbm_status lbm_batch_set_active(lbm_batch* b, const int32_t* active);
 
 /* Run every active member to steady state with the rule of
@@ -398,8 +398,8 @@ lbm_status lbm_batch_run_to_steady(lbm_batch* b, double tol, int64_t check_every
 
 /* Launch shape: threads per block (a multiple of 64, >= the largest nx, at
  * most 1024), blocks per compute unit (1..32: a persistent grid whose blocks
- * walk the tile list; 0: one block per tile of the whole batch, blocks past
- * the active tiles returning at once), steps per captured graph (even, 0
+ * walk the list; 0: one block per tile, threads / nx whole x-rows of one plane,
+ * of the whole batch, blocks past the active pieces returning at once), steps per captured graph (even, 0
  * disables graphs). */
 lbm_status lbm_batch_set_launch(lbm_batch* b, int32_t threads, int32_t blocks_per_cu,
                                 int32_t graph_steps);

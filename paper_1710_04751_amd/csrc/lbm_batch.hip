@@ -305,7 +305,7 @@ void fill_kcoef(const lbm_handle* h, KCoef<R>* k) {
 }
 
 // Rebuild the host table for the current launch shape and upload it, then
-// rebuild the device tile list.
+// rebuild the device list of pieces.
 lbm_status upload_table(lbm_batch* b) {
     b->tiles_all = 0;
     uint64_t active_bytes = 0;  // both states of the members that step
@@ -366,9 +366,10 @@ lbm_status upload_table(lbm_batch* b) {
         }                                                                              \
     } while (0)
 
-// Grid of the batched kernels: bpc blocks per compute unit walking the tile
-// list, or (bpc = 0) one block per tile of the whole batch; blocks beyond the
-// active tiles return at once, so the grid stays valid as members retire.
+// Grid of the batched kernels: bpc blocks per compute unit walking the list of
+// pieces, or (bpc = 0) one block per tile of the whole batch (never fewer than
+// the pieces); blocks beyond the active pieces return at once, so the grid
+// stays valid as members retire.
 unsigned batch_grid(const lbm_batch* b) {
     return (unsigned)(b->bpc > 0 ? (int64_t)b->cu_count * b->bpc : std::max<int64_t>(1, b->tiles_all));
 }

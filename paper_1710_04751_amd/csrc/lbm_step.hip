@@ -1,7 +1,8 @@
 // gfx950 kernels of the cascaded double-distribution lattice Boltzmann
 // update (arXiv:1710.04751) and the observables around it.
 //
-// Step kernel: one thread per cell, one pass per time step (A -> B).
+// Step kernel: one thread per cell, one pass per time step (A -> B); boxes of
+// few cells take three steps a pass (k_step3).
 //   * pull streaming (eq. 2b, 13b): population a of cell x is read from
 //     x - e_a in the previous post-collision state; each value is read once
 //     and written once, so the kernel moves (15 + q) values in and out per
@@ -16,7 +17,8 @@
 //     which take precedence on edges; bounce-back across the adiabatic ones);
 //   * T = sum g (eq. 25), F = g beta (T - T0) z (Boussinesq), then the flow
 //     collision and the scalar collision with the same step's velocity, all
-//     in registers, then non-temporal stores of the post-collision state;
+//     in registers, then the stores of the post-collision state, under the
+//     block's cache policy (Policy);
 //   * blocks are numbered so that each of the 8 XCDs works on a contiguous
 //     range of tiles: neighbouring tiles of a row share the partly-read
 //     cache lines of the x-shifted populations in the same L2.

@@ -1,6 +1,6 @@
 // Shared device code of the fused step: lattice tables, range-checked
 // population access and the per-cell stream-collide update.  Included by
-// the single-cavity kernels (lbm_kernels.hip) and the batched kernels
+// the single-cavity kernels (lbm_step.hip) and the batched kernels
 // (lbm_batch.hip).
 #pragma once
 

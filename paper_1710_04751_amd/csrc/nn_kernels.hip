@@ -2332,11 +2332,10 @@ constexpr int64_t kPartFloats = 8 << 20;
 constexpr int64_t kPartBlocks = 1024;
 
 // Blocks of k_wgrad_tr<rs> (rs 1 or 2) for one generation on the device:
-// the compute units times the blocks each holds at once, at most 2 (asked
-// once per process; 512 if the runtime cannot say).  With 48-64 registers 3-4
-// fit, but fewer blocks each walking more bricks were faster (64^3, batch 8:
-// 16 -> 16 channels 70 -> 53 us, 32 -> 48 channels 77 -> 53 us): neighbouring
-// bricks of a range share halo cells and output rows in L2.
+// the compute units times the blocks each holds at once (one: the ring of
+// halo planes takes 140 KB of LDS; at most 2 if that ever shrinks, since fewer
+// blocks each walking more bricks share halo cells and output rows in L2).
+// Asked once per process; 512 if the runtime cannot say.
 int64_t wgrad_tr_resident(int rs) {
     static int64_t cached[2] = {0, 0};
     int64_t& c = cached[rs == 2];
