@@ -552,7 +552,8 @@ __device__ __forceinline__ void copies_landed() {
 // Four more waves make the copies (two the halo, two the output gradient): the
 // scalar work of their addresses, done by every wave, had cost more issue slots
 // than the products (174 scalar instructions a wave and brick beside 18
-// products: 51 us for a 16-channel layer at 64^3).
+// products: 51 us for a 16-channel layer at 64^3).  They have the higher wave
+// priority (16 channels at 64^3 45 -> 40 us, 48 -> 16 122 -> 106).
 //
 // Lane groups q and q ^ 1 of a k step take neighbouring rows, and the LDS rows
 // are padded so that their reads fall in opposite halves of the banks (a row of
@@ -566,10 +567,10 @@ __device__ __forceinline__ void copies_landed() {
 //
 // Measured, 8 samples, before (nine waves, one brick copied ahead by all of
 // them, four blocks a compute unit) -> now: 16 -> 16 channels at 64^3
-// 55 -> 45 us (134 MB: 3.0 TB/s; copies alone 31, products alone 31), 48 -> 16
-// at 64^3 155 -> 123, 32 -> 32 at 32^3 25 -> 22, 96 -> 32 at 32^3 58 -> 46,
-// 192 -> 64 at 16^3 52 -> 30; slower: 16 -> 32
-// at 32^3 and 32 -> 64 at 16^3 (few bricks a block), 14.6 -> 15.9.
+// 55 -> 40 us (134 MB: 3.3 TB/s; copies alone 31, products alone 31), 48 -> 16
+// at 64^3 155 -> 106, 32 -> 32 at 32^3 25 -> 21, 96 -> 32 at 32^3 58 -> 45,
+// 192 -> 64 at 16^3 52 -> 29; slower: 16 -> 32 at 32^3 and 32 -> 64 at 16^3
+// (few bricks a block), 14.6 -> 15.5.
 constexpr int kWtWaves = 9;                    // k_wgrad_small
 constexpr int kWgWaves = 16;                   // k_wgrad_tr: 12 for the products, 4 for the copies
 constexpr int kWtHaloRow = 20;                 // voxels per LDS halo row (18 + 2 padding)
@@ -780,6 +781,7 @@ __global__ void __launch_bounds__(64 * kWgWaves) k_wgrad_tr(WgradArgs a, int64_t
     // products start.
     auto follows = [&](int b) { return b > b0 && (b & (nbz - 1)) != 0; };
     if (copier >= 0) {
+        __builtin_amdgcn_s_setprio(3);  // the next bricks' copies go out before the products' work
         int next = b0, end = 0, wslot = 0, wbuf = 0;  // next brick, ring position (counting up), slot, buffer
         int base = 0;                                 // position of the current brick's first plane
         for (int b = b0; b < b1; ++b) {
