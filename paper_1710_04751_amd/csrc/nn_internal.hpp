@@ -6,28 +6,11 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "nn_plan.hpp"
+
 namespace lbmnn {
 
 constexpr int kMaxBatch = 64;  // samples per call
-
-// One convolution over n samples on a cubic grid of edge 2^lg.  The input
-// is the channel concatenation of x1 (c1s stored channels on this grid, of
-// which c1 are real; the rest hold zeros) and, when c2 > 0, x2 (c2 channels
-// on the grid of edge 2^(lg-1), read through nearest-neighbour upsampling).
-struct ConvGeom {
-    int32_t n, lg;
-    int32_t taps;       // 27 (3x3x3) or 1 (1x1x1)
-    int32_t c1, c1s, c2;
-    int32_t cin;        // c1s + c2: stored input channels, K per tap
-    int32_t K, kpad;    // taps * cin, rounded up to 32
-    int32_t cout;       // real output channels
-    int32_t coutp;      // rows of the packed weight: cout rounded up to 16
-    int32_t ys;         // stored channels of the output and its gradient: cout rounded up to 8
-    int32_t kpad_t;     // columns of the transposed weight: taps * ys rounded up to 32
-    int32_t cinp;       // rows of the transposed weight: cin rounded up to 16
-};
-
-ConvGeom make_geom(int n, int lg, int taps, int c1, int c2, int cout);
 
 // Master weights of layer l at theta + woff[l], w[co][tap][ci] (ci over the
 // c1 + c2 real channels) -> packed BF16 rows wp[l][coutp][kpad] (k = tap *
@@ -74,12 +57,13 @@ hipError_t conv_backward_concat(const ConvGeom& g, const __bf16* dy, const __bf1
 // Weight and bias gradients, written into the master layout:
 // dw[co][tap][ci] = sum_v dpre[v][co] x(v + tap)[ci], db[co] = sum_v
 // dpre[v][co] (dpre = dy, masked by y > 0 when relu).  Blocks sum ranges of
-// voxels into scratch (wgrad_scratch_floats(g) floats, device), a second
-// kernel adds the ranges in a fixed order.
-int64_t wgrad_scratch_floats(const ConvGeom& g);
+// voxels into scratch (scratch_floats device floats, refused when they are
+// fewer than the plan needs: wgrad_scratch_floats(g, wgrad_blocks()) serve any
+// call of up to g.n samples), a second kernel adds the ranges in a fixed order.
+WgradBlocks wgrad_blocks();  // of the current device
 hipError_t conv_backward_weight(const ConvGeom& g, const __bf16* x1, const __bf16* x2,
                                 const __bf16* dy, const __bf16* y, int relu, float* dw,
-                                float* db, float* scratch, hipStream_t s);
+                                float* db, float* scratch, int64_t scratch_floats, hipStream_t s);
 
 // Average pooling of 2x2x2 blocks: x on grid 2^lg, y on 2^(lg-1), c channels.
 hipError_t pool_forward(int n, int lg, int c, const __bf16* x, __bf16* y, hipStream_t s);

@@ -37,9 +37,6 @@ typedef __attribute__((address_space(3))) void* lds_void_ptr;  // LDS destinatio
 
 namespace {
 
-inline int ceil_div(int64_t a, int64_t b) { return (int)((a + b - 1) / b); }
-inline int round_up(int a, int b) { return (a + b - 1) / b * b; }
-
 // Per-sample scalars passed by value (at most kMaxBatch samples).
 struct SampleFloats {
     float v[kMaxBatch];
@@ -420,7 +417,6 @@ __global__ void __launch_bounds__(256) k_wgrad(WgradArgs a) {
 // consecutive rows, fewer in the last), in order.  One thread per (slice,
 // column), so the loads of many rows are in flight at once; the weight
 // slices go to out, the bias slices after them.
-constexpr int kRowSlice = 16;
 __global__ void k_sum_row_slices(const float* __restrict__ in, int64_t boff, int64_t rows,
                                  int64_t ww, int64_t bw, float* __restrict__ out) {
     const int64_t slices = (rows + kRowSlice - 1) / kRowSlice;
@@ -2147,25 +2143,6 @@ hipError_t launch_conv(const ConvArgs& a, int coutp, float* scratch, int64_t scr
 
 }  // namespace
 
-ConvGeom make_geom(int n, int lg, int taps, int c1, int c2, int cout) {
-    ConvGeom g;
-    g.n = n;
-    g.lg = lg;
-    g.taps = taps;
-    g.c1 = c1;
-    g.c1s = round_up(c1, 8);
-    g.c2 = c2;
-    g.cin = g.c1s + c2;
-    g.K = taps * g.cin;
-    g.kpad = round_up(g.K, 32);
-    g.cout = cout;
-    g.coutp = round_up(cout, 16);
-    g.ys = round_up(cout, 8);
-    g.kpad_t = round_up(taps * g.ys, 32);
-    g.cinp = round_up(g.cin, 16);
-    return g;
-}
-
 hipError_t pack_weights(int layers, const ConvGeom* g, const float* theta, const int64_t* woff,
                         __bf16* const* wp, __bf16* const* wt, hipStream_t s) {
     if (layers < 1 || layers > kMaxPackLayers) return hipErrorInvalidValue;
@@ -2302,37 +2279,6 @@ int64_t conv_scratch_floats(const ConvGeom& g) {
 
 namespace {
 
-// Launch plan of the weight gradient: a brick kernel (grids of at least 16
-// cells, 27 taps, 16/32 output channels with >= 8 input channels, 64 with
-// >= 16) or the tiled kernel, its grid, and the floats of partial sums it
-// writes.
-struct WgradPlan {
-    bool small;          // 8-cell grids: k_wgrad_small, one block per (group, sample, 32 channels)
-    bool brick;
-    int rs, cs;
-    int chunks, groups;  // brick: channel groups x brick ranges
-    int64_t per;         // brick: bricks per range
-    int kt, ct, nz;      // tiled: column tiles, row tiles, voxel chunks
-    int64_t vchunk;
-    int64_t part_floats, bias_off;  // partial sums of every block
-    int64_t rows, wwidth, bwidth;   // rows of partials, weight / bias floats per row
-    int64_t scratch_floats;         // partials + the first reduction pass
-    bool slices;                    // whether the first reduction pass runs
-};
-
-// Scratch of the first reduction pass, after the partials: the weight rows
-// and the bias rows summed over slices of kRowSlice rows.
-void finish_plan(WgradPlan* p) {
-    p->slices = p->rows > 2 * kRowSlice;
-    const int64_t sl = p->slices ? (p->rows + kRowSlice - 1) / kRowSlice : 0;
-    p->scratch_floats = p->part_floats + sl * (p->wwidth + p->bwidth);
-}
-
-// Partial sums kept to about 32 MB and 1024 blocks: enough blocks to fill
-// the chip, and a second pass that reads far less than the layer's inputs.
-constexpr int64_t kPartFloats = 8 << 20;
-constexpr int64_t kPartBlocks = 1024;
-
 // Blocks of k_wgrad_tr<rs> (rs 1 or 2) for one generation on the device:
 // the compute units times the blocks each holds at once (one: the ring of
 // halo planes takes 140 KB of LDS; at most 2 if that ever shrinks, since fewer
@@ -2351,75 +2297,6 @@ int64_t wgrad_tr_resident(int rs) {
         c = e == hipSuccess && cus > 0 && per > 0 ? (int64_t)cus * std::min(per, 2) : 512;
     }
     return c;
-}
-
-// (The brick kernel reads the output gradient unmasked: relu != 0 takes the
-// tiled kernel.)
-WgradPlan wgrad_plan(const ConvGeom& g, int relu) {
-    WgradPlan p = {};
-    const int64_t M = (int64_t)g.n << (3 * g.lg);
-    // (8 input channels, the network's first layer, takes a channel group
-    // of 16 whose upper half loads zeros; only k_wgrad_tr is checked for
-    // that, so 64 output channels need 16.)
-    p.small = !relu && g.lg == 3 && g.taps == 27 && g.c2 == 0 && g.cin % 16 == 0 &&
-              g.coutp % 32 == 0;
-    if (p.small) {
-        p.rs = g.coutp / 16;
-        p.chunks = g.cin / 16;
-        p.groups = g.n;  // partial rows: one per sample
-        const int64_t blk_floats = (int64_t)27 * g.coutp * 16;
-        p.bias_off = (int64_t)g.n * p.chunks * blk_floats;
-        p.part_floats = p.bias_off + (int64_t)g.n * g.coutp;
-        p.rows = g.n;
-        p.wwidth = (int64_t)p.chunks * blk_floats;
-        p.bwidth = g.coutp;
-        p.slices = false;
-        p.scratch_floats = p.part_floats;
-        return p;
-    }
-    p.brick = !relu && g.lg >= 4 && g.taps == 27 &&
-              (g.c2 == 0 || g.c1s % 16 == 0) &&
-              ((g.cin >= 8 && (g.coutp == 16 || g.coutp == 32)) || (g.cin >= 16 && g.coutp == 64));
-    if (p.brick) {
-        p.rs = g.coutp / 16;
-        p.chunks = ceil_div(g.cin, 16);
-        const int64_t nbricks = M / 256;  // 16 x 4 x 4 voxels
-        const int64_t blk_floats = (int64_t)27 * g.coutp * 16;
-        // one generation of resident blocks (64 output channels: two a range)
-        const int64_t blocks = p.rs == 4 ? wgrad_tr_resident(2) / 2 : wgrad_tr_resident(p.rs);
-        const int64_t cap = std::max<int64_t>(
-            1, std::min<int64_t>(blocks, kPartFloats / blk_floats) / p.chunks);
-        const int64_t groups = std::max<int64_t>(1, std::min<int64_t>(nbricks, cap));
-        p.per = (nbricks + groups - 1) / groups;
-        p.groups = ceil_div(nbricks, p.per);
-        p.bias_off = (int64_t)p.groups * p.chunks * blk_floats;
-        p.part_floats = p.bias_off + (int64_t)p.groups * g.coutp;
-        p.rows = p.groups;
-        p.wwidth = (int64_t)p.chunks * blk_floats;
-        p.bwidth = g.coutp;
-        p.slices = false;  // one pass (k_brick_partials_sum)
-        p.scratch_floats = p.part_floats;
-        return p;
-    }
-    p.rs = g.coutp >= 64 ? 4 : g.coutp >= 32 ? 2 : 1;
-    p.cs = 8 / p.rs;
-    p.ct = ceil_div(g.coutp, 16 * p.rs);
-    p.kt = ceil_div(g.K, 16 * p.cs);
-    const int64_t steps = (M + 31) / 32;
-    const int64_t blk_floats = (int64_t)p.rs * 16 * p.cs * 16;
-    const int64_t tiles = (int64_t)p.kt * p.ct;
-    const int64_t cap = std::max<int64_t>(
-        1, std::min<int64_t>(2 * kPartBlocks, kPartFloats / blk_floats) / tiles);
-    const int64_t chunks = std::max<int64_t>(1, std::min<int64_t>(steps, cap));
-    p.vchunk = (steps + chunks - 1) / chunks * 32;
-    p.nz = ceil_div(M, p.vchunk);
-    p.bias_off = (int64_t)p.nz * tiles * blk_floats;
-    p.part_floats = p.bias_off + (int64_t)p.nz * p.ct * p.rs * 16;
-    p.rows = p.nz;
-    p.wwidth = tiles * blk_floats;
-    p.bwidth = (int64_t)p.ct * p.rs * 16;
-    finish_plan(&p);
-    return p;
 }
 
 // First reduction pass over the partials of plan p, when they have more
@@ -2445,9 +2322,7 @@ hipError_t sum_slices(const WgradPlan& p, const WgradArgs& a, WgradArgs* b, int6
 
 }  // namespace
 
-int64_t wgrad_scratch_floats(const ConvGeom& g) {
-    return std::max(wgrad_plan(g, 0).scratch_floats, wgrad_plan(g, 1).scratch_floats);
-}
+WgradBlocks wgrad_blocks() { return {wgrad_tr_resident(1), wgrad_tr_resident(2)}; }
 
 // One pass over a brick or 8-cell partial table (rows x W weight entries,
 // then the bias rows).
@@ -2471,10 +2346,12 @@ hipError_t launch_partials_sum(const WgradArgs& a, int chunks, int rows, int rs,
 
 hipError_t conv_backward_weight(const ConvGeom& g, const __bf16* x1, const __bf16* x2,
                                 const __bf16* dy, const __bf16* y, int relu, float* dw,
-                                float* db, float* scratch, hipStream_t s) {
+                                float* db, float* scratch, int64_t scratch_floats,
+                                hipStream_t s) {
     if (!x1 || !dy || !dw || !db || !scratch || (relu && !y) || (g.c2 > 0 && (!x2 || g.lg < 1)))
         return hipErrorInvalidValue;
-    const WgradPlan p = wgrad_plan(g, relu);
+    const WgradPlan p = wgrad_plan(g, relu, wgrad_blocks());
+    if (p.scratch_floats > scratch_floats) return hipErrorInvalidValue;
     WgradArgs a;
     a.x1 = x1;
     a.x2 = x2;

@@ -20,25 +20,7 @@ namespace {
 constexpr size_t kAlign = 256;
 size_t align_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
 
-// Layer table: input x1 (c1 channels on the layer's level), optional x2
-// (c2 channels one level coarser, upsampled), output channels, kernel taps,
-// level (0 = G, 1 = G/2, ...).
-struct LayerDef {
-    const char* name;
-    int c1, c2, cout, taps, level, relu;
-};
-constexpr int kLayers = 16;
 static_assert(kLayers <= kMaxPackLayers, "one packing launch covers every layer");
-constexpr LayerDef kDefs[kLayers] = {
-    {"enc1a", 4, 0, 16, 27, 0, 1},    {"enc1b", 16, 0, 16, 27, 0, 1},
-    {"enc2a", 16, 0, 32, 27, 1, 1},   {"enc2b", 32, 0, 32, 27, 1, 1},
-    {"enc3a", 32, 0, 64, 27, 2, 1},   {"enc3b", 64, 0, 64, 27, 2, 1},
-    {"bota", 64, 0, 128, 27, 3, 1},   {"botb", 128, 0, 128, 27, 3, 1},
-    {"botc", 128, 0, 128, 27, 3, 1},  {"dec3a", 64, 128, 64, 27, 2, 1},
-    {"dec3b", 64, 0, 64, 27, 2, 1},   {"dec2a", 32, 64, 32, 27, 1, 1},
-    {"dec2b", 32, 0, 32, 27, 1, 1},   {"dec1a", 16, 32, 16, 27, 0, 1},
-    {"dec1b", 16, 0, 16, 27, 0, 1},   {"head", 16, 0, 4, 1, 0, 0},
-};
 
 int64_t layer_params(const LayerDef& d) {
     return (int64_t)d.cout * d.taps * (d.c1 + d.c2) + d.cout;
@@ -141,12 +123,13 @@ Layout make_layout(const lbm_nn_config& c) {
     }
     L.partial = take(((c0 + 255) / 256) * 8);
     L.loss = take(64);
+    const WgradBlocks resident = wgrad_blocks();
     int64_t wpart = 0;
     for (int l = 0; l < kLayers; ++l) {
         const LayerDef& d = kDefs[l];
         const ConvGeom g = make_geom(B, lg0 - d.level, d.taps, d.c1, d.c2, d.cout);
         wpart = std::max(wpart, l == kLayers - 1 ? head_scratch_floats(g)
-                                                 : std::max(wgrad_scratch_floats(g),
+                                                 : std::max(wgrad_scratch_floats(g, resident),
                                                             conv_scratch_floats(g)));
     }
     L.wpart = take((size_t)wpart * 4);
@@ -238,7 +221,7 @@ lbm_status backward(lbm_nn* nn, int n) {
         float* dw = grad + nn->off[l];
         float* db = dw + (int64_t)d.cout * d.taps * (d.c1 + d.c2);
         NN_TRY(conv_backward_weight(g, x1, x2, dact(l), nullptr, 0, dw, db,
-                                    nn->at<float>(L.wpart), s),
+                                    nn->at<float>(L.wpart), L.wpart_floats, s),
                "weight grad");
         if (l == 0) break;
         // (the weight gradient above has finished with wpart: same stream)
