@@ -58,12 +58,15 @@ hipError_t conv_backward_concat(const ConvGeom& g, const __bf16* dy, const __bf1
 // dw[co][tap][ci] = sum_v dpre[v][co] x(v + tap)[ci], db[co] = sum_v
 // dpre[v][co] (dpre = dy, masked by y > 0 when relu).  Blocks sum ranges of
 // voxels into scratch (scratch_floats device floats, refused when they are
-// fewer than the plan needs: wgrad_scratch_floats(g, wgrad_blocks()) serve any
-// call of up to g.n samples), a second kernel adds the ranges in a fixed order.
+// fewer than the plan needs: wgrad_scratch_floats(g, resident) serve any call
+// of up to g.n samples), a second kernel adds the ranges in a fixed order.
+// resident: what wgrad_blocks() gave when the scratch was sized, so that the
+// plans are the ones it was sized for.
 WgradBlocks wgrad_blocks();  // of the current device
 hipError_t conv_backward_weight(const ConvGeom& g, const __bf16* x1, const __bf16* x2,
                                 const __bf16* dy, const __bf16* y, int relu, float* dw,
-                                float* db, float* scratch, int64_t scratch_floats, hipStream_t s);
+                                float* db, const WgradBlocks& resident, float* scratch,
+                                int64_t scratch_floats, hipStream_t s);
 
 // Average pooling of 2x2x2 blocks: x on grid 2^lg, y on 2^(lg-1), c channels.
 hipError_t pool_forward(int n, int lg, int c, const __bf16* x, __bf16* y, hipStream_t s);

@@ -2279,26 +2279,6 @@ int64_t conv_scratch_floats(const ConvGeom& g) {
 
 namespace {
 
-// Blocks of k_wgrad_tr<rs> (rs 1 or 2) for one generation on the device:
-// the compute units times the blocks each holds at once (one: the ring of
-// halo planes takes 140 KB of LDS; at most 2 if that ever shrinks, since fewer
-// blocks each walking more bricks share halo cells and output rows in L2).
-// Asked once per process; 512 if the runtime cannot say.
-int64_t wgrad_tr_resident(int rs) {
-    static int64_t cached[2] = {0, 0};
-    int64_t& c = cached[rs == 2];
-    if (c == 0) {
-        int dev = 0, cus = 0, per = 0;
-        hipError_t e = hipGetDevice(&dev);
-        if (e == hipSuccess) e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
-        if (e == hipSuccess)
-            e = rs == 2 ? hipOccupancyMaxActiveBlocksPerMultiprocessor(&per, k_wgrad_tr<2>, 64 * kWgWaves, 0)
-                        : hipOccupancyMaxActiveBlocksPerMultiprocessor(&per, k_wgrad_tr<1>, 64 * kWgWaves, 0);
-        c = e == hipSuccess && cus > 0 && per > 0 ? (int64_t)cus * std::min(per, 2) : 512;
-    }
-    return c;
-}
-
 // First reduction pass over the partials of plan p, when they have more
 // than 2 kRowSlice rows (more than the second pass's lane groups read
 // quickly).
@@ -2322,7 +2302,30 @@ hipError_t sum_slices(const WgradPlan& p, const WgradArgs& a, WgradArgs* b, int6
 
 }  // namespace
 
-WgradBlocks wgrad_blocks() { return {wgrad_tr_resident(1), wgrad_tr_resident(2)}; }
+// Blocks of k_wgrad_tr for one generation on the current device: the compute
+// units times the blocks each holds at once (one: the ring of halo planes takes
+// 140 KB of LDS; at most 2 if that ever shrinks, since fewer blocks each walking
+// more bricks share halo cells and output rows in L2).  512 if the runtime
+// cannot say.  Asked once per device; an answer it did not give is not kept.
+WgradBlocks wgrad_blocks() {
+    static std::atomic<int64_t> known[64][2];
+    int dev = 0;
+    if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return {512, 512};
+    int64_t blocks[2];
+    for (int two = 0; two < 2; ++two) {
+        blocks[two] = known[dev][two].load(std::memory_order_relaxed);
+        if (blocks[two] > 0) continue;
+        int cus = 0, per = 0;
+        hipError_t e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
+        if (e == hipSuccess)
+            e = two ? hipOccupancyMaxActiveBlocksPerMultiprocessor(&per, k_wgrad_tr<2>, 64 * kWgWaves, 0)
+                    : hipOccupancyMaxActiveBlocksPerMultiprocessor(&per, k_wgrad_tr<1>, 64 * kWgWaves, 0);
+        if (e != hipSuccess || cus <= 0 || per <= 0) return {512, 512};
+        blocks[two] = (int64_t)cus * std::min(per, 2);
+        known[dev][two].store(blocks[two], std::memory_order_relaxed);
+    }
+    return {blocks[0], blocks[1]};
+}
 
 // One pass over a brick or 8-cell partial table (rows x W weight entries,
 // then the bias rows).
@@ -2346,11 +2349,11 @@ hipError_t launch_partials_sum(const WgradArgs& a, int chunks, int rows, int rs,
 
 hipError_t conv_backward_weight(const ConvGeom& g, const __bf16* x1, const __bf16* x2,
                                 const __bf16* dy, const __bf16* y, int relu, float* dw,
-                                float* db, float* scratch, int64_t scratch_floats,
-                                hipStream_t s) {
+                                float* db, const WgradBlocks& resident, float* scratch,
+                                int64_t scratch_floats, hipStream_t s) {
     if (!x1 || !dy || !dw || !db || !scratch || (relu && !y) || (g.c2 > 0 && (!x2 || g.lg < 1)))
         return hipErrorInvalidValue;
-    const WgradPlan p = wgrad_plan(g, relu, wgrad_blocks());
+    const WgradPlan p = wgrad_plan(g, relu, resident);
     if (p.scratch_floats > scratch_floats) return hipErrorInvalidValue;
     WgradArgs a;
     a.x1 = x1;

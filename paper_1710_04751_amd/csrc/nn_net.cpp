@@ -48,6 +48,7 @@ struct Layout {
     size_t wpart;  // weight-gradient partial sums (the largest layer's, or the head's);
                    // also the 8-cell convolutions' partial sums (wpart_floats floats)
     int64_t wpart_floats;
+    WgradBlocks resident;  // the weight gradient's plans, and so wpart, follow it
     size_t total;
 };
 
@@ -123,13 +124,13 @@ Layout make_layout(const lbm_nn_config& c) {
     }
     L.partial = take(((c0 + 255) / 256) * 8);
     L.loss = take(64);
-    const WgradBlocks resident = wgrad_blocks();
+    L.resident = wgrad_blocks();
     int64_t wpart = 0;
     for (int l = 0; l < kLayers; ++l) {
         const LayerDef& d = kDefs[l];
         const ConvGeom g = make_geom(B, lg0 - d.level, d.taps, d.c1, d.c2, d.cout);
         wpart = std::max(wpart, l == kLayers - 1 ? head_scratch_floats(g)
-                                                 : std::max(wgrad_scratch_floats(g, resident),
+                                                 : std::max(wgrad_scratch_floats(g, L.resident),
                                                             conv_scratch_floats(g)));
     }
     L.wpart = take((size_t)wpart * 4);
@@ -221,7 +222,7 @@ lbm_status backward(lbm_nn* nn, int n) {
         float* dw = grad + nn->off[l];
         float* db = dw + (int64_t)d.cout * d.taps * (d.c1 + d.c2);
         NN_TRY(conv_backward_weight(g, x1, x2, dact(l), nullptr, 0, dw, db,
-                                    nn->at<float>(L.wpart), L.wpart_floats, s),
+                                    L.resident, nn->at<float>(L.wpart), L.wpart_floats, s),
                "weight grad");
         if (l == 0) break;
         // (the weight gradient above has finished with wpart: same stream)
