@@ -500,15 +500,20 @@ __global__ void k_wgrad_reduce(WgradArgs a, int kt, int ct, int nz, int rs, int 
 typedef int intx4 __attribute__((ext_vector_type(4)));
 __device__ __forceinline__ intx4 buffer_words(const void* base, uint32_t bytes) {
     const uint64_t p = (uint64_t)base;
-    return intx4{__builtin_amdgcn_readfirstlane((int)(uint32_t)p),
-                 __builtin_amdgcn_readfirstlane((int)(uint32_t)(p >> 32) & 0xFFFF),
-                 __builtin_amdgcn_readfirstlane((int)bytes), 0x00020000};
+    intx4 words = {__builtin_amdgcn_readfirstlane((int)(uint32_t)p),
+                   __builtin_amdgcn_readfirstlane((int)(uint32_t)(p >> 32) & 0xFFFF),
+                   __builtin_amdgcn_readfirstlane((int)bytes), 0x00020000};
+    // the five wait states a buffer instruction needs after a vector
+    // instruction wrote its descriptor, which the compiler does not count
+    // for an instruction in inline assembly
+    __asm__ volatile("s_nop 4" : "+s"(words));
+    return words;
 }
 __device__ __forceinline__ void copy_to_lds(intx4 rsrc, uint32_t lds, uint32_t off) {
     __asm__ volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds"
                      :
                      : "s"(lds), "v"(off), "s"(rsrc)
-                     : "memory");
+                     : "memory", "m0");
 }
 // Waits until at most `later` of this wave's vector-memory operations are
 // outstanding (they finish in order) and its LDS reads are done, then for the
