@@ -599,7 +599,7 @@ lbm_status lbm_state_info(const lbm_handle* h, const void** F, const void** G,
 
 const char* lbm_step_kernel_name(const lbm_handle* h) {
     if (!h) return "";
-    return step_kernel_name((Prec)h->p.precision, h->p.thermal_q, h->general);
+    return step_kernel_name((Prec)h->p.precision, h->p.thermal_q, h->general, h->geom);
 }
 
 lbm_status lbm_set_block(lbm_handle* h, int32_t bx, int32_t by) {

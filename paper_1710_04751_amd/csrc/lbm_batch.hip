@@ -80,7 +80,7 @@ k_batch_step(const DevCav* __restrict__ cavs, const uint32_t* __restrict__ list,
         if (z >= C.nz) continue;
         uint32_t seed = 0;
         if constexpr (std::is_same<S, _Float16>::value) seed = keys[c] + key_off;
-        update_cell_policy<R, S, QT, HG>(t, keep16, C.stream_loads, (const S*)C.F[parity],
+        update_cell_policy<R, S, QT, HG, sizeof(S) == 2 ? 3 : 7>(t, keep16, C.stream_loads, (const S*)C.F[parity],
                                          (S*)C.F[1 - parity], x, y, z, (int)f.y0, (int)f.z0, C.nx,
                                          C.ny, C.nz, C.pl.gs, coef_of<R>(C), seed);
     }

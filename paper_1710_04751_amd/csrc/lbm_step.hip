@@ -27,6 +27,7 @@
 #include <stdint.h>
 
 #include <algorithm>
+#include <string>
 #include <type_traits>
 
 #include "lbm_dispatch.hpp"
@@ -76,12 +77,12 @@ __device__ __forceinline__ CellPos tile_cell(const Geom& g) {
 }
 
 // Single cavity: one thread per cell, blocks of bx * by cells.
-template <typename R, typename S, int QT, bool HG>
+template <typename R, typename S, int QT, bool HG, int WAYS>
 __global__ void __launch_bounds__(1024)
 k_step(const S* __restrict__ in, S* __restrict__ out, Geom g, KCoef<R> k) {
     const CellPos p = tile_cell(g);
     if (!p.ok) return;
-    update_cell_policy<R, S, QT, HG>(blockIdx.x, g.keep16, g.stream_loads, in, out, p.x, p.y, p.z,
+    update_cell_policy<R, S, QT, HG, WAYS>(blockIdx.x, g.keep16, g.stream_loads, in, out, p.x, p.y, p.z,
                                      p.y0, p.z0, g.nx, g.ny, g.nz, g.gs, k, k.seed);
 }
 
@@ -159,6 +160,12 @@ hipError_t step3_impl(const Geom& g, StateBuf in, StateBuf out, const Coefs& c, 
     return hipGetLastError();
 }
 
+// The cache policies a box's blocks take: update_cell_policy's WAYS.
+int ways_of(const Geom& g) {
+    if (g.keep16 == 16) return 1 << kKeep;
+    return (g.keep16 ? 1 << kKeep : 0) | (g.stream_loads ? 1 << kStreamLoads : 1 << kStream);
+}
+
 template <typename R, typename S, int QT, bool HG>
 hipError_t step_impl(const Geom& g, StateBuf in, StateBuf out, const Coefs& c, hipStream_t s) {
     const KCoef<R> k = make_kcoef<R>(c, QT);
@@ -166,8 +173,23 @@ hipError_t step_impl(const Geom& g, StateBuf in, StateBuf out, const Coefs& c, h
     const int64_t ncell = (int64_t)g.nx * g.ny * g.nz, threads = (int64_t)g.bx * g.by;
     const dim3 grid((unsigned)(g.tiles_x ? (int64_t)g.tiles_x * g.tiles_y * g.nz
                                          : (ncell + threads - 1) / threads), 1, 1);
-    hipLaunchKernelGGL((k_step<R, S, QT, HG>), grid, block, 0, s, (const S*)in.F, (S*)out.F, g,
-                       k);
+    auto launch = [&](auto ways) {
+        hipLaunchKernelGGL((k_step<R, S, QT, HG, decltype(ways)::value>), grid, block, 0, s,
+                           (const S*)in.F, (S*)out.F, g, k);
+    };
+    constexpr int keep = 1 << kKeep, plain = 1 << kStream, loads = 1 << kStreamLoads;
+    switch (ways_of(g)) {
+        case keep: launch(std::integral_constant<int, keep>{}); break;
+        case plain: launch(std::integral_constant<int, plain>{}); break;
+        case keep | plain: launch(std::integral_constant<int, keep | plain>{}); break;
+        default:
+            if constexpr (sizeof(S) > 2) {  // (streams_loads)
+                if (g.keep16 == 0)
+                    launch(std::integral_constant<int, loads>{});
+                else
+                    launch(std::integral_constant<int, keep | loads>{});
+            }
+    }
     return hipGetLastError();
 }
 
@@ -202,15 +224,22 @@ hipError_t launch_step3(Prec p, int qt, bool general, const Geom& g, StateBuf in
     }
 }
 
-const char* step_kernel_name(Prec p, int qt, bool general) {
-    static const char* names[3][2][2] = {
-        {{"lbm::kern::k_step<double, double, 7, false>", "lbm::kern::k_step<double, double, 7, true>"},
-         {"lbm::kern::k_step<double, double, 15, false>", "lbm::kern::k_step<double, double, 15, true>"}},
-        {{"lbm::kern::k_step<float, float, 7, false>", "lbm::kern::k_step<float, float, 7, true>"},
-         {"lbm::kern::k_step<float, float, 15, false>", "lbm::kern::k_step<float, float, 15, true>"}},
-        {{"lbm::kern::k_step<float, _Float16, 7, false>", "lbm::kern::k_step<float, _Float16, 7, true>"},
-         {"lbm::kern::k_step<float, _Float16, 15, false>", "lbm::kern::k_step<float, _Float16, 15, true>"}}};
-    return names[(int)p][qt == 15][general ? 1 : 0];
+const char* step_kernel_name(Prec p, int qt, bool general, const Geom& g) {
+    struct Names {
+        std::string of[3][2][2][8];  // precision, lattice, collision, ways
+        Names() {
+            const char* types[3] = {"double, double", "float, float", "float, _Float16"};
+            for (int t = 0; t < 3; ++t)
+                for (int q = 0; q < 2; ++q)
+                    for (int c = 0; c < 2; ++c)
+                        for (int w = 0; w < 8; ++w)
+                            of[t][q][c][w] = std::string("lbm::kern::k_step<") + types[t] +
+                                             (q ? ", 15, " : ", 7, ") + (c ? "true, " : "false, ") +
+                                             std::to_string(w) + ">";
+        }
+    };
+    static const Names names;
+    return names.of[(int)p][qt == 15][general ? 1 : 0][ways_of(g)].c_str();
 }
 
 }  // namespace lbm

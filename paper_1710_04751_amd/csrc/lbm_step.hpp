@@ -300,6 +300,12 @@ __device__ __forceinline__ void put_cell(const idx::Window& w, const idx::CellAt
     for (int a = 0; a < QT; ++a) st(idx::store_at(w, c, 15 + a), gq[a]);
 }
 
+// v, in a form the compiler cannot relate to what v was computed from.
+__device__ __forceinline__ int opaque(int v) {
+    __asm__ volatile("" : "+v"(v));
+    return v;
+}
+
 // (z0, y0): the first row of the block's cells, the same for all of them.
 // seed: the step index keying stochastic rounding (FP16 storage with k.sr).
 // POL: the block's cache policy (Policy).
@@ -313,7 +319,11 @@ __device__ __forceinline__ void update_cell(const S* __restrict__ in, S* __restr
     const idx::Window w = idx::window_of(z0, y0, nxi, nyi, nzi, gs, 15 + QT, (int)sizeof(S));
     const __amdgpu_buffer_rsrc_t ri = pop_rsrc(in + (size_t)w.g0 * w.glen, w.bytes);
     const __amdgpu_buffer_rsrc_t ro = pop_rsrc(out + (size_t)w.g0 * w.glen, w.bytes);
-    const idx::CellAt c = idx::cell_at(w, x, y, z, nxi, nyi, nzi);
+    idx::CellAt c = idx::cell_at(w, x, y, z, nxi, nyi, nzi);
+    // FP64: the stores' offsets follow from one register kept over the
+    // collision, not from partial results of the loads' (D3Q15 with a source
+    // would spill: 256^3 1330 us a step, 1310 so; FP32 and FP16 lose by it)
+    if constexpr (sizeof(R) == 8) c.own = (uint32_t)opaque((int)c.own);
     R d[15], gq[QT];
     gather_collide<R, QT, HG>(w, c, [&](uint32_t i) __attribute__((always_inline)) {
         return Buf<S>::template ld<R, POL>(ri, i); }, k, d, gq);
@@ -322,33 +332,41 @@ __device__ __forceinline__ void update_cell(const S* __restrict__ in, S* __restr
         ((uint32_t)z * w.ny + (uint32_t)y) * w.nx + (uint32_t)x, d, gq);
 }
 
-// update_cell under the block's cache policy; b: the block's number,
-// stream_loads: streams_loads of the box.  Each branch takes its own opaque
-// copy of x: otherwise the compiler computes what the branches have in common
-// before them and holds it in registers (FP64 D3Q7 72 instead of 64, D3Q15
-// spilled).
-__device__ __forceinline__ int opaque(int v) {
-    __asm__ volatile("" : "+v"(v));
-    return v;
-}
-template <typename R, typename S, int QT, bool HG>
+// update_cell under the block's cache policy, one of WAYS (1 << PolicyKind
+// each): keeping where keeps(b, keep16), else with the loads that stream_loads
+// names.  A launch names the ways its blocks take, for every further copy of
+// the update behind a branch costs registers.  With more than one way, each
+// copy in FP64 and FP16 takes its own opaque cell, or the compiler computes
+// what the copies share before the branch and holds it in more registers still
+// (FP64 D3Q15 would spill).  FP32 fits either way and is faster without (a
+// batch of 64 members of 16^3 to 40^3 59.2 us a step, 62.2 with).
+template <typename R, typename S, int QT, bool HG, int WAYS>
 __device__ __forceinline__ void update_cell_policy(uint32_t b, uint32_t keep16, int stream_loads,
                                                    const S* __restrict__ in, S* __restrict__ out,
                                                    int x, int y, int z, int y0, int z0, int nx,
                                                    int ny, int nz, int gs, const KCoef<R>& k,
                                                    uint32_t seed) {
-    if (keeps(b, keep16)) {
-        update_cell<R, S, QT, HG, kKeep>(in, out, opaque(x), opaque(y), opaque(z), y0, z0, nx, ny, nz, gs, k, seed);
-        return;
-    }
-    if constexpr (sizeof(S) > 2) {
-        if (stream_loads) {
-            update_cell<R, S, QT, HG, kStreamLoads>(in, out, opaque(x), opaque(y), opaque(z), y0, z0, nx, ny, nz, gs, k,
-                                                    seed);
+    constexpr bool keep = WAYS & 1 << kKeep, plain = WAYS & 1 << kStream,
+                   loads = WAYS & 1 << kStreamLoads;
+    auto update = [&](auto policy) __attribute__((always_inline)) {
+        constexpr bool same = keep + plain + loads == 1 || sizeof(S) == 4;
+        update_cell<R, S, QT, HG, decltype(policy)::value>(in, out, same ? x : opaque(x), same ? y : opaque(y),
+                                                           same ? z : opaque(z), y0, z0, nx, ny, nz, gs,
+                                                           k, seed);
+    };
+    if constexpr (keep) {
+        if ((!plain && !loads) || keeps(b, keep16)) {
+            update(std::integral_constant<int, kKeep>{});
             return;
         }
     }
-    update_cell<R, S, QT, HG, kStream>(in, out, opaque(x), opaque(y), opaque(z), y0, z0, nx, ny, nz, gs, k, seed);
+    if constexpr (loads) {
+        if (!plain || stream_loads) {
+            update(std::integral_constant<int, kStreamLoads>{});
+            return;
+        }
+    }
+    if constexpr (plain) update(std::integral_constant<int, kStream>{});
 }
 
 }  // namespace kern
