@@ -59,6 +59,15 @@ __device__ __forceinline__ void decode_piece(uint32_t d, int& cav, uint32_t& pie
 // active members, and keep_sixteenths of their states.
 enum { kTilesWord, kPiecesWord, kKeepWord };
 
+// The cache policies of a batch's blocks: members that stream load ordinarily,
+// except FP64 D3Q7's.  Non-temporal loads, which single boxes of whole lines
+// gain from, cost a batch (us a step, ordinary / non-temporal, autotuned): 20
+// members of 96^3 FP32 D3Q7 506 / 525, D3Q15 707 / 747, FP64 D3Q15 1430 / 1463;
+// 4 of 192^3 FP32 D3Q7 810 / 838, D3Q15 1151 / 1200; but 12 of 128^3 FP64 D3Q7
+// 1459 / 1420.
+template <typename S, int QT>
+constexpr int kBatchWays = 1 << kKeep | 1 << kStream | (sizeof(S) == 8 && QT == 7 ? 1 << kStreamLoads : 0);
+
 // keys[c] + key_off: member c's step index, the key of its stochastic
 // rounding (FP16 storage), so a member draws the random bits a single run of
 // it draws.  key_off is the step's position within a captured graph (the
@@ -80,7 +89,7 @@ k_batch_step(const DevCav* __restrict__ cavs, const uint32_t* __restrict__ list,
         if (z >= C.nz) continue;
         uint32_t seed = 0;
         if constexpr (std::is_same<S, _Float16>::value) seed = keys[c] + key_off;
-        update_cell_policy<R, S, QT, HG, sizeof(S) == 2 ? 3 : 7>(t, keep16, C.stream_loads, (const S*)C.F[parity],
+        update_cell_policy<R, S, QT, HG, kBatchWays<S, QT>>(t, keep16, C.stream_loads, (const S*)C.F[parity],
                                          (S*)C.F[1 - parity], x, y, z, (int)f.y0, (int)f.z0, C.nx,
                                          C.ny, C.nz, C.pl.gs, coef_of<R>(C), seed);
     }

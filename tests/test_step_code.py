@@ -30,3 +30,13 @@ def test_steps_of_one_policy_keep_their_registers(tmp_path):
         assert int(spilled) == 0, name
         checked += 1
     assert checked >= 24
+
+
+def test_batches_load_ordinarily(tmp_path):
+    """Non-temporal loads cost a batch; only FP64 D3Q7 members use them."""
+    code, _ = compiled("lbm_batch.hip", tmp_path)
+    kernels = re.findall(r"^(\S*k_batch_stepI\S*):(.*?)s_endpgm", code, re.S | re.M)
+    assert len(kernels) == 12
+    for name, body in kernels:
+        nt = re.findall(r"buffer_load_\S+ v\S*, v\d+,.* nt$", body, re.M)
+        assert bool(nt) == ("IddLi7" in name), name
