@@ -195,8 +195,9 @@ void set_geom(lbm_handle* h, int bx, int by) {
     h->geom.tiles_y = tile ? (h->p.ny + by - 1) / by : 0;
     h->geom.mx = idx::small_magic((uint32_t)h->p.nx);
     h->geom.my = idx::small_magic((uint32_t)h->p.ny);
-    h->geom.keep16 = keep_sixteenths(2 * (uint64_t)h->lay.state_bytes);
-    h->geom.stream_loads = streams_loads(h->p.nx, value_bytes((Prec)h->p.precision));
+    const int vb = value_bytes((Prec)h->p.precision);
+    h->geom.keep16 = keep_sixteenths(2 * (uint64_t)h->lay.state_bytes, vb);
+    h->geom.stream_loads = streams_loads(h->p.nx, vb);
     h->geom.gs = h->lay.pl.gs;
 }
 

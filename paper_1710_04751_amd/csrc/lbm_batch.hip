@@ -348,7 +348,7 @@ lbm_status upload_table(lbm_batch* b) {
                            hipMemcpyHostToDevice, b->stream);
     if (e != hipSuccess) return hip_fail(e, "batch table upload");
     hipLaunchKernelGGL(k_batch_compact, dim3(1), dim3(1024), 0, b->stream, b->d_table(),
-                       b->d_active(), b->n, (uint32_t)b->threads, keep_sixteenths(active_bytes),
+                       b->d_active(), b->n, (uint32_t)b->threads, keep_sixteenths(active_bytes, value_bytes(b->prec)),
                        b->d_list(), b->d_counts());
     e = hipGetLastError();
     if (e != hipSuccess) return hip_fail(e, "batch compaction");

@@ -69,10 +69,14 @@ inline bool streams_loads(int64_t nx, int vbytes) {
 // Of 16 blocks of the step, how many leave their results in the 256 MB
 // memory-side cache (Policy, lbm_step.hpp), for states of `bytes` in all (A
 // and B): all of them while everything fits, else the share that holds about
-// 170 MB, none once that is below 1/16.
-inline uint32_t keep_sixteenths(uint64_t bytes) {
+// 170 MB, none once that is below 1/16 (2/16 in FP16, where the registers of
+// the mix cost more than it saves: 256^3 D3Q15 with a source 407 us a step
+// without, 416 with 1/16).
+inline uint32_t keep_sixteenths(uint64_t bytes, int vbytes) {
     constexpr uint64_t MB = 1 << 20;
-    return bytes <= 240 * MB ? 16u : (uint32_t)(16 * 170 * MB / bytes);
+    if (bytes <= 240 * MB) return 16;
+    const uint32_t share = (uint32_t)(16 * 170 * MB / bytes);
+    return vbytes == 2 && share < 2 ? 0 : share;
 }
 
 hipError_t launch_step(Prec p, int qt, bool general, const Geom& g, StateBuf in,
