@@ -322,7 +322,8 @@ lbm_status lbm_gather_cells(lbm_handle* h, const int64_t* cells, int64_t n, doub
 lbm_status lbm_state_info(const lbm_handle* h, const void** F, const void** G,
                           int64_t* pop_stride, int32_t* value_bytes);
 
-/* Name of the kernel of a single step (for profiler summaries). */
+/* Name of the kernel that takes the handle's steps (for profiler summaries):
+ * of a small box's three steps a launch, else of a single step. */
 const char* lbm_step_kernel_name(const lbm_handle* h);
 
 /* Threads per block of the step kernel: set (each a multiple of 64 total,
@@ -330,8 +331,9 @@ const char* lbm_step_kernel_name(const lbm_handle* h);
  * and keep the fastest.  lbm_autotune advances the state by the steps it
  * times (it is meant for warm-up); results: the chosen block_x, block_y.
  * Boxes of few cells (about 24^3 in FP64, 32^3 in FP32 and FP16) take three
- * steps a launch in blocks of their own; the shape set here serves the one or
- * two steps left over. */
+ * steps a launch in blocks of their own, also after lbm_autotune, and the
+ * default or tuned shape serves the one or two steps left over; setting a shape,
+ * here or in lbm_params, makes every step a launch of that shape. */
 lbm_status lbm_set_block(lbm_handle* h, int32_t block_x, int32_t block_y);
 lbm_status lbm_autotune(lbm_handle* h, int32_t steps_per_trial, int32_t* block_x,
                         int32_t* block_y);

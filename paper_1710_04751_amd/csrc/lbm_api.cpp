@@ -241,8 +241,10 @@ lbm_status make_handle(const lbm_params* p, void* workspace, size_t bytes, void*
     h->c.seed = 0;
     h->c.spec = p->scalar_specular;
     int bx = p->block_x, by = p->block_y;
-    if (!bx || !by) default_block(lay.ncell, &bx, &by);
+    const bool shaped = bx && by;
+    if (!shaped) default_block(lay.ncell, &bx, &by);
     set_geom(h, bx, by);
+    h->threes = !shaped && steps_in_threes((Prec)p->precision, h->geom);
     h->owner = nullptr;
     if (hipGetDevice(&h->device) != hipSuccess) h->device = -1;
     *out = h;
@@ -410,7 +412,7 @@ static lbm_status take_steps(lbm_handle* h, int64_t nsteps, bool threes) {
 }
 
 lbm_status lbm_step(lbm_handle* h, int64_t nsteps) {
-    return take_steps(h, nsteps, h && steps_in_threes((Prec)h->p.precision, h->geom));
+    return take_steps(h, nsteps, h && h->threes);
 }
 
 lbm_status lbm_macros(lbm_handle* h, void* rho, void* ux, void* uy, void* uz, void* T, int fp64) {
@@ -600,7 +602,7 @@ lbm_status lbm_state_info(const lbm_handle* h, const void** F, const void** G,
 
 const char* lbm_step_kernel_name(const lbm_handle* h) {
     if (!h) return "";
-    return step_kernel_name((Prec)h->p.precision, h->p.thermal_q, h->general, h->geom);
+    return step_kernel_name((Prec)h->p.precision, h->p.thermal_q, h->general, h->threes, h->geom);
 }
 
 lbm_status lbm_set_block(lbm_handle* h, int32_t bx, int32_t by) {
@@ -608,6 +610,7 @@ lbm_status lbm_set_block(lbm_handle* h, int32_t bx, int32_t by) {
     if (bx <= 0 || by <= 0 || (bx * by) % 64 || bx * by > 1024)
         return fail(LBM_ERR_ARG, "block_x * block_y must be a positive multiple of 64, at most 1024");
     set_geom(h, bx, by);
+    h->threes = false;
     return LBM_OK;
 }
 
@@ -644,6 +647,7 @@ lbm_status lbm_autotune(lbm_handle* h, int32_t steps_per_trial, int32_t* out_bx,
     (void)hipEventDestroy(e0);
     (void)hipEventDestroy(e1);
     set_geom(h, bbx, bby);
+    h->threes = steps_in_threes((Prec)h->p.precision, h->geom);
     if (s != LBM_OK) return s;
     if (e != hipSuccess) return hip_fail(e, "autotune");
     if (out_bx) *out_bx = bbx;

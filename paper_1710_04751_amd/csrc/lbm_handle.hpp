@@ -56,6 +56,7 @@ struct lbm_handle {
     bool snap_valid;
     bool general;
     lbm::Geom geom;
+    bool threes;       // steps go three a launch (small boxes whose block shape nobody set)
     lbm_batch* owner;  // set for members of a batch (the batch steps them)
     int device;        // HIP device current at creation (-1 if unknown)
 

@@ -119,6 +119,6 @@ hipError_t launch_gather_cells(Prec p, int qt, int64_t ncell, PopLay pl, StateBu
                                const int64_t* cells, int64_t n, double* F, double* G,
                                hipStream_t s);
 hipError_t launch_copy(void* dst, const void* src, size_t bytes, hipStream_t s);
-const char* step_kernel_name(Prec p, int qt, bool general, const Geom& g);
+const char* step_kernel_name(Prec p, int qt, bool general, bool threes, const Geom& g);
 
 }  // namespace lbm

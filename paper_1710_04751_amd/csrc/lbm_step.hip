@@ -224,22 +224,22 @@ hipError_t launch_step3(Prec p, int qt, bool general, const Geom& g, StateBuf in
     }
 }
 
-const char* step_kernel_name(Prec p, int qt, bool general, const Geom& g) {
+const char* step_kernel_name(Prec p, int qt, bool general, bool threes, const Geom& g) {
     struct Names {
-        std::string of[3][2][2][8];  // precision, lattice, collision, ways
+        std::string of[3][2][2][8];  // precision, lattice, collision; ways, 0: k_step3
         Names() {
             const char* types[3] = {"double, double", "float, float", "float, _Float16"};
             for (int t = 0; t < 3; ++t)
                 for (int q = 0; q < 2; ++q)
                     for (int c = 0; c < 2; ++c)
                         for (int w = 0; w < 8; ++w)
-                            of[t][q][c][w] = std::string("lbm::kern::k_step<") + types[t] +
-                                             (q ? ", 15, " : ", 7, ") + (c ? "true, " : "false, ") +
-                                             std::to_string(w) + ">";
+                            of[t][q][c][w] = std::string(w ? "lbm::kern::k_step<" : "lbm::kern::k_step3<") +
+                                             types[t] + (q ? ", 15, " : ", 7, ") + (c ? "true" : "false") +
+                                             (w ? ", " + std::to_string(w) + ">" : ">");
         }
     };
     static const Names names;
-    return names.of[(int)p][qt == 15][general ? 1 : 0][ways_of(g)].c_str();
+    return names.of[(int)p][qt == 15][general ? 1 : 0][threes ? 0 : ways_of(g)].c_str();
 }
 
 }  // namespace lbm
