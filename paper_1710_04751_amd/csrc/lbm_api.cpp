@@ -14,6 +14,7 @@
 
 #include "lbm_handle.hpp"
 #include "lbm_index.hpp"
+#include "lbm_units.hpp"
 
 using namespace lbm;
 
@@ -201,6 +202,11 @@ void set_geom(lbm_handle* h, int bx, int by) {
     h->geom.gs = h->lay.pl.gs;
 }
 
+static bool threes_by_rule(const lbm_handle* h) {
+    return steps_in_threes((Prec)h->p.precision, h->p.thermal_q, h->general, h->p.round_stochastic,
+                           h->p.scalar_specular, h->geom, compute_units());
+}
+
 lbm_status make_handle(const lbm_params* p, void* workspace, size_t bytes, void* stream,
                        lbm_handle** out) {
     std::string why;
@@ -244,7 +250,7 @@ lbm_status make_handle(const lbm_params* p, void* workspace, size_t bytes, void*
     const bool shaped = bx && by;
     if (!shaped) default_block(lay.ncell, &bx, &by);
     set_geom(h, bx, by);
-    h->threes = !shaped && steps_in_threes((Prec)p->precision, h->geom);
+    h->threes = !shaped && threes_by_rule(h);
     h->owner = nullptr;
     if (hipGetDevice(&h->device) != hipSuccess) h->device = -1;
     *out = h;
@@ -647,7 +653,7 @@ lbm_status lbm_autotune(lbm_handle* h, int32_t steps_per_trial, int32_t* out_bx,
     (void)hipEventDestroy(e0);
     (void)hipEventDestroy(e1);
     set_geom(h, bbx, bby);
-    h->threes = steps_in_threes((Prec)h->p.precision, h->geom);
+    h->threes = threes_by_rule(h);
     if (s != LBM_OK) return s;
     if (e != hipSuccess) return hip_fail(e, "autotune");
     if (out_bx) *out_bx = bbx;

@@ -83,7 +83,51 @@ hipError_t launch_step(Prec p, int qt, bool general, const Geom& g, StateBuf in,
                        StateBuf out, const Coefs& c, hipStream_t s);
 // Three steps (keyed c.seed, + 1, + 2) in one launch, for boxes where
 // steps_in_threes.
-bool steps_in_threes(Prec p, const Geom& g);
+constexpr int kTripleTile = 4;
+inline int64_t triple_tiles(int64_t n) { return (n + kTripleTile - 1) / kTripleTile; }
+
+// Whether a box goes three steps a launch, on a device of `units` compute
+// units: while every block of k_step3 runs at once, one a unit, or two where two
+// fit and share a unit well.  FP64: one, for its 90-123 KB of LDS.  Two: D3Q7
+// without stochastic rounding; with one of D3Q15 and stochastic rounding (which
+// make the update longer than a launch's latency) while rows are whole tiles and
+// short, so that the blocks' stores share few lines; else one.  Us a step, one
+// a launch / three, 256 units (blocks in brackets):
+//   FP64 24^3 (216) D3Q7 4.17 / 3.48, D3Q15 with a source 5.29 / 4.88, 28^3 (343)
+//     D3Q7 4.36 / 5.75
+//   FP32 D3Q7 32^3 (512) 4.23 / 3.50, with a source 30^3 (512) 4.30 / 4.07, 40^3
+//     (1000) 4.53 / 5.52
+//   FP32 D3Q15 32^3 4.95 / 4.77, 40x28x28 (490) 4.93 / 4.72, but 64x16x32 (512)
+//     5.06 / 5.26, 30^3 4.90 / 5.29, 32^3 with a source 5.12 / 5.20
+//   FP16 D3Q7 stochastic 32^3 3.99 / 3.76, 25^3 (343) 3.92 / 4.32; D3Q15 32^3 4.81
+//     / 4.38, 25^3 4.73 / 4.91; D3Q15 stochastic 32^3 5.08 / 5.35, 24^3 (216) 5.00 /
+//     3.72
+// D3Q15 boxes whose rows end one or two cells into a tile go singly where the
+// blocks are few or a row has 2, 4, 8, .. of them (so that every XCD, which takes
+// each eighth block, always has the same part of the rows) and they are a tile
+// thick in y or, in FP64 and FP16, the update is longer still (a source, specular
+// faces, stochastic rounding): those lose, by time between the blocks' work that
+// the counters do not attribute:
+//   FP64 with a source 13^3 5.30 / 6.26, 13x24x24 5.28 / 5.59, 9^3 5.23 / 6.20, but
+//     12x24x24 5.38 / 4.40, 15x20x24 5.26 / 4.50, 18^3 5.22 / 4.82
+//   FP64 plain 17x4x40 5.10 / 5.57, 13^3 5.20 / 5.27; FP16 stochastic 13^3 5.37 / 5.69
+inline bool steps_in_threes(Prec p, int qt, bool general, bool stochastic, bool specular,
+                            const Geom& g, int units) {
+    const int64_t row = triple_tiles(g.nx), blocks = row * triple_tiles(g.ny) * triple_tiles(g.nz);
+    const int over = g.nx % kTripleTile;
+    if (qt == 15 && (over == 1 || over == 2) && (blocks < 100 || (row & (row - 1)) == 0) &&
+        (g.ny <= kTripleTile || (p != Prec::FP32 && (general || stochastic || specular))))
+        return false;
+    const bool q15 = qt == 15;
+    bool two = false;
+    if (p != Prec::FP64) {
+        if (!q15 && !stochastic)
+            two = true;
+        else if (!(q15 && (stochastic || (general && p == Prec::FP32))))
+            two = g.nx % kTripleTile == 0 && g.nx <= 48;
+    }
+    return blocks <= (two ? 2 : 1) * (int64_t)units;
+}
 hipError_t launch_step3(Prec p, int qt, bool general, const Geom& g, StateBuf in, StateBuf out,
                         const Coefs& c, hipStream_t s);
 hipError_t launch_fill_zero(void* ptr, size_t bytes, hipStream_t s);

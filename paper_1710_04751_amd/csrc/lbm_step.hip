@@ -97,7 +97,7 @@ k_step(const S* __restrict__ in, S* __restrict__ out, Geom g, KCoef<R> k) {
 // Bound by three updates' latency on one or two waves a SIMD.  Us a step, one
 // step a launch -> three: 16^3 FP64 4.0 -> 2.8, FP32 3.75 -> 2.16, FP16 3.97 ->
 // 2.22, FP32 D3Q15 4.7 -> 2.9; 32^3 FP32 4.2 -> 3.5.
-constexpr int kTripleTile = 4, kTripleEdge = 8, kTripleCells = 512;
+constexpr int kTripleEdge = 8, kTripleCells = 512;
 
 template <typename R, typename S, int QT, bool HG>
 __global__ void __launch_bounds__(kTripleCells)
@@ -154,9 +154,9 @@ k_step3(const S* __restrict__ in, S* __restrict__ out, Geom g, KCoef<R> k) {
 template <typename R, typename S, int QT, bool HG>
 hipError_t step3_impl(const Geom& g, StateBuf in, StateBuf out, const Coefs& c, hipStream_t s) {
     const KCoef<R> k = make_kcoef<R>(c, QT);
-    auto tiles = [](int n) { return (unsigned)((n + kTripleTile - 1) / kTripleTile); };
-    hipLaunchKernelGGL((k_step3<R, S, QT, HG>), dim3(tiles(g.nx), tiles(g.ny), tiles(g.nz)),
-                       dim3(kTripleCells), 0, s, (const S*)in.F, (S*)out.F, g, k);
+    const dim3 grid((unsigned)triple_tiles(g.nx), (unsigned)triple_tiles(g.ny),
+                    (unsigned)triple_tiles(g.nz));
+    hipLaunchKernelGGL((k_step3<R, S, QT, HG>), grid, dim3(kTripleCells), 0, s, (const S*)in.F, (S*)out.F, g, k);
     return hipGetLastError();
 }
 
@@ -203,16 +203,6 @@ hipError_t launch_step(Prec p, int qt, bool general, const Geom& g, StateBuf in,
     } else {
         LBM_DISPATCH_PQ(p, qt, return (step_impl<R, S, Q, false>(g, in, out, c, s)));
     }
-}
-
-// While every block of k_step3 runs at once, one a compute unit (256) in FP64,
-// whose 90-123 KB of LDS leave no room for a second, two in FP32 and FP16.  Us
-// a step, one a launch / three: FP64 24^3 (216 blocks) 4.09 / 3.51, D3Q15 5.04 /
-// 4.42, 28^3 (343) 4.36 / 5.75; FP32 32^3 (512) 4.19 / 3.50, D3Q15 4.88 / 4.76,
-// 40^3 (1000) 4.53 / 5.52; FP16 32^3 4.07 / 3.17, 40^3 4.24 / 4.66.
-bool steps_in_threes(Prec p, const Geom& g) {
-    auto tiles = [](int n) { return (int64_t)((n + kTripleTile - 1) / kTripleTile); };
-    return tiles(g.nx) * tiles(g.ny) * tiles(g.nz) <= (p == Prec::FP64 ? 256 : 512);
 }
 
 hipError_t launch_step3(Prec p, int qt, bool general, const Geom& g, StateBuf in, StateBuf out,

@@ -26,9 +26,12 @@
 #include <algorithm>
 #include <atomic>
 
+#include "lbm_units.hpp"
 #include "nn_internal.hpp"
 
 namespace lbmnn {
+
+using lbm::compute_units;
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
@@ -2048,21 +2051,6 @@ hipError_t launch_conv_ks(const ConvArgs& a, int coutp, hipStream_t s) {
     }
 #undef LBMNN_CONV
     return hipGetLastError();
-}
-
-// Compute units of the current device (asked once per device; 256 if the
-// runtime cannot say).
-int compute_units() {
-    static std::atomic<int> known[64];
-    int dev = 0, cus = 0;
-    if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return 256;
-    cus = known[dev].load(std::memory_order_relaxed);
-    if (cus > 0) return cus;
-    if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
-        cus <= 0)
-        return 256;
-    known[dev].store(cus, std::memory_order_relaxed);
-    return cus;
 }
 
 // Bricks of 8 rows (1024 threads) when they give every compute unit one, else
