@@ -128,9 +128,11 @@ bool validate(const lbm_params* p, lbm_lattice* L, std::string* why) {
     }
     const int64_t ncell = (int64_t)p->nx * p->ny * p->nz;
     const int vb = value_bytes((Prec)p->precision);
-    // The step kernel addresses a window of at most 3 ny + 2 rows (the rows
-    // of a tile and one plane plus one row on either side) widened to whole
-    // row groups, with 32-bit byte offsets; cell indices are 32-bit.
+    // A block of the step addresses a window of its own rows and one plane plus
+    // one row on either side, widened to whole row groups, with 32-bit byte
+    // offsets; cell indices are 32-bit.  Its own rows are those of a tile or the
+    // 1024 / nx + 2 that 1024 consecutive cells touch: at most ny, and so 3 ny + 2
+    // rows in all, wherever nx is large enough for the limit to matter.
     const int64_t grp = (int64_t)1 << run_rows_log2(p);
     const uint64_t window = (uint64_t)(3 * (int64_t)p->ny + 2 + 2 * grp) * (15 + p->thermal_q) *
                             (uint64_t)p->nx * (uint64_t)vb;

@@ -1717,7 +1717,6 @@ k_conv_brick(ConvArgs a, int work, int per) {
 #pragma unroll
             for (int i = 0; i < 4; ++i) bias[j][i] = a.bias[cobase + j * 16 + 4 * q + i];
     }
-    const float floor = a.relu ? 0.f : -INFINITY;
     auto clear = [&]() __attribute__((always_inline)) {
 #pragma unroll
         for (int m = 0; m < 4; ++m)
@@ -1821,7 +1820,7 @@ k_conv_brick(ConvArgs a, int work, int per) {
 #pragma unroll
                 for (int i = 0; i < 4; ++i) {
                     float t = acc[m][j][i];
-                    if constexpr (EPI == kBias || EPI == kBiasPool) t = fmaxf(t + bias[j][i], floor);
+                    if constexpr (EPI == kBias || EPI == kBiasPool) t = fmaxf(t + bias[j][i], 0.f);
                     if constexpr (EPI == kMask) {
                         const bf16x4 k = __builtin_bit_cast(bf16x4, mask[m * NSUB + j]);
                         t = (float)k[i] > 0.f ? t : 0.f;
@@ -2062,16 +2061,22 @@ hipError_t launch_conv_wy(const ConvArgs& a, int groups, int64_t bricks, hipStre
     const int64_t per = (bricks + most - 1) / most;
     const dim3 grid((unsigned)((bricks + per - 1) / per), groups), block(64 * kCvPlanes * WY);
     const int w = (int)bricks, p = (int)per;
-    if (a.low && a.bias)
-        hipLaunchKernelGGL((k_conv_brick<NSUB, WY, ONE, kBiasPool>), grid, block, 0, s, a, w, p);
-    else if (a.low)
+    if (a.low && !a.bias) {
         hipLaunchKernelGGL((k_conv_brick<NSUB, WY, ONE, kUp>), grid, block, 0, s, a, w, p);
-    else if (a.omask)
-        hipLaunchKernelGGL((k_conv_brick<NSUB, WY, ONE, kMask>), grid, block, 0, s, a, w, p);
-    else if (a.bias)
-        hipLaunchKernelGGL((k_conv_brick<NSUB, WY, ONE, kBias>), grid, block, 0, s, a, w, p);
-    else
-        hipLaunchKernelGGL((k_conv_brick<NSUB, WY, ONE, kPlain>), grid, block, 0, s, a, w, p);
+    } else if constexpr (NSUB < 3) {
+        if (a.low)
+            hipLaunchKernelGGL((k_conv_brick<NSUB, WY, ONE, kBiasPool>), grid, block, 0, s, a, w, p);
+        else if (a.omask)
+            hipLaunchKernelGGL((k_conv_brick<NSUB, WY, ONE, kMask>), grid, block, 0, s, a, w, p);
+        else if (a.bias)
+            hipLaunchKernelGGL((k_conv_brick<NSUB, WY, ONE, kBias>), grid, block, 0, s, a, w, p);
+        else if constexpr (!ONE)
+            hipLaunchKernelGGL((k_conv_brick<NSUB, WY, ONE, kPlain>), grid, block, 0, s, a, w, p);
+        else  // (every layer of at most 16 output channels masks its input gradient)
+            return hipErrorInvalidValue;
+    } else {  // (three groups: launch_conv_brick)
+        return hipErrorInvalidValue;
+    }
     return hipGetLastError();
 }
 
@@ -2082,22 +2087,24 @@ hipError_t launch_conv_wy(const ConvArgs& a, int groups, int64_t bricks, hipStre
 bool conv_brick_covers(const ConvArgs& a, int coutp) {
     return a.taps == 27 && a.lg >= 4 && a.kpad >= 27 * a.cin &&
            (a.cin % 16 == 0 || (a.cin == 8 && a.c2 == 0)) && (a.c2 == 0 || a.c1s % 16 == 0) &&
-           a.cout == coutp && a.ys == coutp && !(a.omask && a.bias) && (a.bias || !a.relu);
+           a.cout == coutp && a.ys == coutp && !(a.omask && a.bias) && !a.bias == !a.relu;
 }
 
 hipError_t launch_conv_brick(const ConvArgs& args, int coutp, hipStream_t s) {
     ConvArgs a = args;
     a.wrows = coutp;
     const int sub = coutp / 16;
+    const bool up = a.low && !a.bias;
     const int64_t G = (int64_t)1 << a.lg, tall = a.n * (G / 16) * (G / 8) * (G / kCvPlanes);
     if (a.cin <= 16) {
-        // three output groups share a step's halo where they are what there is
-        if (sub % 3 == 0 && tall * (sub / 3) >= compute_units())
+        // three output groups share a step's halo in the gradients of
+        // concatenated inputs (48, 96, 192 channels)
+        if (up && sub % 3 == 0 && tall * (sub / 3) >= compute_units())
             return launch_conv_wy<3, 2, true>(a, sub / 3, tall, s);
         if (tall * sub >= compute_units()) return launch_conv_wy<1, 2, true>(a, sub, tall, s);
         return launch_conv_wy<1, 1, true>(a, sub, 2 * tall, s);
     }
-    if (sub % 3 == 0 && 2 * tall * (sub / 3) >= compute_units())
+    if (up && sub % 3 == 0 && 2 * tall * (sub / 3) >= compute_units())
         return launch_conv_wy<3, 1, false>(a, sub / 3, 2 * tall, s);
     if (tall * sub >= compute_units()) return launch_conv_wy<1, 2, false>(a, sub, tall, s);
     return launch_conv_wy<1, 1, false>(a, sub, 2 * tall, s);
