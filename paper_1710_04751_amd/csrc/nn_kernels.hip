@@ -28,6 +28,7 @@
 
 #include "lbm_units.hpp"
 #include "nn_internal.hpp"
+#include "nn_wgrad_index.hpp"
 
 namespace lbmnn {
 
@@ -577,8 +578,6 @@ __device__ __forceinline__ void copies_landed() {
 // (few bricks a block), 14.6 -> 15.5.
 constexpr int kWtWaves = 9;                    // k_wgrad_small
 constexpr int kWgWaves = 16;                   // k_wgrad_tr: 12 for the products, 4 for the copies
-constexpr int kWtHaloRow = 20;                 // voxels per LDS halo row (18 + 2 padding)
-constexpr int kWtPlaneItems = 256;             // 16-byte items per plane slot: 6 rows, padding
 typedef short shortx4 __attribute__((ext_vector_type(4)));
 typedef __attribute__((address_space(3))) shortx4* lds_shortx4_ptr;
 
@@ -589,28 +588,13 @@ __device__ __forceinline__ bf16x8 tr_fragment(const char* lds, uint32_t byte0, u
 }
 
 template <int RS>
-struct WgShape {
-    static constexpr int dy_row = RS == 1 ? 40 : 66;   // 16-byte items per output-gradient row (padded)
-    static constexpr int dy_items = 16 * dy_row;       // 4 planes x 4 rows
-    static constexpr int dy_buf = (dy_items + 63) / 64 * 64;
-    static constexpr int dy_copies = dy_buf / 64;
-    static constexpr int dy_it = (dy_copies + 1) / 2;  // per copying wave, at most
-    static constexpr int dy_min = dy_copies / 2;       // and at least
-    static constexpr int ahead = RS == 1 ? 4 : 3;      // bricks copied ahead
-    static constexpr int ring = 6 + 4 * ahead;         // plane slots
-    static constexpr int halo = ring * kWtPlaneItems;
-    static constexpr int lds_items = halo + (ahead + 1) * dy_buf;
-    static_assert(lds_items * 16 <= 160 * 1024, "one block's LDS");
-};
-
-template <int RS>
 __global__ void __launch_bounds__(64 * kWgWaves) k_wgrad_tr(WgradArgs a, int64_t bricks_per_block) {
     using W = WgShape<RS>;
     __shared__ __attribute__((aligned(16))) __bf16 set[W::lds_items * 8];
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int r = lane & 15, q = lane >> 4;
-    const int lg = a.lg, G = 1 << lg;
+    const int lg = a.lg;
     // XCD-grouped order: the dispatcher deals consecutive blocks to the 8 XCDs
     // in turn, so logical block (lin mod 8) (total / 8) + lin / 8 puts runs of
     // consecutive (range, channel group) pairs on one XCD: the channel groups
@@ -620,104 +604,63 @@ __global__ void __launch_bounds__(64 * kWgWaves) k_wgrad_tr(WgradArgs a, int64_t
     const uint32_t lblk = total % 8 ? lin : (lin % 8) * (total / 8) + lin / 8;
     const int chunk = (int)(lblk % gridDim.x), grp = (int)(lblk / gridDim.x);
     const int c0 = chunk * 16, co0 = (int)blockIdx.z * RS * 16;
-    const int nbx = G >> 4, nby = G >> 2, nbz = G >> 2;
-    const int nbricks = a.n * nbz * nby * nbx;
+    const int nbricks = a.n << (3 * lg - 8);
     const int per = (int)bricks_per_block;
     const int b0 = grp * per, b1 = b0 + per < nbricks ? b0 + per : nbricks;
-    const int h = lg - 1;
     const bool lo = c0 < a.c1s;  // the group's channels lie in x1 (else x2; c1s is then a multiple of 16)
     const int chans = lo ? a.c1s : a.c2;
-    const int hl = lo ? lg : h, sh = lo ? 0 : 1;
     const int cloc = lo ? c0 : c0 - a.c1s;
-    const int64_t sample_x = (int64_t)chans << (3 * hl), sample_d = (int64_t)a.ys << (3 * lg);
+    const int64_t sample_x = (int64_t)chans << (3 * (lo ? lg : lg - 1)), sample_d = (int64_t)a.ys << (3 * lg);
     const __bf16 *xin = lo ? a.x1 : a.x2, *dyin = a.dy;
     __asm__ volatile("" : "+s"(xin), "+s"(dyin));  // held in scalars, not fetched again each brick
-    // Waves 12 and 13 copy the halo (items 128 (w % 2) .. + 127 of each plane:
-    // slot t / 2 of 20 x 6, channel half t % 2), waves 14 and 15 the output
-    // gradient in turn (item t: row t / dy_row, 4 plane + row; voxel and 8
-    // channels of item t % dy_row).  Decoded once: from: the item's byte from
-    // the brick's first halo row (of the output gradient: its first voxel);
-    // side: the sides of the halo it lies on, 64 for padding, channel halves
-    // past the input and channels past ys, 128 in all (for a plane outside the
-    // grid).  Items that read zeros take offsets with bit 31 set (samples are
-    // below 2^31 bytes): past the buffer's end.
-    constexpr uint32_t kOutside = 0x80000000u;
+    // Waves 12 and 13 copy the halo (items 128 (w % 2) .. + 127 of each plane),
+    // waves 14 and 15 the output gradient in turn; a lane's items are decoded
+    // once (nn_wgrad_index.hpp).
     const int copier = wave - 12;
-    uint32_t from[W::dy_it], side[2] = {0, 0};
+    uint32_t dyfrom[W::dy_it];
+    WgHaloItem item[2] = {};
     if (copier == 0 || copier == 1) {
 #pragma unroll
-        for (int i = 0; i < 2; ++i) {
-            const int t = copier * 128 + i * 64 + lane, half = t & 1, hv = t >> 1;
-            const int hx = hv % kWtHaloRow, hy = hv / kWtHaloRow;
-            const bool never = hy >= 6 || hx >= 18 || c0 + half * 8 >= a.cin;
-            const int v = lo ? (hy << lg) + hx : ((hy + 1) >> 1 << h) + ((hx + 1) >> 1);
-            from[i] = (uint32_t)(v * chans + cloc + half * 8) * 2u;
-            side[i] = (uint32_t)((hx == 0) | (hx == 17) << 1 | (hy == 0) << 2 | (hy == 5) << 3 |
-                                 never << 6 | 128);
-        }
+        for (int i = 0; i < 2; ++i)
+            item[i] = wg_halo_item(copier * 128 + i * 64 + lane, lo, lg, chans, cloc, c0 + 8 < a.cin);
     } else if (copier > 1) {
 #pragma unroll
-        for (int i = 0; i < W::dy_it; ++i) {
-            const int t = (2 * i + copier - 2) * 64 + lane;
-            const int row = t / W::dy_row, it = t - row * W::dy_row;
-            const int px = it / (2 * RS), co = co0 + (it % (2 * RS)) * 8;
-            const int v = ((row >> 2) << (2 * lg)) + ((row & 3) << lg) + px;
-            const bool ok = t < W::dy_items && px < 16 && co < a.ys;
-            from[i] = ok ? (uint32_t)(v * a.ys + co) * 2u : kOutside;
-        }
+        for (int i = 0; i < W::dy_it; ++i)
+            dyfrom[i] = wg_dy_item<RS>((2 * i + copier - 2) * 64 + lane, lg, a.ys, co0);
     }
     const uint32_t lds0 = (uint32_t)(uintptr_t)(lds_void_ptr)&set[0];
-    auto negative = [](int v) { return (uint32_t)v >> 31; };
-    auto slot = [](int s) { return s >= W::ring ? s - W::ring : s; };  // s < 2 ring
-    // The copies of brick b (z fastest, then x, y, sample: powers of two): the
-    // halo planes from z0 - 1 + p0 on into the slots from `to` on (p0: 0, or 2
-    // for a brick that follows its z neighbour), the output gradient into
-    // buffer buf.
+    // The copies of brick b: the halo planes from z0 - 1 + p0 on into the slots
+    // from `to` on (p0: 0, or 2 for a brick that follows its z neighbour), the
+    // output gradient into buffer buf.
     auto issue = [&](int b, int p0, int to, int buf) __attribute__((always_inline)) {
-        const int z0 = (b & (nbz - 1)) * 4;
-        b >>= lg - 2;
-        const int x0 = (b & (nbx - 1)) * 16;
-        b >>= lg - 4;
-        const int y0 = (b & (nby - 1)) * 4, smp = b >> (lg - 2);
+        const WgBrick o = wg_brick(b, lg);
         if (copier < 2) {
-            const intx4 rx = buffer_words(xin + smp * sample_x, (uint32_t)(sample_x * 2));
-            const uint32_t edges = negative(x0 - 1) | negative(G - 17 - x0) << 1 | negative(y0 - 1) << 2 |
-                                   negative(G - 5 - y0) << 3 | 64u;
-            const int row0 = (((y0 >> sh) - 1) << hl) + (x0 >> sh) - 1;
+            const intx4 rx = buffer_words(xin + o.smp * sample_x, (uint32_t)(sample_x * 2));
+            const uint32_t edges = wg_sides(o, lg);
             for (int p = p0; p < 6; ++p) {
-                const int zz = z0 - 1 + p;
-                const uint32_t sides = edges | (negative(zz) | negative(G - 1 - zz)) << 7;
-                const uint32_t first = (uint32_t)(((zz >> sh) << (2 * hl)) + row0) * (uint32_t)chans * 2u;
+                const int zz = o.z0 - 1 + p;
+                const uint32_t sides = edges | wg_plane_sides(zz, lg);
+                const uint32_t first = wg_plane_first(o, zz, lo, lg, chans);
                 const uint32_t dst =
-                    lds0 + (uint32_t)(slot(to + p - p0) * kWtPlaneItems + copier * 128) * 16u;
+                    lds0 + (uint32_t)(W::slot(to + p - p0) * kWtPlaneItems + copier * 128) * 16u;
 #pragma unroll
-                for (int i = 0; i < 2; ++i) {
-                    const uint32_t v = from[i] + first;
-                    const uint32_t off = side[i] & sides ? kOutside : v;
-                    copy_to_lds(rx, dst + i * 1024, off);
-                }
+                for (int i = 0; i < 2; ++i)
+                    copy_to_lds(rx, dst + i * 1024, wg_halo_offset(item[i], sides, first));
             }
         } else {
-            const intx4 rd = buffer_words(dyin + smp * sample_d, (uint32_t)(sample_d * 2));
-            const uint32_t first = (uint32_t)((z0 << (2 * lg)) + (y0 << lg) + x0) * (uint32_t)a.ys * 2u;
+            const intx4 rd = buffer_words(dyin + o.smp * sample_d, (uint32_t)(sample_d * 2));
+            const uint32_t first = wg_dy_first(o, lg, a.ys);
             const uint32_t dst = lds0 + (uint32_t)(W::halo + buf * W::dy_buf) * 16u;
 #pragma unroll
             for (int i = 0; i < W::dy_it; ++i) {
                 const int c = 2 * i + copier - 2;
                 if (c >= W::dy_copies) continue;
-                const uint32_t off = from[i] + first;
-                copy_to_lds(rd, dst + (uint32_t)c * 1024u, off);
+                copy_to_lds(rd, dst + (uint32_t)c * 1024u, dyfrom[i] + first);
             }
         }
     };
-    // k value 8 q + 4 i + e of a step (i: which piece, e = r / 4) is the voxel
-    // (row 2 rp + q % 2, cell 8 (q / 2) + 4 i + e) of its plane; the lane reads
-    // channels 4 (r % 4) .. + 3 of it
-    const int e = r >> 2, ac = r & 3;
     const int dyw = wave % 3, plane = wave / 3;  // this wave's dy + 1 and plane (waves 0 .. 11)
-    const uint32_t laneA = (uint32_t)(W::halo * 16 + ((q & 1) * W::dy_row + (8 * (q >> 1) + e) * 2 * RS) * 16 +
-                                      ac * 8 + plane * 4 * W::dy_row * 16);
-    const uint32_t laneB = (uint32_t)((((q & 1) + dyw) * kWtHaloRow + 8 * (q >> 1) + e) * 32 + ac * 8);
+    const uint32_t laneA = wg_lane_dy<RS>(lane, plane), laneB = wg_lane_halo(lane, dyw);
     floatx4 acc[3][3][RS];
 #pragma unroll
     for (int z = 0; z < 3; ++z)
@@ -737,8 +680,7 @@ __global__ void __launch_bounds__(64 * kWgWaves) k_wgrad_tr(WgradArgs a, int64_t
         for (int rp = 0; rp < 2; ++rp)
 #pragma unroll
             for (int m = 0; m < RS; ++m) {
-                const uint32_t at = la + 2 * rp * W::dy_row * 16 + m * 32;
-                av[rp][m] = tr_fragment(sb, at, at + 4 * 32 * RS);
+                av[rp][m] = tr_fragment(sb, la + wg_dy_read<RS>(rp, m, 0), la + wg_dy_read<RS>(rp, m, 1));
             }
         if (bias_wave) {
 #pragma unroll
@@ -750,7 +692,7 @@ __global__ void __launch_bounds__(64 * kWgWaves) k_wgrad_tr(WgradArgs a, int64_t
         }
 #pragma unroll
         for (int z = 0; z < 3; ++z) {  // dz + 1: halo plane `plane` + z
-            const uint32_t lb = laneB + (uint32_t)(slot(base + plane + z) * kWtPlaneItems * 16);
+            const uint32_t lb = laneB + (uint32_t)(W::slot(base + plane + z) * kWtPlaneItems * 16);
 #pragma unroll
             for (int rp = 0; rp < 2; ++rp) {
                 typedef uint32_t uintx2 __attribute__((ext_vector_type(2)));
@@ -760,7 +702,7 @@ __global__ void __launch_bounds__(64 * kWgWaves) k_wgrad_tr(WgradArgs a, int64_t
                 for (int i = 0; i < 3; ++i) {
                     const uintx2 d = __builtin_bit_cast(
                         uintx2, __builtin_amdgcn_ds_read_tr16_b64_v4i16(
-                                    (lds_shortx4_ptr)(sb + lb + (2 * rp * kWtHaloRow + 4 * i) * 32)));
+                                    (lds_shortx4_ptr)(sb + lb + wg_halo_read(rp, i))));
                     w[2 * i] = d[0];
                     w[2 * i + 1] = d[1];
                 }
@@ -783,30 +725,26 @@ __global__ void __launch_bounds__(64 * kWgWaves) k_wgrad_tr(WgradArgs a, int64_t
     // A brick's first halo plane is 4 ring slots on from its z neighbour's, 6 on
     // at the start of a column; its slots are free again once the next brick's
     // products start.
-    auto follows = [&](int b) { return b > b0 && (b & (nbz - 1)) != 0; };
+    auto follows = [&](int b) { return wg_follows(b, b0, lg); };
     if (copier >= 0) {
         __builtin_amdgcn_s_setprio(3);  // the next bricks' copies go out before the products' work
-        int next = b0, end = 0, wslot = 0, wbuf = 0;  // next brick, ring position (counting up), slot, buffer
-        int base = 0;                                 // position of the current brick's first plane
+        WgAhead<RS> at(b0);
         for (int b = b0; b < b1; ++b) {
             // copy ahead as far as the ring and the buffers go: once under way,
             // one brick (whose slots the last brick has left)
             auto fill = [&]() __attribute__((always_inline)) {
-                while (next < b1 && next - b <= W::ahead) {
-                    const bool f = follows(next);
+                for (;;) {
+                    const bool f = follows(at.next);
                     const int planes = f ? 4 : 6;
-                    if (end + planes - base > W::ring) break;
-                    issue(next, f ? 2 : 0, wslot, wbuf);
-                    end += planes;
-                    wslot = slot(wslot + planes);
-                    wbuf = wbuf == W::ahead ? 0 : wbuf + 1;
-                    ++next;
+                    if (!at.can(b, b1, planes)) break;
+                    issue(at.next, f ? 2 : 0, at.wslot, at.wbuf);
+                    at.copied(planes);
                 }
             };
             if (b == b0) fill();
             // the brick's copies have landed: later ones of this wave, at least
             // 8 (dy_min) for each brick copied after it, may be outstanding
-            const int later = next - b - 1;
+            const int later = at.next - b - 1;
             if (copier < 2) {
                 if (later >= 4) copies_outstanding<32>();
                 else if (later == 3) copies_outstanding<24>();
@@ -822,15 +760,15 @@ __global__ void __launch_bounds__(64 * kWgWaves) k_wgrad_tr(WgradArgs a, int64_t
             }
             block_barrier();
             if (b > b0) fill();
-            base += follows(b + 1) ? 4 : 6;
+            at.base += follows(b + 1) ? 4 : 6;
         }
     } else {
         int bslot = 0, bbuf = 0;
         for (int b = b0; b < b1; ++b) {
             copies_landed<0>();  // (none of its own: its LDS reads are done)
             products(bslot, bbuf);
-            bslot = slot(bslot + (follows(b + 1) ? 4 : 6));
-            bbuf = bbuf == W::ahead ? 0 : bbuf + 1;
+            bslot = W::slot(bslot + (follows(b + 1) ? 4 : 6));
+            bbuf = W::next_buf(bbuf);
         }
     }
     // The four planes' sums: planes 2 and 3 through LDS to 0 and 1, then 1 to 0.
