@@ -149,9 +149,9 @@ __global__ void __launch_bounds__(64 * KS) k_conv(ConvArgs a) {
     // lane's 8 k values start at kw + 32 KS s.  The fragments of a step are
     // the voxels (8 channels of one tap per lane) and NSUB weight tiles.  The
     // loop body has no branches (a lane outside the grid loads voxel 0 and
-    // takes zeros; a step past the last reloads the last one's addresses with
-    // zero voxels, so its products add 0), so the compiler keeps the loads
-    // ahead of the products and the waits cover only the step in use.
+    // takes zeros; a step past the last takes zero voxels and zero weights, so
+    // its products add 0 whatever the weights are), so the compiler keeps the
+    // loads ahead of the products and the waits cover only the step in use.
     const int kw = q * 8 + 32 * wave;
     const int nst = 32 * wave < a.kpad ? (a.kpad / 32 - 1 - wave) / KS + 1 : 0;  // (kpad: whole steps)
     const float icin = 1.f / (float)a.cin;
@@ -179,7 +179,7 @@ __global__ void __launch_bounds__(64 * KS) k_conv(ConvArgs a) {
         for (int i = 0; i < 8; ++i) av[i] = ok ? v[i] : (__bf16)0.f;
 #pragma unroll
         for (int j = 0; j < NSUB; ++j)
-            bv[j] = *(const bf16x8*)(a.w + (int64_t)(cobase + j * 16 + r) * a.kpad + k);
+            bv[j] = live ? *(const bf16x8*)(a.w + (int64_t)(cobase + j * 16 + r) * a.kpad + k) : bf16x8{};
     };
     // bit t: tap t of this voxel lies in the grid
     uint32_t inside = 0;
@@ -230,7 +230,7 @@ __global__ void __launch_bounds__(64 * KS) k_conv(ConvArgs a) {
         av = __builtin_bit_cast(bf16x8, v);
 #pragma unroll
         for (int j = 0; j < NSUB; ++j) {
-            const uint32_t o = wbase + (uint32_t)(j * 16 * a.kpad + k) * 2u;
+            const uint32_t o = wbase + (live ? (uint32_t)(j * 16 * a.kpad + k) * 2u : 0x80000000u);
             bv[j] = __builtin_bit_cast(bf16x8, __builtin_amdgcn_raw_buffer_load_b128(rw, o, 0, 0));
         }
     };
