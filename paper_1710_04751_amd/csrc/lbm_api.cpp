@@ -391,7 +391,8 @@ lbm_status lbm_init_macros(lbm_handle* h, const float* ux, const float* uy, cons
     // the partial ones
     hipError_t e = launch_init_macros((Prec)h->p.precision, h->p.thermal_q, h->geom, h->lay.pl,
                                       h->buf(0), ux, uy, uz, T, h->red() + 10, h->nu_hot(),
-                                      (int64_t)2 * h->p.ny * h->p.nz, h->c, h->stream);
+                                      (int64_t)((h->lay.off_red - h->lay.off_nu) / sizeof(double)), h->c,
+                                      h->stream);
     if (e != hipSuccess) return hip_fail(e, "init_macros");
     h->cur = 0;
     h->steps = 0;

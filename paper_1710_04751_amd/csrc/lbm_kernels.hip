@@ -28,9 +28,11 @@ __global__ void k_fill_zero(uint4* __restrict__ p, size_t n16) {
 
 // Staggered sums of an initial state: sum (-1)^x ux, sum (-1)^y uy,
 // sum (-1)^z uz and sum (-1)^z (T - T_ref), FP64, in a fixed order and without
-// atomics: each block adds the rows its waves walk (wave w of the grid takes
-// rows w, w + waves, ...; lane l the cells l, l + 64, ...) and writes four
-// partial sums, which k_stagger_total adds up.  Bound by reading the fields
+// atomics: each block adds the pieces its waves walk (a piece is a row, or 1024
+// cells of a longer one; wave w of the grid takes pieces w, w + waves, ...; lane
+// l the cells l, l + 64, ...) and writes four partial sums, which k_stagger_total
+// adds up.  (With whole rows the 16 of a 100000 x 4 x 4 box gave 16 waves work: a
+// start 1690 us, 336 with the atomics.)  Bound by reading the fields
 // once.  One block per 256 cells adding into four shared words by FP64 atomics
 // had been bound by those: 397 us at 128^3 (25 ms at 512^3) against
 // about 18 us for the two kernels (a whole start at 128^3, with the projection
@@ -40,26 +42,31 @@ __device__ __forceinline__ double wave_add(double v) {
     return v;
 }
 
-constexpr int kStagWaves = 4;  // waves per block
+constexpr int kStagWaves = 4;     // waves per block
+constexpr int kStagPiece = 1024;  // cells of a piece (even: a lane's x keeps its parity)
 
 __global__ void __launch_bounds__(64 * kStagWaves)
 k_stagger_sums(const float* __restrict__ ux, const float* __restrict__ uy,
                const float* __restrict__ uz, const float* __restrict__ T, double T_ref, Geom g,
                double* __restrict__ part) {
     __shared__ double red[kStagWaves][4];
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const uint32_t rows = (uint32_t)g.ny * (uint32_t)g.nz;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const uint32_t per_row = (uint32_t)(g.nx + kStagPiece - 1) / kStagPiece;
+    const uint32_t pieces = (uint32_t)g.ny * (uint32_t)g.nz * per_row;
     // the loops run over lane and row strides whose x parity is the lane's
     const double sx = (lane & 1) ? -1.0 : 1.0;
     double a[4] = {0.0, 0.0, 0.0, 0.0};
-    for (uint32_t row = blockIdx.x * kStagWaves + wave; row < rows;
-         row += gridDim.x * kStagWaves) {
+    for (uint32_t piece = blockIdx.x * kStagWaves + wave; piece < pieces;
+         piece += gridDim.x * kStagWaves) {
+        const uint32_t row = per_row == 1 ? piece : piece / per_row;
+        const int x0 = (int)(piece - row * per_row) * kStagPiece;
+        const int x1 = x0 + kStagPiece < g.nx ? x0 + kStagPiece : g.nx;
         const uint32_t z = row / (uint32_t)g.ny, y = row - z * (uint32_t)g.ny;
         const double sy = (y & 1) ? -1.0 : 1.0, sz = (z & 1) ? -1.0 : 1.0;
         const int64_t base = (int64_t)row * g.nx;
         double r[4] = {0.0, 0.0, 0.0, 0.0};
 #pragma unroll 4
-        for (int x = lane; x < g.nx; x += 64) {
+        for (int x = x0 + lane; x < x1; x += 64) {
             const int64_t c = base + x;
             if (ux) r[0] += (double)ux[c];
             if (uy) r[1] += (double)uy[c];
@@ -373,10 +380,10 @@ hipError_t launch_init_macros(Prec p, int qt, const Geom& g, PopLay pl, StateBuf
                               double* stag, double* scratch, int64_t scratch_doubles,
                               const Coefs& c, hipStream_t s) {
     const int64_t ncell = (int64_t)g.nx * g.ny * g.nz;
-    // about 8 blocks per compute unit, as many as there are rows and scratch for
-    const int64_t rows = (int64_t)g.ny * g.nz;
+    // about 8 blocks per compute unit, as many as there are pieces and scratch for
+    const int64_t pieces = (int64_t)g.ny * g.nz * ((g.nx + kStagPiece - 1) / kStagPiece);
     const int blocks = (int)std::max<int64_t>(
-        1, std::min<int64_t>({2048, (rows + kStagWaves - 1) / kStagWaves, scratch_doubles / 4}));
+        1, std::min<int64_t>({2048, (pieces + kStagWaves - 1) / kStagWaves, scratch_doubles / 4}));
     hipLaunchKernelGGL(k_stagger_sums, dim3(blocks), dim3(64 * kStagWaves), 0, s, ux, uy, uz, T,
                        c.T_ref, g, scratch);
     hipError_t e = hipGetLastError();
