@@ -25,9 +25,9 @@
 #include <hip/hip_runtime.h>
 #include <math.h>
 #include <stdint.h>
+#include <stdio.h>
 
 #include <algorithm>
-#include <string>
 #include <type_traits>
 
 #include "lbm_dispatch.hpp"
@@ -76,7 +76,8 @@ __device__ __forceinline__ CellPos tile_cell(const Geom& g) {
     return c;
 }
 
-// Single cavity: one thread per cell, blocks of bx * by cells.
+// Single cavity: one thread per cell, blocks of bx * by cells.  WAYS: the cache
+// policies the blocks take (update_cell_policy, ways_of).
 template <typename R, typename S, int QT, bool HG, int WAYS>
 __global__ void __launch_bounds__(1024)
 k_step(const S* __restrict__ in, S* __restrict__ out, Geom g, KCoef<R> k) {
@@ -216,20 +217,22 @@ hipError_t launch_step3(Prec p, int qt, bool general, const Geom& g, StateBuf in
 
 const char* step_kernel_name(Prec p, int qt, bool general, bool threes, const Geom& g) {
     struct Names {
-        std::string of[3][2][2][8];  // precision, lattice, collision; ways, 0: k_step3
+        char of[3][2][2][8][56];  // precision, lattice, collision; ways, 0: k_step3
         Names() {
             const char* types[3] = {"double, double", "float, float", "float, _Float16"};
             for (int t = 0; t < 3; ++t)
                 for (int q = 0; q < 2; ++q)
                     for (int c = 0; c < 2; ++c)
-                        for (int w = 0; w < 8; ++w)
-                            of[t][q][c][w] = std::string(w ? "lbm::kern::k_step<" : "lbm::kern::k_step3<") +
-                                             types[t] + (q ? ", 15, " : ", 7, ") + (c ? "true" : "false") +
-                                             (w ? ", " + std::to_string(w) + ">" : ">");
+                        for (int w = 0; w < 8; ++w) {
+                            const char ways[] = {',', ' ', (char)('0' + w), 0};
+                            snprintf(of[t][q][c][w], sizeof of[t][q][c][w], "lbm::kern::k_step%s<%s, %d, %s%s>",
+                                     w ? "" : "3", types[t], q ? 15 : 7, c ? "true" : "false",
+                                     w ? ways : "");
+                        }
         }
     };
     static const Names names;
-    return names.of[(int)p][qt == 15][general ? 1 : 0][threes ? 0 : ways_of(g)].c_str();
+    return names.of[(int)p][qt == 15][general ? 1 : 0][threes ? 0 : ways_of(g)];
 }
 
 }  // namespace lbm
